@@ -83,6 +83,61 @@ __device__ __forceinline__ int fast_div(int n, int d, unsigned magic)
     return (int)__umulhi((unsigned)n, magic);
 }
 
+// block -> (worker, split, tile_m, tile_n); false: a block of the rounded-up grid that has no tile
+struct BlockTile { int w, split, tile_m, tile_n; };
+__device__ __forceinline__ bool block_tile(const GemmArgs &p, const unsigned bid, BlockTile &t)
+{
+    // Workgroups go to the eight accelerator dies (XCDs, each with its own L2) in turn, by block index.
+    // With xcd_chunk > 0 the grid is a multiple of 8 and block b works on the logical index
+    // (b % 8) * xcd_chunk + b / 8: each die then owns a run of consecutive tiles, i.e. whole workers,
+    // so that an operand panel shared by the tiles of a worker is fetched into one L2 only.
+    const int tiles = p.tiles_m * p.tiles_n;
+    int id = (int)bid;
+    if (p.xcd_chunk > 0) {
+        id = (id & 7) * p.xcd_chunk + (id >> 3);
+        if (id >= tiles * p.splits * p.P) return false;
+    }
+    int tile, split, w;
+    if (p.die_workers > 0) {
+        // Elastic epilogues read the time-t center tile, which all workers share: with the tiles of a die's workers
+        // interleaved, the die fetches each center tile once instead of once per worker.
+        const int q = (int)(bid >> 3);
+        tile = fast_div(q, p.die_workers, p.magic_die);
+        split = 0;
+        w = (int)(bid & 7) * p.die_workers + (q - tile * p.die_workers);
+    } else {
+        const int rest = fast_div(id, tiles, p.magic_tiles);
+        tile = id - rest * tiles;
+        if (p.splits == 1) {
+            split = 0;
+            w = rest;
+        } else {
+            split = rest % p.splits;
+            w = rest / p.splits;
+        }
+    }
+    int tile_m, tile_n;
+    if (p.band_log2 > 0) {
+        // The blocks a die runs at the same time are a few dozen consecutive tiles of each of its workers.  In
+        // row-major tile order those are one row of tiles: one panel of A and every panel of B, so B is swept
+        // again for each row of tiles, and what streams through the L2 in between (the replica and momentum
+        // tiles of the epilogue) has evicted it by then.  Walking bands of 2^band_log2 tile columns row by row
+        // makes the concurrent tiles a near-square patch that shares a few panels of each operand.
+        const int band = fast_div(tile, p.band_tiles, p.magic_band);
+        const int rem = tile - band * p.band_tiles;
+        tile_m = rem >> p.band_log2;
+        tile_n = (band << p.band_log2) + (rem & ((1 << p.band_log2) - 1));
+    } else {
+        tile_m = fast_div(tile, p.tiles_n, p.magic_tiles_n);
+        tile_n = tile - tile_m * p.tiles_n;
+    }
+    t.w = w;
+    t.split = split;
+    t.tile_m = tile_m;
+    t.tile_n = tile_n;
+    return true;
+}
+
 // Four elements idx0..idx0+3 along the contiguous axis of a row that starts at `row`.
 // Elements at or beyond `lim` read as 0, except index `ones` which reads as 1.
 template <bool VEC>
@@ -133,52 +188,10 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
     float (*Bs)[BK * PITCH_B] = reinterpret_cast<float (*)[BK * PITCH_B]>(lds + 2 * BK * PITCH_A);
     static_assert((2 * BK * PITCH_A) % 4 == 0, "B tiles must stay 16-byte aligned");
 
-    // block -> (worker, split, tile_m, tile_n)
-    // Workgroups go to the eight accelerator dies (XCDs, each with its own L2) in turn, by block index.
-    // With xcd_chunk > 0 the grid is a multiple of 8 and block b works on the logical index
-    // (b % 8) * xcd_chunk + b / 8: each die then owns a run of consecutive tiles, i.e. whole workers,
-    // so that an operand panel shared by the tiles of a worker is fetched into one L2 only.
-    const int tiles = p.tiles_m * p.tiles_n;
-    int id = (int)bid;
-    if (p.xcd_chunk > 0) {
-        id = (id & 7) * p.xcd_chunk + (id >> 3);
-        if (id >= tiles * p.splits * p.P) return;
-    }
-    int tile, split, w;
-    if (p.die_workers > 0) {
-        // Elastic epilogues read the time-t center tile, which all workers share: with the tiles of a die's workers
-        // interleaved, the die fetches each center tile once instead of once per worker.
-        const int q = (int)(bid >> 3);
-        tile = fast_div(q, p.die_workers, p.magic_die);
-        split = 0;
-        w = (int)(bid & 7) * p.die_workers + (q - tile * p.die_workers);
-    } else {
-        const int rest = fast_div(id, tiles, p.magic_tiles);
-        tile = id - rest * tiles;
-        if (p.splits == 1) {
-            split = 0;
-            w = rest;
-        } else {
-            split = rest % p.splits;
-            w = rest / p.splits;
-        }
-    }
-    int tile_m, tile_n;
-    if (p.band_log2 > 0) {
-        // The blocks a die runs at the same time are a few dozen consecutive tiles of each of its workers.  In
-        // row-major tile order those are one row of tiles: one panel of A and every panel of B, so B is swept
-        // again for each row of tiles, and what streams through the L2 in between (the replica and momentum
-        // tiles of the epilogue) has evicted it by then.  Walking bands of 2^band_log2 tile columns row by row
-        // makes the concurrent tiles a near-square patch that shares a few panels of each operand.
-        const int band = fast_div(tile, p.band_tiles, p.magic_band);
-        const int rem = tile - band * p.band_tiles;
-        tile_m = rem >> p.band_log2;
-        tile_n = (band << p.band_log2) + (rem & ((1 << p.band_log2) - 1));
-    } else {
-        tile_m = fast_div(tile, p.tiles_n, p.magic_tiles_n);
-        tile_n = tile - tile_m * p.tiles_n;
-    }
-    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    BlockTile bt;
+    if (!block_tile(p, bid, bt)) return;
+    const int w = bt.w, split = bt.split;
+    const int m0 = bt.tile_m * BM, n0 = bt.tile_n * BN;
     const int k_begin = split * p.k_per_split;
     const int k_end = min(p.K, k_begin + p.k_per_split);
 

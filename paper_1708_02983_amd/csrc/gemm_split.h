@@ -1,0 +1,461 @@
+// Batched fp32 matrix products on the bfloat16 matrix cores, without giving up fp32 accuracy.
+//
+// Every fp32 operand is the exact sum of three bfloat16 numbers, x = h + m + l (h = x rounded to nearest, m = x - h
+// rounded, l = the rest: 8 + 8 + 8 significant bits; exact for |x| >= 2^-110, an error below 2^-133 otherwise).  Of
+// the nine products of two such sums the six that matter are taken,
+//     x*y = hh + (hm + mh) + (mm + hl + lh)      what is left out is below 2^-24 of |x*y|
+// each exact in fp32, accumulated in fp32 by v_mfma_f32_32x32x16_bf16.  The large products hh and the small rest go
+// to two accumulators that meet once at the end, so that a rounding of the large sum happens once per 16 values of k
+// (the fp32 instruction rounds at every one): against 64-bit sums the result is two to three times closer than that
+// of v_mfma_f32_32x32x2_f32 (relative error of a sum of 1 024: 1.9e-7 against 5.7e-7, of 64: 4.9e-8 against 1.4e-7).
+// The bfloat16 instruction has sixteen times the fp32 one's rate, so six of them still leave 2.7 times; the 5.5 vector
+// instructions per operand element that split it run beside the matrix instructions of the same SIMD for free
+// (measured: 24 matrix instructions with six vector instructions behind each take 3 % longer than without).
+// An operand beyond the largest finite bfloat16 (3.39e38) counts as infinite.  An infinity or a NaN makes the small
+// sums NaN; the result then is the sum of the large products alone, which holds what the fp32 product would.
+//
+#pragma once
+#include "gemm_mfma.h"
+
+namespace easgd {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+struct SplitFrag { u32x4 h, m, l; };       // eight values of k: three bfloat16 planes of 16 bytes
+
+// two floats rounded to nearest even, a in the low half
+__device__ __forceinline__ unsigned bf16_pack(float a, float b)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));      // v_cvt_pk_bf16_f32
+}
+
+// The split of eight values in six parts of four to eight independent instructions each (x is used up): a part fits
+// behind one matrix instruction, and no instruction waits for the one before it.
+__device__ __forceinline__ void split_part(int part, f32x8 &x, SplitFrag &f, u32x4 &t)
+{
+    auto low = [](unsigned d) { return __uint_as_float(d << 16); };
+    auto high = [](unsigned d) { return __uint_as_float(d & 0xffff0000u); };
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (part == 0) f.h[e] = bf16_pack(x[2 * e], x[2 * e + 1]);
+        if (part == 1) { f.l[e] = __float_as_uint(low(f.h[e])); t[e] = __float_as_uint(high(f.h[e])); }
+        if (part == 2) { x[2 * e] -= __uint_as_float(f.l[e]); x[2 * e + 1] -= __uint_as_float(t[e]); }
+        if (part == 3) f.m[e] = bf16_pack(x[2 * e], x[2 * e + 1]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if ((part == 3 && e < 2) || (part == 4 && e >= 2)) { f.l[e] = __float_as_uint(low(f.m[e])); t[e] = __float_as_uint(high(f.m[e])); }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if ((part == 4 && e < 2) || (part == 5 && e >= 2)) { x[2 * e] -= __uint_as_float(f.l[e]); x[2 * e + 1] -= __uint_as_float(t[e]); }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (part == 5) f.l[e] = bf16_pack(x[2 * e], x[2 * e + 1]);
+}
+
+__device__ __forceinline__ void split8(f32x8 &x, SplitFrag &f)
+{
+    u32x4 t;
+#pragma unroll
+    for (int part = 0; part < 6; ++part) split_part(part, x, f, t);
+}
+
+// Tile configuration: a block of four wavefronts, WN side by side along n and WK along k, owns a (TM*32) x (WN*32)
+// tile of C; every wavefront owns all TM*32 rows of 32 columns.  A slab is KS steps of sixteen k per wavefront.
+template <int TM, int WN, int WK>
+struct SplitTile {
+    static_assert(WN * WK == 4, "four wavefronts");
+    static constexpr int BM = TM * 32, BN = WN * 32;
+    static constexpr int KS = WK == 1 ? 2 : 1;
+    static constexpr int BK = 16 * WK * KS, K8 = BK / 8;
+    static constexpr int UNITS = BM * K8;                            // (row of A, eight k) pieces of a slab
+    static constexpr int IT = (UNITS + 255) / 256;
+    static constexpr int SLAB_VECS = (BK / 16) * 3 * TM * 64;        // 16-byte vectors of a slab of A in LDS
+    // two slabs, or the sums that the WK wavefronts of a tile exchange at the end
+    static constexpr int EXCHANGE_VECS = WK > 1 ? 4 * TM * 4 * 64 : 0;
+    static constexpr int LDS_VECS = 2 * SLAB_VECS > EXCHANGE_VECS ? 2 * SLAB_VECS : EXCHANGE_VECS;
+};
+
+template <int TM, int WN, int WK, int A_LAYOUT, int B_LAYOUT, int EPI>
+__device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bid, u32x4 *__restrict__ lds)
+{
+    typedef SplitTile<TM, WN, WK> T;
+    constexpr int BM = T::BM, BN = T::BN, BK = T::BK, K8 = T::K8, IT = T::IT, KS = T::KS;
+    BlockTile bt;
+    if (!block_tile(p, bid, bt)) return;
+    const int w = __builtin_amdgcn_readfirstlane(bt.w);
+    const int tile_m = __builtin_amdgcn_readfirstlane(bt.tile_m), tile_n = __builtin_amdgcn_readfirstlane(bt.tile_n);
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, q = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave % WK, wn = wave / WK;
+    const int m0 = tile_m * BM, n0 = tile_n * BN + wn * 32;     // n0: the wavefront's columns
+    const int k_begin = __builtin_amdgcn_readfirstlane(bt.split) * p.k_per_split, k_end = min(p.K, k_begin + p.k_per_split);
+    const float *__restrict__ A = p.A + (size_t)w * p.a_ws;
+    const float *__restrict__ B = p.B + (size_t)w * p.b_ws;
+    const int a_rows = (A_LAYOUT == K_CONTIG) ? p.M : p.a_lim;        // rows that are stored (the ones vector is not)
+
+    // ---- loader geometry ----
+    // Buffer loads: a 32-bit byte offset per lane and a uniform one per load.
+    // A: unit u = tid + it*256 is eight k of one row, k8 = 0..K8-1.  An operand that is contiguous along k is read with
+    // neighbouring lanes along k (whole cache lines of a row), one that is contiguous along m with neighbouring lanes
+    // along m.  In LDS a unit is 16 bytes per plane, at the place where the matrix instruction's lane reads it; for
+    // the first kind the rows of a unit's column are permuted so that its eight lanes write to different banks.
+    auto rsrc = [](const float *base, unsigned elements) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, (int)(4u * elements), 0x00020000);
+    };
+    const auto ab = rsrc(A, (unsigned)(A_LAYOUT == K_CONTIG ? p.M : p.K) * (unsigned)p.lda);
+    const auto bb = rsrc(B, (unsigned)(B_LAYOUT == K_CONTIG ? p.N : p.K) * (unsigned)p.ldb);
+    unsigned a_off[IT];
+    int a_dst[IT], a_k[IT];
+    bool a_one[IT];                                                  // the row of C that multiplies by ones
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int u = tid + it * 256;
+        const int row = (A_LAYOUT == K_CONTIG) ? u / K8 : u % BM, k8 = (A_LAYOUT == K_CONTIG) ? u % K8 : u / BM;
+        const int swz = (A_LAYOUT == K_CONTIG) ? k8 * (8 / K8) : 0;
+        const int m = min(m0 + row, a_rows - 1);
+        a_one[it] = A_LAYOUT == MN_CONTIG && m0 + row == p.a_ones;
+        a_k[it] = 8 * k8;
+        a_off[it] = (A_LAYOUT == K_CONTIG) ? 4u * ((unsigned)m * (unsigned)p.lda + 8u * k8) : 4u * (8u * k8 * (unsigned)p.lda + (unsigned)m);
+        a_dst[it] = ((k8 >> 1) * 3 * TM + (row >> 5)) * 64 + (((row & 31) ^ swz) + 32 * (k8 & 1));
+    }
+    const int bn = min(n0 + l32, p.N - 1);
+    const unsigned b_off = (B_LAYOUT == K_CONTIG) ? 4u * ((unsigned)bn * (unsigned)p.ldb + 8u * q) : 4u * (8u * q * (unsigned)p.ldb + (unsigned)bn);
+
+    struct RawA { f32x8 x[IT]; };
+    struct RawB { f32x8 x[KS]; };
+    auto k8_vec = [](auto rs, unsigned off, unsigned uni, f32x8 &x) {
+        const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, (int)uni, 0);
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off + 16, (int)uni, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { x[e] = __uint_as_float(u[e]); x[4 + e] = __uint_as_float(v[e]); }
+    };
+    // Slabs that lie inside both operands along k are loaded as they are; in the others every element has an address of
+    // its own that is held inside the operand, and is replaced by what it stands for when it is used (cut).
+    const int a_klim = (A_LAYOUT == K_CONTIG) ? min(p.a_lim, k_end) : k_end;
+    const int n_slabs = (k_end - k_begin + BK - 1) / BK;
+    const int n_fast = (a_klim - k_begin) / BK;
+    // what lies at or beyond `lim` along k is zero, or one where the ones vector sits
+    auto cut = [](f32x8 &x, int k, int lim, int ones) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = k + e < lim ? x[e] : (k + e == ones ? 1.f : 0.f);
+    };
+    const int k_ones = (A_LAYOUT == K_CONTIG && p.a_ones < k_end) ? p.a_ones : -1;
+    auto load_a = [&](int slab, auto inner, int it, RawA &r) {
+        const int k0 = k_begin + slab * BK;
+        if (decltype(inner)::value || slab < n_fast) {
+            if (A_LAYOUT == K_CONTIG) k8_vec(ab, a_off[it], 4u * (unsigned)k0, r.x[it]);
+            else
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    r.x[it][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)a_off[it], (int)(4u * (unsigned)(k0 + e) * (unsigned)p.lda), 0));
+        } else if (slab < n_slabs) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const unsigned k = (unsigned)min(k0 + a_k[it] + e, a_klim - 1);
+                const unsigned off = (A_LAYOUT == K_CONTIG) ? a_off[it] - 4u * (unsigned)a_k[it] + 4u * k
+                                                            : a_off[it] + 4u * (k - (unsigned)a_k[it]) * (unsigned)p.lda;
+                r.x[it][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)off, 0, 0));
+            }
+        }
+    };
+    auto load_b_step = [&](int slab, auto inner, int ks, RawB &r) {
+        const int kb = k_begin + slab * BK + 16 * (wk + ks * WK);
+        if (decltype(inner)::value || slab < n_fast) {
+            if (B_LAYOUT == K_CONTIG) k8_vec(bb, b_off, 4u * (unsigned)kb, r.x[ks]);
+            else
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    r.x[ks][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bb, (int)b_off, (int)(4u * (unsigned)(kb + e) * (unsigned)p.ldb), 0));
+        } else if (slab < n_slabs) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const unsigned k = (unsigned)min(kb + 8 * q + e, k_end - 1);
+                const unsigned off = (B_LAYOUT == K_CONTIG) ? b_off - 32u * (unsigned)q + 4u * k : b_off + 4u * (k - 8u * (unsigned)q) * (unsigned)p.ldb;
+                r.x[ks][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bb, (int)off, 0, 0));
+            }
+        }
+    };
+    // the slab that is only partly inside the operands along k
+    auto cut_a = [&](int k0, int it, RawA &r) { cut(r.x[it], k0 + a_k[it], a_klim, k_ones); };
+    auto cut_b = [&](int k0, int ks, RawB &r) { cut(r.x[ks], k0 + 16 * (wk + ks * WK) + 8 * q, k_end, -1); };
+    auto a_here = [&](int it) { return T::UNITS % 256 == 0 || tid + it * 256 < T::UNITS; };
+    auto put_ones = [&](int it, RawA &r) {
+        if (A_LAYOUT == MN_CONTIG) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r.x[it][e] = a_one[it] ? 1.f : r.x[it][e];
+        }
+    };
+    auto store_a = [&](int buf, int it, const SplitFrag &f) {
+        if (!a_here(it)) return;
+        u32x4 *dst = lds + buf * T::SLAB_VECS + a_dst[it];
+        dst[0] = f.h;
+        dst[TM * 64] = f.m;
+        dst[2 * TM * 64] = f.l;
+    };
+
+    f32x16 hi[TM], lo[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) hi[i][r] = lo[i][r] = 0.f;
+    auto mm = [](const u32x4 &x, const u32x4 &y, f32x16 &c) {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
+    };
+    // The fragments of A come from LDS one tile ahead of the products that use them.
+    auto fetch = [&](int buf, int ks, int i, SplitFrag &f) {
+        const int step = wk + ks * WK, k8 = 2 * step + q;
+        const int swz = (A_LAYOUT == K_CONTIG) ? k8 * (8 / K8) : 0;
+        const u32x4 *src = lds + buf * T::SLAB_VECS + (step * 3 * TM + i) * 64 + ((l32 ^ swz) + 32 * q);
+        f.h = src[0];
+        f.m = src[TM * 64];
+        f.l = src[2 * TM * 64];
+    };
+    auto multiply = [&](int part, int i, const SplitFrag &f, const SplitFrag &fb) {
+        if (part == 0) mm(f.l, fb.h, lo[i]);
+        if (part == 1) mm(f.h, fb.h, hi[i]);
+        if (part == 2) mm(f.h, fb.l, lo[i]);
+        if (part == 3) mm(f.m, fb.m, lo[i]);
+        if (part == 4) mm(f.m, fb.h, lo[i]);
+        if (part == 5) mm(f.h, fb.m, lo[i]);
+    };
+
+    // Slab s is multiplied from LDS buffer s % 2, tile by tile and step by step ("items" of six matrix instructions).
+    // The vector instructions that prepare what comes next run between the matrix instructions of an item: the split
+    // of the slab's second step of B, the split of slab s+1 of A on its way to the other LDS buffer, the split of
+    // slab s+1's first step of B.  A raw register is reloaded as soon as it has been split, one slab ahead.
+    constexpr int ITEMS = KS * TM;
+    RawA ra;
+    RawB rb;
+    SplitFrag fb[2];
+    // before the loop: slab 0 is split, the raw registers hold what the loop expects to find (A from slab 1 on; B from
+    // the second step of slab 0 on)
+#pragma unroll
+    for (int u = 0; u < IT; ++u) load_a(0, std::false_type{}, u, ra);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) load_b_step(0, std::false_type{}, ks, rb);
+#pragma unroll
+    for (int u = 0; u < IT; ++u) {
+        SplitFrag f;
+        if (0 >= n_fast) cut_a(k_begin, u, ra);
+        put_ones(u, ra);
+        split8(ra.x[u], f);
+        store_a(0, u, f);
+        load_a(1, std::false_type{}, u, ra);
+    }
+    if (0 >= n_fast) cut_b(k_begin, 0, rb);
+    split8(rb.x[0], fb[0]);
+    load_b_step(1, std::false_type{}, 0, rb);
+    __syncthreads();
+    auto slab = [&](int s, auto parity, auto last_slabs) {
+        constexpr int buf = decltype(parity)::value;
+        constexpr bool LAST = decltype(last_slabs)::value;
+        constexpr std::integral_constant<bool, !LAST> inner{};           // every slab that is loaded here lies inside the operands
+        // fragments of B: step ks of this slab, and where the first step of the next slab goes
+        constexpr int F0 = KS == 1 ? buf : 0, F1 = KS == 1 ? (buf ^ 1) : 0;
+        SplitFrag fa[2], fs[IT];
+        u32x4 t[IT + 1];
+        fetch(buf, 0, 0, fa[0]);
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int ks = it / TM, i = it % TM;
+            if (it + 1 < ITEMS) fetch(buf, (it + 1) / TM, (it + 1) % TM, fa[(it + 1) & 1]);
+            const bool b1 = KS == 2 && it == 0, b0 = it == (KS == 2 ? TM : ITEMS - 1);      // which split of B runs here
+            if (LAST && b1 && s >= n_fast) cut_b(k_begin + s * BK, 1, rb);
+            if (LAST && b0 && s + 1 >= n_fast) cut_b(k_begin + (s + 1) * BK, 0, rb);
+            auto a_unit = [&](int u) { return it == (ITEMS >= 4 ? 1 + u % 2 : 0); };        // which units of A
+#pragma unroll
+            for (int u = 0; u < IT; ++u)
+                if (a_unit(u)) {
+                    if (LAST && s + 1 >= n_fast) cut_a(k_begin + (s + 1) * BK, u, ra);
+                    put_ones(u, ra);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            // a step that lies beyond the K range holds zeros only
+            const bool live = !LAST || k_begin + s * BK + 16 * (wk + ks * WK) < k_end;      // uniform
+#pragma unroll
+            for (int part = 0; part < 6; ++part) {
+                if (live) multiply(part, i, fa[it & 1], fb[ks == 0 ? F0 : 1]);
+                if (b1) split_part(part, rb.x[KS - 1], fb[1], t[IT]);
+                if (b0) split_part(part, rb.x[0], fb[F1], t[IT]);
+#pragma unroll
+                for (int u = 0; u < IT; ++u)
+                    if (a_unit(u)) split_part(part, ra.x[u], fs[u], t[u]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (b1) load_b_step(s + 1, inner, 1, rb);
+            if (b0) load_b_step(s + 2, inner, 0, rb);
+#pragma unroll
+            for (int u = 0; u < IT; ++u)
+                if (a_unit(u)) {
+                    if (!LAST || s + 1 < n_slabs) store_a(buf ^ 1, u, fs[u]);
+                    load_a(s + 2, inner, u, ra);
+                }
+        }
+        __syncthreads();
+    };
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    int s = 0;
+    for (; s + 3 < n_fast; s += 2) {
+        slab(s, even, std::false_type{});
+        slab(s + 1, odd, std::false_type{});
+    }
+    for (; s < n_slabs; s += 2) {
+        slab(s, even, std::true_type{});
+        if (s + 1 >= n_slabs) break;
+        slab(s + 1, odd, std::true_type{});
+    }
+
+    // ---- the two sums meet (the small one is NaN where an operand was not finite: see the head of the file) ----
+    f32x16 acc[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float c = lo[i][r];
+            acc[i][r] = hi[i][r] + (fabsf(c) <= 3.402823466e38f ? c : 0.f);
+        }
+
+    // ---- epilogue ----
+    // Register r of lane l is C[8*(r/4) + 4*q + r%4][l%32] of its 32x32 tile.  Where WK wavefronts share a tile,
+    // wavefront wk finishes the register groups r/4 = wk mod WK; the partial sums of the others come through LDS and
+    // are added in ascending order of k.
+    constexpr bool ELASTIC = (EPI == EPI_ELASTIC || EPI == EPI_ELASTIC_MOM || EPI == EPI_ELASTIC_MOM_BF16);
+    constexpr bool MOM = (EPI == EPI_ELASTIC_MOM);
+    constexpr bool MOM16 = (EPI == EPI_ELASTIC_MOM_BF16);
+    constexpr bool OUT16 = (EPI == EPI_STORE_BF16);
+    constexpr int GROUPS = 4 / WK;                       // register groups a wavefront finishes per tile
+    float val[TM][GROUPS][4];
+    if constexpr (WK > 1) {
+        f32x4 *ex = reinterpret_cast<f32x4 *>(lds) + (size_t)wn * (WK * TM * 4 * 64);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                ex[((wk * TM + i) * 4 + g) * 64 + lane] = f32x4{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int gg = 0; gg < GROUPS; ++gg) {
+                const int g = gg * WK + wk;
+                f32x4 v = ex[(i * 4 + g) * 64 + lane];
+#pragma unroll
+                for (int o = 1; o < WK; ++o) v += ex[((o * TM + i) * 4 + g) * 64 + lane];
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) val[i][gg][rr] = v[rr];
+            }
+    } else {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int gg = 0; gg < GROUPS; ++gg)
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) val[i][gg][rr] = acc[i][4 * gg + rr];
+    }
+    const bool keep = !OUT16 && (!ELASTIC || p.C != nullptr);                         // uniform
+    float *__restrict__ C = keep ? p.C + (size_t)w * p.c_ws + (size_t)bt.split * p.c_ss : nullptr;
+    unsigned short *__restrict__ C16 = OUT16 ? p.C16 + (size_t)w * p.c_ws : nullptr;
+    const float *__restrict__ mask = (EPI == EPI_MASK) ? p.mask + (size_t)w * p.mask_ws : nullptr;
+    float *__restrict__ Wr = ELASTIC ? p.Wt + (size_t)w * p.c_ws : nullptr;
+    float *__restrict__ Vr = MOM ? p.Vt + (size_t)w * p.c_ws : nullptr;
+    unsigned short *__restrict__ Vr16 = MOM16 ? p.Vt16 + (size_t)w * p.c_ws : nullptr;
+    const float *__restrict__ Cc = ELASTIC ? p.center : nullptr;
+    const int n = n0 + l32, nc = min(n, p.N - 1);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int mt = m0 + 32 * i;                                                   // uniform
+        if (mt >= p.M) break;
+        const bool rows_in = mt + 32 <= p.M;
+        auto row = [&](int gg, int rr) { return mt + 8 * (gg * WK + wk) + 4 * q + rr; };
+        float wv[GROUPS][4], cv[GROUPS][4], vv[GROUPS][4], gate[GROUPS][4];
+        unsigned short v16[GROUPS][4];
+        (void)wv; (void)cv; (void)vv; (void)gate; (void)v16;
+        // all loads of the tile first; a lane whose element lies outside C reads the last row or column instead
+#pragma unroll
+        for (int gg = 0; gg < GROUPS; ++gg)
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const int mc = min(row(gg, rr), p.M - 1);
+                if constexpr (ELASTIC) {
+                    const size_t at = (size_t)mc * p.ldc + nc;
+                    wv[gg][rr] = Wr[at];
+                    cv[gg][rr] = Cc[at];
+                    if constexpr (MOM) vv[gg][rr] = Vr[at];
+                    if constexpr (MOM16) v16[gg][rr] = Vr16[at];
+                }
+                if constexpr (EPI == EPI_MASK) gate[gg][rr] = mask[(size_t)mc * p.ldmask + nc];
+            }
+        auto finish = [&](auto checked) {
+#pragma unroll
+            for (int gg = 0; gg < GROUPS; ++gg)
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const int m = row(gg, rr);
+                    const size_t at = (size_t)m * p.ldc + n;
+                    float v = val[i][gg][rr];
+                    if constexpr (MOM16) worker_rule_bf16<true>(wv[gg][rr], v16[gg][rr], v, cv[gg][rr], p.eta, p.rho, p.alpha, p.delta);
+                    else if constexpr (ELASTIC) worker_rule<MOM>(wv[gg][rr], vv[gg][rr], v, cv[gg][rr], p.eta, p.rho, p.alpha, p.delta);
+                    if (EPI == EPI_RELU) v = fmaxf(v, 0.f);
+                    if (EPI == EPI_MASK) v = gate[gg][rr] > 0.f ? v : 0.f;
+                    if (decltype(checked)::value && m >= p.M) continue;
+                    if constexpr (ELASTIC) {
+                        Wr[at] = wv[gg][rr];
+                        if constexpr (MOM) Vr[at] = vv[gg][rr];
+                        if constexpr (MOM16) Vr16[at] = v16[gg][rr];
+                    }
+                    if constexpr (OUT16) C16[at] = bf16_narrow(v);
+                    else if (keep) C[at] = v;
+                }
+        };
+        if (n < p.N) {
+            if (rows_in) finish(std::false_type{});
+            else finish(std::true_type{});
+        }
+    }
+}
+
+// Blocks per compute unit that the registers leave room for.
+template <int TM> constexpr int split_blocks_per_cu() { return TM == 1 ? 4 : TM == 2 ? 3 : 2; }
+
+template <int TM, int WN, int WK, int A_LAYOUT, int B_LAYOUT, int EPI>
+__global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_kernel(GemmArgs p)
+{
+    __shared__ u32x4 lds[SplitTile<TM, WN, WK>::LDS_VECS];
+    if (p.ctr.blocks > 0 && blockIdx.x >= p.ctr.first_block) {         // uniform for the block
+        const size_t b = blockIdx.x - p.ctr.first_block;
+        if (p.ctr.vec) center_rule_block<f32x4>(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
+        else center_rule_block<float>(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
+        return;
+    }
+    split_block<TM, WN, WK, A_LAYOUT, B_LAYOUT, EPI>(p, blockIdx.x, lds);
+}
+
+// The weight-gradient products of two layers in one launch (gemm_pair_kernel's purpose).
+template <int TM, int WN, int WK, int EPI>
+__global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_dw_pair_kernel(GemmArgs p0, GemmArgs p1, unsigned n0)
+{
+    __shared__ u32x4 lds[SplitTile<TM, WN, WK>::LDS_VECS];
+    if (blockIdx.x < n0) split_block<TM, WN, WK, MN_CONTIG, MN_CONTIG, EPI>(p0, blockIdx.x, lds);
+    else split_block<TM, WN, WK, MN_CONTIG, MN_CONTIG, EPI>(p1, blockIdx.x - n0, lds);
+}
+
+// An input-gradient product with the weight-gradient product of a narrow layer, whose few blocks come first: they are a
+// chain of round trips to memory, which the blocks of the other product cover.
+template <int TM, int WN, int WK, int EPI>
+__global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_da_narrow_dw_kernel(GemmArgs da, GemmArgs dw, unsigned n_dw)
+{
+    constexpr int NARROW = gemm_lds_floats<128, 32, 32, MN_CONTIG, MN_CONTIG>() / 4, SPLIT = SplitTile<TM, WN, WK>::LDS_VECS;
+    __shared__ u32x4 lds[NARROW > SPLIT ? NARROW : SPLIT];
+    if (blockIdx.x < n_dw) gemm_block<128, 32, 32, 4, 1, MN_CONTIG, MN_CONTIG, false, EPI>(dw, blockIdx.x, reinterpret_cast<float *>(lds));
+    else split_block<TM, WN, WK, K_CONTIG, K_CONTIG, EPI_MASK>(da, blockIdx.x - n_dw, lds);
+}
+
+}  // namespace easgd

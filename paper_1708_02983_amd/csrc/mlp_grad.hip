@@ -20,7 +20,7 @@
 // kernel of its own), the input-gradient product of a layer runs before its
 // weight-gradient product, and that product applies the worker rule Eq. (1) /
 // Eq. (5),(6) to the layer's slice of every replica in its epilogue.
-#include "gemm_mfma.h"
+#include "gemm_split.h"
 #include "mlp_head.h"
 #include "persistent_round.h"
 #include <mutex>
@@ -238,19 +238,7 @@ static unsigned place_blocks(GemmArgs &a)
     return (unsigned)total;
 }
 
-// Two products of backward propagation in one launch (gemm_pair_kernel).
-// (i) the input-gradient product of layer l (64x64 tiles) with the weight-gradient product of a narrow layer
-//     l+1 (128x32 tile): the few blocks of the second fill wave slots the first leaves idle;
-// (ii) the weight-gradient products of two layers (64x64 tiles both): one launch boundary and one tail less.
-template <int EPI, bool VEC_DW>
-static void launch_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, hipStream_t s)
-{
-    const unsigned n0 = place_blocks<64, 64>(da), n1 = place_blocks<128, 32>(dw);
-    EASGD_LAUNCH((gemm_pair_kernel<64, 64, 32, 2, 2, K_CONTIG, K_CONTIG, true, EPI_MASK,
-                                         128, 32, SPLIT_BK, 4, 1, MN_CONTIG, MN_CONTIG, VEC_DW, EPI>),
-                       dim3(n0 + n1), dim3(256), 0, s, da, dw, n0);
-}
-
+// The weight-gradient products of two layers (64x64 tiles both) in one launch: one launch boundary and one tail less.
 template <int EPI>
 static void launch_pair_dw_dw(GemmArgs d0, GemmArgs d1, hipStream_t s)
 {
@@ -275,51 +263,121 @@ static void launch_tile(const GemmArgs &a_in, bool vec, hipStream_t s)
     else EASGD_LAUNCH((gemm_mfma_kernel<BM, BN, BK, WM, WN, AL, BL, false, EPI, MT>), grid, block, 0, s, a);
 }
 
-// A batch that is not a multiple of 32 rows wastes matrix-core time in 32-row MFMA tiles (b = 100: 128 rows are
-// multiplied, 28 % more than stored).  The 16x16x4 instruction has the same rate, so a block tile of 3, 5 or 7 x 16
-// rows by 128 columns (four wavefronts side by side, 3, 5 or 7 x 2 accumulators each) multiplies 48, 80 or 112
-// rows per tile.  It is chosen for the products whose M is the batch (forward, input gradient) when one of the
-// three heights covers M with fewer rows than 32-row tiles do and still gives every compute unit about two
-// blocks.  Returns that height, or 0.
-static int tile16_rows(int M, int N, int P, int splits)
+// ---- products on the bfloat16 matrix cores (gemm_split.h) ----
+
+// Which tile of gemm_split.h a product takes: rows x columns, or none.
+enum SplitPick { SPLIT_NONE, SPLIT_128x128, SPLIT_64x128, SPLIT_64x64, SPLIT_32x128, SPLIT_32x32 };
+
+static bool split_fits(const GemmArgs &a, bool a_k_contig, bool b_k_contig)
 {
-    if (N <= 32) return 0;
-    long best_rows = (long)((M + 31) / 32) * 32;
-    int best = 0;
-    for (int bm : {112, 80, 48}) {
-        const long rows = (long)((M + bm - 1) / bm) * bm;
-        if (rows < best_rows) {
-            best_rows = rows;
-            best = bm;
-        }
-    }
-    if (best == 0) return 0;
-    return (size_t)((M + best - 1) / best) * ((N + 127) / 128) * splits * P >= (size_t)(2 * num_cus()) ? best : 0;
+    // byte offsets inside an operand of one worker are 32 bits wide
+    const size_t ra = a_k_contig ? a.M : a.K, rb = b_k_contig ? a.N : a.K, lim = (size_t)1 << 30;
+    return (ra + 128) * (size_t)a.lda < lim && (rb + 128) * (size_t)a.ldb < lim;
 }
 
-// Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile.  Otherwise 64x64 blocks (four per
-// compute unit, so that the epilogue of one overlaps the products of the others) unless the caller asks
-// for the large tile and it still gives every compute unit about two blocks: that pays for the long-K
-// forward products, not for the short-K weight gradients with their heavy epilogues.
+// The products whose rows are the minibatch: the largest tile that still gives every compute unit a block.  The smaller
+// the grid, the more a block's own chain of slabs decides, and the more wavefronts share a tile along k (the last two
+// numbers of a tile's name in gemm_split.h).  Measured, us per product, 128x128 / 64x128 / 64x64 / 32x32, and the fp32
+// matrix instruction's best tile (forward: d_in -> d_out, workers, minibatch):
+//   3072->2048, 32, 100   276 / 291 / 359 / 521     365
+//   3072->2048,  8, 256   147 / 150 / 182 / 258     207
+//    784->1024, 16, 128    37 /  27 /  29 /  40      32
+//   1023-> 777,  6,  37    41 /  28 /  21 /  15      48 (no 128-bit loads)
+//    784-> 500,  8,  50    34 /  24 /  17 /  11      18
+static SplitPick split_pick(int M, int N, int P, int splits)
+{
+    const size_t cus = (size_t)num_cus();
+    auto blocks = [&](int bm, int bn) { return (size_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * (size_t)P * (size_t)splits; };
+    if (M > 64 && blocks(128, 128) >= cus) return SPLIT_128x128;
+    if (M > 32 && blocks(64, 128) >= cus) return SPLIT_64x128;
+    if (M > 32 && blocks(64, 64) >= cus) return SPLIT_64x64;
+    if (M <= 32 && blocks(32, 128) >= cus) return SPLIT_32x128;
+    return SPLIT_32x32;
+}
+
+template <int TM, int WN, int WK, int AL, int BL, int EPI>
+static void launch_split(const GemmArgs &a_in, hipStream_t s)
+{
+    GemmArgs a = a_in;
+    size_t total = place_blocks<TM * 32, WN * 32>(a);
+    if (a.ctr.blocks > 0) {
+        a.ctr.first_block = (unsigned)total;
+        total += a.ctr.blocks;
+    }
+    EASGD_LAUNCH((gemm_split_kernel<TM, WN, WK, AL, BL, EPI>), dim3((unsigned)total), dim3(256), 0, s, a);
+}
+
+// Weight gradients: 64x128 tiles when they give every compute unit two blocks, or when the operands rule out the fp32
+// path's 128-bit loads.  Below that the 64x64 fp32 tiles win: their sums are so short that a block is its latency
+// (784 -> 500, 8 workers, minibatch 50: 10.2 us against 9.3; 1024 -> 1024, 16, 128: 39 against 48; 3072 -> 2048, 32, 100:
+// 390 against 420; 1023 -> 777, 6, 37, odd widths: 12.5 against 14.1).
+static bool split_dw(const GemmArgs &a, bool vec)
+{
+    if (options().gemm_tile != 0 || a.N <= 32 || !split_fits(a, false, false)) return false;
+    return !vec || (size_t)((a.M + 63) / 64) * ((a.N + 127) / 128) * (size_t)a.P >= (size_t)(2 * num_cus());
+}
+
+template <int EPI>
+static void launch_split_pair_dw_dw(GemmArgs d0, GemmArgs d1, hipStream_t s)
+{
+    const unsigned n0 = place_blocks<64, 128>(d0), n1 = place_blocks<64, 128>(d1);
+    EASGD_LAUNCH((gemm_split_dw_pair_kernel<2, 4, 1, EPI>), dim3(n0 + n1), dim3(256), 0, s, d0, d1, n0);
+}
+
+// An input-gradient product and the weight-gradient product of a narrow layer in one launch; false: this tile has none.
+template <int EPI>
+static bool launch_split_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, SplitPick pick, hipStream_t s)
+{
+    const unsigned n_dw = place_blocks<128, 32>(dw);
+    if (pick == SPLIT_64x128) {
+        const unsigned n = place_blocks<64, 128>(da);
+        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<2, 4, 1, EPI>), dim3(n + n_dw), dim3(256), 0, s, da, dw, n_dw);
+    } else if (pick == SPLIT_64x64) {
+        const unsigned n = place_blocks<64, 64>(da);
+        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<2, 2, 2, EPI>), dim3(n + n_dw), dim3(256), 0, s, da, dw, n_dw);
+    } else if (pick == SPLIT_32x32) {
+        const unsigned n = place_blocks<32, 32>(da);
+        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<1, 1, 4, EPI>), dim3(n + n_dw), dim3(256), 0, s, da, dw, n_dw);
+    } else return false;
+    return true;
+}
+
+// Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile of the fp32 matrix instruction, everything else the
+// tiles of gemm_split.h (split_pick, split_dw), but for small weight gradients and where EASGD_OPT_GEMM_TILE forces a
+// shape: those take 64x64 blocks of the fp32 instruction (four per compute unit, so that the epilogue of one
+// overlaps the products of the others) or the forced tile.
+// beside: a kernel of another stream has to fit on the chip next to this launch (two 128x128 blocks fill a compute
+// unit's registers, two 64x128 blocks leave a third; both sum in the same order, so the bits are the same).
 template <int AL, int BL, int EPI>
-static void launch_gemm(const GemmArgs &a, bool vec, bool large_ok, hipStream_t s)
+static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, bool beside = false)
 {
     if (a.N <= 32) {
         launch_tile<128, 32, SPLIT_BK, 4, 1, AL, BL, EPI>(a, vec, s);
         return;
     }
-    const size_t big = (size_t)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.splits * a.P;
     long tile = options().gemm_tile;
-    if constexpr (AL == K_CONTIG && (EPI == EPI_NONE || EPI == EPI_RELU || EPI == EPI_MASK)) {
-        int bm16 = (tile == 0) ? tile16_rows(a.M, a.N, a.P, a.splits) : 0;
-        if (tile == 4) bm16 = a.M <= 48 ? 48 : a.M <= 80 ? 80 : 112;    // forced: the smallest height that covers M, else 112
-        if (bm16 == 112) launch_tile<112, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
-        else if (bm16 == 80) launch_tile<80, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
-        else if (bm16 == 48) launch_tile<48, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
-        if (bm16) return;
+    if constexpr (AL == K_CONTIG) {
+        if (tile == 0 && split_fits(a, AL == K_CONTIG, BL == K_CONTIG)) {
+            SplitPick pick = split_pick(a.M, a.N, a.P, a.splits);
+            if (pick == SPLIT_128x128 && beside) pick = SPLIT_64x128;
+            if (pick == SPLIT_128x128) launch_split<4, 4, 1, AL, BL, EPI>(a, s);
+            else if (pick == SPLIT_64x128) launch_split<2, 4, 1, AL, BL, EPI>(a, s);
+            else if (pick == SPLIT_64x64) launch_split<2, 2, 2, AL, BL, EPI>(a, s);
+            else if (pick == SPLIT_32x128) launch_split<1, 4, 1, AL, BL, EPI>(a, s);
+            else launch_split<1, 1, 4, AL, BL, EPI>(a, s);
+            return;
+        }
+        if (tile == 4) {                // the smallest height of the 16-row tiles that covers M, else 112
+            if (a.M <= 48) launch_tile<48, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
+            else if (a.M <= 80) launch_tile<80, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
+            else launch_tile<112, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
+            return;
+        }
+    } else if (split_dw(a, vec)) {
+        launch_split<2, 4, 1, AL, BL, EPI>(a, s);
+        return;
     }
-    if (tile == 4) tile = 0;            // the weight-gradient products have no 16-row form
-    if (tile == 0) tile = (large_ok && big >= (size_t)(2 * num_cus())) ? 1 : 2;
+    if (tile == 0 || tile == 4) tile = 2;   // the weight-gradient products have no 16-row form
     if (tile == 1) launch_tile<128, 128, 16, 2, 2, AL, BL, EPI>(a, vec, s);
     else if (tile == 2) launch_tile<64, 64, 32, 2, 2, AL, BL, EPI>(a, vec, s);
     else launch_tile<128, 64, 32, 2, 2, AL, BL, EPI>(a, vec, s);
@@ -328,19 +386,23 @@ static void launch_gemm(const GemmArgs &a, bool vec, bool large_ok, hipStream_t 
 static inline bool mult4(size_t x) { return (x & 3u) == 0; }
 
 // Whether the launch of a forward product (M x N per worker, P workers, `splits` K splits) leaves room on the
-// chip for extra blocks that do bandwidth-bound work beside it.  Mirrors launch_gemm: the 128x32 and 64x64
-// tiles use few enough registers and LDS for four blocks per compute unit, the 128x128 tile for two, and it
-// is chosen exactly when its blocks already fill those.
-static bool forward_launch_has_room(int M, int N, int P, int splits)
+// chip for extra blocks that do bandwidth-bound work beside it.  Mirrors launch_gemm: blocks per compute unit that the
+// registers and LDS of a tile allow, one of which has to stay free.
+static bool forward_launch_has_room(const GemmArgs &a)
 {
     const size_t cus = (size_t)num_cus();
-    if (N <= 32) return (size_t)((M + 127) / 128) * splits * P <= 3 * cus;
-    long tile = options().gemm_tile;
-    if (tile == 4 || (tile == 0 && tile16_rows(M, N, P, splits) != 0)) return false;
-    const size_t big = (size_t)((M + 127) / 128) * ((N + 127) / 128) * splits * P;
-    if (tile == 0) tile = (big >= 2 * cus) ? 1 : 2;
-    if (tile != 2) return false;
-    return (size_t)((M + 63) / 64) * ((N + 63) / 64) * splits * P <= 3 * cus;
+    auto fits = [&](int bm, int bn, size_t per_cu) { return (size_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.splits * a.P <= (per_cu - 1) * cus; };
+    if (a.N <= 32) return fits(128, 32, 4);
+    const long tile = options().gemm_tile;
+    if (tile != 0) return tile == 2 && fits(64, 64, 4);
+    if (!split_fits(a, true, false)) return fits(64, 64, 4);
+    switch (split_pick(a.M, a.N, a.P, a.splits)) {
+    case SPLIT_64x128: return fits(64, 128, split_blocks_per_cu<2>());
+    case SPLIT_64x64: return fits(64, 64, split_blocks_per_cu<2>());
+    case SPLIT_32x128: return fits(32, 128, split_blocks_per_cu<1>());
+    case SPLIT_32x32: return fits(32, 32, split_blocks_per_cu<1>());
+    default: return false;
+    }
 }
 
 // Elastic update fused into the backward pass.  Eq. (2) runs first and saves the time-t
@@ -562,8 +624,9 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         // enough to read to be worth the tens of microseconds that ordering two streams costs; else its own kernel.
         const long overlap = options().round_overlap;
         const int splits0 = (L == 1) ? pl.splits : 1;
-        const bool room = (head && L == 1) ? head_blocks(P, b) <= 3u * (unsigned)num_cus()
-                                           : forward_launch_has_room(b, dims[1], P, splits0);
+        GemmArgs first = {};
+        first.M = b; first.N = dims[1]; first.K = dims[0] + 1; first.lda = dims[0]; first.ldb = dims[1]; first.P = P; first.splits = splits0;
+        const bool room = (head && L == 1) ? head_blocks(P, b) <= 3u * (unsigned)num_cus() : forward_launch_has_room(first);
         attach_center = (overlap == 3) || (overlap == 1 && room);
         if (!attach_center && (overlap == 2 || (overlap == 1 && (size_t)P * pl.N >= ((size_t)1 << 24)))) {
             lane_guard = std::unique_lock<std::mutex>(side_mutex);
@@ -608,8 +671,8 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         a.c_ss = (size_t)P * b * d_out;
         if (l == 0) a.ctr = center_job;
         const bool vec = base_vec && mult4(d_in) && mult4(d_out) && mult4(pl.off[l]);
-        if (last) launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, true, s);
-        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, true, s);
+        if (last) launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, s);
+        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s, lane != nullptr);
     }
     float *row_loss = reinterpret_cast<float *>(ws + pl.rowloss_off);
     const int rows = P * b;
@@ -632,18 +695,29 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     // below when the held one is narrow, or with the weight-gradient product of the layer below.
     const int epi = !step ? (G16 ? EPI_STORE_BF16 : EPI_NONE) : (step->V16 ? EPI_ELASTIC_MOM_BF16 : (step->V ? EPI_ELASTIC_MOM : EPI_ELASTIC));
     const bool pairing = options().gemm_pair != 0;
-    const bool tile64 = options().gemm_tile == 0 || options().gemm_tile == 2;   // wide backward products use 64x64
+    const bool tile64 = options().gemm_tile == 0 || options().gemm_tile == 2;   // wide weight gradients use 64x64 or gemm_split.h
     struct Held { bool have = false; GemmArgs a; bool vec = false; } held;
     auto launch_dw = [&](const GemmArgs &d, bool vec) {
-        if (epi == EPI_NONE) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_NONE>(d, vec, false, s);
-        else if (epi == EPI_STORE_BF16) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_STORE_BF16>(d, vec, false, s);
-        else if (epi == EPI_ELASTIC) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC>(d, vec, false, s);
-        else if (epi == EPI_ELASTIC_MOM) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM>(d, vec, false, s);
-        else launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM_BF16>(d, vec, false, s);
+        if (epi == EPI_NONE) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_NONE>(d, vec, s);
+        else if (epi == EPI_STORE_BF16) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_STORE_BF16>(d, vec, s);
+        else if (epi == EPI_ELASTIC) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC>(d, vec, s);
+        else if (epi == EPI_ELASTIC_MOM) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM>(d, vec, s);
+        else launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM_BF16>(d, vec, s);
+    };
+    // the first kernel that changes W waits for the center rule, which reads W at time t
+    bool joined = lane == nullptr;
+    auto join = [&]() {
+        if (!joined && hipStreamWaitEvent(s, lane->join, 0) != hipSuccess) return false;
+        joined = true;
+        return true;
     };
     auto flush = [&]() {
-        if (held.have) launch_dw(held.a, held.vec);
+        if (held.have) {
+            if (!join()) return false;
+            launch_dw(held.a, held.vec);
+        }
         held.have = false;
+        return true;
     };
     for (int l = L - 1; l >= 0; --l) {
         const int d_in = dims[l], d_out = dims[l + 1];
@@ -657,35 +731,23 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
             a.M = b; a.N = d_in; a.K = d_out; a.P = P;
             a.splits = 1; a.k_per_split = (a.K + 63) / 64 * 64;
             const bool vec = base_vec && mult4(d_out) && mult4(pl.off[l]);
-            // sharing costs the input-gradient blocks some occupancy (the kernel takes the larger register count
-            // of its two halves), so it is done only when their launch leaves wave slots idle anyway
-            const bool room = (size_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * P <= (size_t)3 * num_cus();
-            if (held.have && pairing && held.a.N <= 32 && vec && tile64 && a.N > 32 && room) {
-                if (epi == EPI_NONE) {
-                    if (held.vec) launch_pair_da_narrow_dw<EPI_NONE, true>(a, held.a, s);
-                    else launch_pair_da_narrow_dw<EPI_NONE, false>(a, held.a, s);
-                } else if (epi == EPI_STORE_BF16) {
-                    if (held.vec) launch_pair_da_narrow_dw<EPI_STORE_BF16, true>(a, held.a, s);
-                    else launch_pair_da_narrow_dw<EPI_STORE_BF16, false>(a, held.a, s);
-                } else if (epi == EPI_ELASTIC) {
-                    if (held.vec) launch_pair_da_narrow_dw<EPI_ELASTIC, true>(a, held.a, s);
-                    else launch_pair_da_narrow_dw<EPI_ELASTIC, false>(a, held.a, s);
-                } else if (epi == EPI_ELASTIC_MOM) {
-                    if (held.vec) launch_pair_da_narrow_dw<EPI_ELASTIC_MOM, true>(a, held.a, s);
-                    else launch_pair_da_narrow_dw<EPI_ELASTIC_MOM, false>(a, held.a, s);
-                } else {
-                    if (held.vec) launch_pair_da_narrow_dw<EPI_ELASTIC_MOM_BF16, true>(a, held.a, s);
-                    else launch_pair_da_narrow_dw<EPI_ELASTIC_MOM_BF16, false>(a, held.a, s);
-                }
-                held.have = false;
-            } else {
-                flush();
-                launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, vec, false, s);
+            // A held narrow product shares this launch where the tile leaves a block per compute unit free; with the center
+            // rule on the second stream it waits, so that the rule has this launch to finish behind as well.
+            bool shared = false;
+            if (held.have && pairing && !lane && held.a.N <= 32 && a.N > 32 && options().gemm_tile == 0 && split_fits(a, true, true)) {
+                const SplitPick pick = split_pick(a.M, a.N, P, 1);
+                if (epi == EPI_NONE) shared = launch_split_pair_da_narrow_dw<EPI_NONE>(a, held.a, pick, s);
+                else if (epi == EPI_STORE_BF16) shared = launch_split_pair_da_narrow_dw<EPI_STORE_BF16>(a, held.a, pick, s);
+                else if (epi == EPI_ELASTIC) shared = launch_split_pair_da_narrow_dw<EPI_ELASTIC>(a, held.a, pick, s);
+                else if (epi == EPI_ELASTIC_MOM) shared = launch_split_pair_da_narrow_dw<EPI_ELASTIC_MOM>(a, held.a, pick, s);
+                else shared = launch_split_pair_da_narrow_dw<EPI_ELASTIC_MOM_BF16>(a, held.a, pick, s);
+            }
+            if (shared) held.have = false;
+            else {
+                launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, vec, s);
+                if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
             }
         }
-        // the first kernel that changes W waits for the center rule, which reads W at time t
-        if (step && lane && l == L - 1 && hipStreamWaitEvent(s, lane->join, 0) != hipSuccess)
-            return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
         // [dW_l ; db_l] = [A_l 1]^T dZ_l, stored at the layer's place in the packed gradient
         GemmArgs d = {};
         d.A = act(l); d.a_ws = (size_t)b * d_in; d.lda = d_in; d.a_lim = d_in; d.a_ones = d_in;
@@ -703,20 +765,28 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         }
         const bool vec = mult4(d_in) && mult4(d_out);
         if (held.have) {     // two weight-gradient products in a row (no input-gradient product for layer 0)
-            if (pairing && tile64 && held.vec && vec && held.a.N > 32 && d.N > 32) {
-                if (epi == EPI_NONE) launch_pair_dw_dw<EPI_NONE>(held.a, d, s);
-                else if (epi == EPI_STORE_BF16) launch_pair_dw_dw<EPI_STORE_BF16>(held.a, d, s);
-                else if (epi == EPI_ELASTIC) launch_pair_dw_dw<EPI_ELASTIC>(held.a, d, s);
-                else if (epi == EPI_ELASTIC_MOM) launch_pair_dw_dw<EPI_ELASTIC_MOM>(held.a, d, s);
-                else launch_pair_dw_dw<EPI_ELASTIC_MOM_BF16>(held.a, d, s);
+            const bool split0 = split_dw(held.a, held.vec), split1 = split_dw(d, vec);
+            const bool both_fp32 = !split0 && !split1 && tile64 && held.vec && vec && held.a.N > 32 && d.N > 32;
+            if (pairing && ((split0 && split1) || both_fp32)) {
+                if (!join()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
+                auto pair = [&](auto e) {
+                    constexpr int E = decltype(e)::value;
+                    if (both_fp32) launch_pair_dw_dw<E>(held.a, d, s);
+                    else launch_split_pair_dw_dw<E>(held.a, d, s);
+                };
+                if (epi == EPI_NONE) pair(std::integral_constant<int, EPI_NONE>{});
+                else if (epi == EPI_STORE_BF16) pair(std::integral_constant<int, EPI_STORE_BF16>{});
+                else if (epi == EPI_ELASTIC) pair(std::integral_constant<int, EPI_ELASTIC>{});
+                else if (epi == EPI_ELASTIC_MOM) pair(std::integral_constant<int, EPI_ELASTIC_MOM>{});
+                else pair(std::integral_constant<int, EPI_ELASTIC_MOM_BF16>{});
                 held.have = false;
                 continue;
             }
-            flush();
+            if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
         }
         held.have = true; held.a = d; held.vec = vec;
     }
-    flush();
+    if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
     return check_launch(name);
 }
 
@@ -749,15 +819,15 @@ extern "C" int easgd_layer_product(int kind, int d_in, int d_out, int P, int b, 
         a.M = b; a.N = d_out; a.K = d_in + 1;
         a.k_per_split = (a.K + 63) / 64 * 64;
         const bool vec = mult4(ld) && mult4(d_in) && mult4(d_out) && aligned16(Wl);
-        if (relu) launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, true, s);
-        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, true, s);
+        if (relu) launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s);
+        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, s);
     } else if (kind == 1) {     // [dW ; db] = [A 1]^T dZ
         a.A = A; a.a_ws = (size_t)b * d_in; a.lda = d_in; a.a_lim = d_in; a.a_ones = d_in;
         a.B = dZ; a.b_ws = (size_t)b * d_out; a.ldb = d_out;
         a.C = out; a.c_ws = out_ws; a.ldc = d_out;
         a.M = d_in + 1; a.N = d_out; a.K = b;
         a.k_per_split = (a.K + 63) / 64 * 64;
-        launch_gemm<MN_CONTIG, MN_CONTIG, EPI_NONE>(a, mult4(d_in) && mult4(d_out), false, s);
+        launch_gemm<MN_CONTIG, MN_CONTIG, EPI_NONE>(a, mult4(d_in) && mult4(d_out), s);
     } else {                    // dA = (dZ W^T) where A > 0
         a.A = dZ; a.a_ws = (size_t)b * d_out; a.lda = d_out; a.a_lim = d_out; a.a_ones = -1;
         a.B = Wl; a.b_ws = ld; a.ldb = d_out;
@@ -765,7 +835,7 @@ extern "C" int easgd_layer_product(int kind, int d_in, int d_out, int P, int b, 
         a.mask = A; a.mask_ws = (size_t)b * d_in; a.ldmask = d_in;
         a.M = b; a.N = d_in; a.K = d_out;
         a.k_per_split = (a.K + 63) / 64 * 64;
-        launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, mult4(ld) && mult4(d_out) && aligned16(Wl), false, s);
+        launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, mult4(ld) && mult4(d_out) && aligned16(Wl), s);
     }
     return check_launch(name);
 }
