@@ -12,6 +12,25 @@ namespace easgd {
 template <typename T>
 __device__ __forceinline__ void keep_loaded(T &x) { asm volatile("" : "+v"(x)); }
 
+// Four floats at any float's address: the hardware's 128-bit accesses need the element's alignment only, so rows that are
+// not multiples of four elements apart take the same instructions as aligned ones.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+template <bool NT>
+__device__ __forceinline__ f32x4 load4(const float *p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(p));
+    else return *reinterpret_cast<const f32x4_any *>(p);
+}
+
+template <bool NT>
+__device__ __forceinline__ void store4(float *p, f32x4 v)
+{
+    if constexpr (NT) __builtin_nontemporal_store((f32x4_any)v, reinterpret_cast<f32x4_any *>(p));
+    else *reinterpret_cast<f32x4_any *>(p) = v;
+}
+
 // s*a + c with one rounding (T = float or a float vector, s a scalar).  The rules below spell out which of their
 // products are fused: left to the compiler the choice depends on the surrounding code (a product with two uses is
 // computed once and then not fused), and kernels that must give the same bits would not.
@@ -69,45 +88,37 @@ __device__ __forceinline__ float worker_rule_bf16(float &w, unsigned short &v16,
     return d;
 }
 
-// Eq. (2) alone, ahead of the worker rules, for block `block` of 256 threads (T = float or a vector of 4 floats;
-// the last of n_blocks blocks also owns the N % 4 tail of the vector form):
+// Eq. (2) alone, ahead of the worker rules, for block `block` of 256 threads, four parameters each (the last of n_blocks
+// blocks also owns the N % 4 tail):
 //   Wc[j] <- c + alpha * sum_i (W_i[j] - c)  with c = Wc[j], workers in ascending order (the order of the fused
 // update kernels), and the time-t value c saved to old[j] for the worker rules that run later in the round.
 // W is read with ordinary loads: the same values are needed again soon.
-template <typename T>
-__device__ __forceinline__ void center_rule_block(const float *__restrict__ Wp, float *__restrict__ Wcp,
-                                                  float *__restrict__ oldp, int P, size_t N, size_t ld, float alpha,
-                                                  size_t block, size_t n_blocks, int tid)
+__device__ __forceinline__ void center_rule_block(const float *__restrict__ W, float *__restrict__ Wc, float *__restrict__ old,
+                                                  int P, size_t N, size_t ld, float alpha, size_t block, size_t n_blocks, int tid)
 {
-    constexpr size_t LANES = sizeof(T) / sizeof(float);
-    const T *__restrict__ W = (const T *)Wp;
-    T *__restrict__ Wc = (T *)Wcp;
-    T *__restrict__ old = (T *)oldp;
-    const size_t n = N / LANES, ldt = ld / LANES;
-    const size_t j = block * 256 + (size_t)tid;
-    if (j < n) {
-        const T c = Wc[j];
-        T acc = c - c;
+    const size_t n4 = N / 4, j = block * 256 + (size_t)tid;
+    if (j < n4) {
+        const f32x4 c = load4<false>(Wc + 4 * j);
+        f32x4 acc = c - c;
         int i = 0;
         for (; i + 4 <= P; i += 4) {
-            T w[4];
+            f32x4 w[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) w[u] = W[(size_t)(i + u) * ldt + j];
+            for (int u = 0; u < 4; ++u) w[u] = load4<false>(W + (size_t)(i + u) * ld + 4 * j);
 #pragma unroll
             for (int u = 0; u < 4; ++u) acc += w[u] - c;
         }
-        for (; i < P; ++i) acc += W[(size_t)i * ldt + j] - c;
-        old[j] = c;
-        Wc[j] = fma_s(alpha, acc, c);
+        for (; i < P; ++i) acc += load4<false>(W + (size_t)i * ld + 4 * j) - c;
+        store4<false>(old + 4 * j, c);
+        store4<false>(Wc + 4 * j, fma_s(alpha, acc, c));
     }
-    const size_t tail = N - n * LANES;        // only for the vector form
-    if (block == n_blocks - 1 && (size_t)tid < tail) {
-        const size_t k = n * LANES + (size_t)tid;
-        const float c = Wcp[k];
+    if (block == n_blocks - 1 && (size_t)tid < N - 4 * n4) {
+        const size_t k = 4 * n4 + (size_t)tid;
+        const float c = Wc[k];
         float acc = 0.f;
-        for (int i = 0; i < P; ++i) acc += Wp[(size_t)i * ld + k] - c;
-        oldp[k] = c;
-        Wcp[k] = fma_s(alpha, acc, c);
+        for (int i = 0; i < P; ++i) acc += W[(size_t)i * ld + k] - c;
+        old[k] = c;
+        Wc[k] = fma_s(alpha, acc, c);
     }
 }
 
@@ -116,7 +127,7 @@ struct CenterJob {
     const float *W;
     float *Wc, *old;
     size_t N, ld;
-    int P, vec;
+    int P;
     float alpha;
     unsigned blocks, first_block;           // the job's blocks are [first_block, first_block + blocks) of the grid
 };

@@ -35,8 +35,28 @@ enum { K_CONTIG = 0, MN_CONTIG = 1 };
 enum { EPI_NONE = 0, EPI_RELU = 1, EPI_MASK = 2, EPI_ELASTIC = 3, EPI_ELASTIC_MOM = 4, EPI_ELASTIC_MOM_BF16 = 5,
        EPI_STORE_BF16 = 6 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// The mean losses, on extra blocks at the end of a weight-gradient launch (blocks == 0: none): as a kernel of its own it
+// is a launch boundary of some 4 us in a round that may take 12.
+struct LossJob {
+    const float *row_loss;              // [P][b]
+    float *loss;                        // [P]
+    int b, P;
+    unsigned blocks, first_block;       // one wavefront per worker, four per block
+};
+
+// loss[w] = mean of the worker's b row losses: lane l adds rows l, l+64, ... in order, then a fixed shuffle tree.
+__device__ __forceinline__ void mean_loss_block(const LossJob &j, unsigned block)
+{
+    const int w = (int)(4 * block + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    if (w >= j.P) return;
+    float acc = 0.f;
+    for (int r = lane; r < j.b; r += 64) acc += j.row_loss[(size_t)w * j.b + r];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    if (lane == 0) j.loss[w] = acc / (float)j.b;
+}
 
 struct GemmArgs {
     const float *A, *B, *mask;
@@ -70,6 +90,7 @@ struct GemmArgs {
     // extra blocks at the end of the grid that run the center rule beside the product (bandwidth-bound
     // work in the shadow of matrix-core-bound work, without a second stream); ctr.blocks == 0: none
     CenterJob ctr;
+    LossJob mean;
 };
 
 // n / d for 0 <= n, d >= 1, with magic = ceil(2^32 / d) when n * d < 2^32 (then the high half of n * magic is the
@@ -794,8 +815,11 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, 2) void gemm_mfma_kernel(Gem
     __shared__ __attribute__((aligned(16))) float lds[gemm_lds_floats<BM, BN, BK, A_LAYOUT, B_LAYOUT>()];
     if (p.ctr.blocks > 0 && blockIdx.x >= p.ctr.first_block) {         // uniform for the block
         const size_t b = blockIdx.x - p.ctr.first_block;
-        if (p.ctr.vec) center_rule_block<f32x4>(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
-        else center_rule_block<float>(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
+        center_rule_block(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
+        return;
+    }
+    if (p.mean.blocks > 0 && blockIdx.x >= p.mean.first_block) {
+        mean_loss_block(p.mean, blockIdx.x - p.mean.first_block);
         return;
     }
     gemm_block<BM, BN, BK, WAVES_M, WAVES_N, A_LAYOUT, B_LAYOUT, VEC, EPI, MT, true>(p, blockIdx.x, lds);
@@ -812,7 +836,8 @@ __global__ __launch_bounds__(256, 2) void gemm_pair_kernel(GemmArgs p0, GemmArgs
     static_assert(WM0 * WN0 == 4 && WM1 * WN1 == 4, "both products use 256 threads");
     constexpr int L0 = gemm_lds_floats<BM0, BN0, BK0, AL0, BL0>(), L1 = gemm_lds_floats<BM1, BN1, BK1, AL1, BL1>();
     __shared__ __attribute__((aligned(16))) float lds[L0 > L1 ? L0 : L1];
-    if (blockIdx.x < n0) gemm_block<BM0, BN0, BK0, WM0, WN0, AL0, BL0, VEC0, EPI0>(p0, blockIdx.x, lds);
+    if (p0.mean.blocks > 0 && blockIdx.x >= p0.mean.first_block) mean_loss_block(p0.mean, blockIdx.x - p0.mean.first_block);
+    else if (blockIdx.x < n0) gemm_block<BM0, BN0, BK0, WM0, WN0, AL0, BL0, VEC0, EPI0>(p0, blockIdx.x, lds);
     else gemm_block<BM1, BN1, BK1, WM1, WN1, AL1, BL1, VEC1, EPI1>(p1, blockIdx.x - n0, lds);
 }
 

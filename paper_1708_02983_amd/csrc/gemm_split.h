@@ -140,22 +140,27 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     // its own that is held inside the operand, and is replaced by what it stands for when it is used (cut).
     const int a_klim = (A_LAYOUT == K_CONTIG) ? min(p.a_lim, k_end) : k_end;
     const int n_slabs = (k_end - k_begin + BK - 1) / BK;
-    const int n_fast = (a_klim - k_begin) / BK;
-    // what lies at or beyond `lim` along k is zero, or one where the ones vector sits
-    auto cut = [](f32x8 &x, int k, int lim, int ones) {
+    // Without the ones vector along k the last slab may start early, so that it lies inside too: what it then holds of
+    // the slab before is replaced by zeros.  (Sums as short as a minibatch have no other slabs to speak of.)
+    const bool early = !(A_LAYOUT == K_CONTIG && B_LAYOUT == MN_CONTIG) && k_end - k_begin >= BK;      // uniform
+    const int n_fast = early ? n_slabs : (a_klim - k_begin) / BK;
+    auto start = [&](int slab) { return early ? min(k_begin + slab * BK, k_end - BK) : k_begin + slab * BK; };
+    // what lies below `first` or at or beyond `lim` along k is zero, or one where the ones vector sits
+    auto cut = [](f32x8 &x, int k, int first, int lim, int ones) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = k + e < lim ? x[e] : (k + e == ones ? 1.f : 0.f);
+        for (int e = 0; e < 8; ++e) x[e] = k + e >= first && k + e < lim ? x[e] : (k + e == ones ? 1.f : 0.f);
     };
+    auto whole = [&](int slab) { return early ? start(slab) == k_begin + slab * BK : slab < n_fast; };
     const int k_ones = (A_LAYOUT == K_CONTIG && p.a_ones < k_end) ? p.a_ones : -1;
     auto load_a = [&](int slab, auto inner, int it, RawA &r) {
-        const int k0 = k_begin + slab * BK;
+        const int k0 = start(slab);
         if (decltype(inner)::value || slab < n_fast) {
             if (A_LAYOUT == K_CONTIG) k8_vec(ab, a_off[it], 4u * (unsigned)k0, r.x[it]);
             else
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     r.x[it][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)a_off[it], (int)(4u * (unsigned)(k0 + e) * (unsigned)p.lda), 0));
-        } else if (slab < n_slabs) {
+        } else if (!early && slab < n_slabs) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const unsigned k = (unsigned)min(k0 + a_k[it] + e, a_klim - 1);
@@ -166,14 +171,14 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
         }
     };
     auto load_b_step = [&](int slab, auto inner, int ks, RawB &r) {
-        const int kb = k_begin + slab * BK + 16 * (wk + ks * WK);
+        const int kb = start(slab) + 16 * (wk + ks * WK);
         if (decltype(inner)::value || slab < n_fast) {
             if (B_LAYOUT == K_CONTIG) k8_vec(bb, b_off, 4u * (unsigned)kb, r.x[ks]);
             else
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     r.x[ks][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bb, (int)b_off, (int)(4u * (unsigned)(kb + e) * (unsigned)p.ldb), 0));
-        } else if (slab < n_slabs) {
+        } else if (!early && slab < n_slabs) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const unsigned k = (unsigned)min(kb + 8 * q + e, k_end - 1);
@@ -182,9 +187,8 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
             }
         }
     };
-    // the slab that is only partly inside the operands along k
-    auto cut_a = [&](int k0, int it, RawA &r) { cut(r.x[it], k0 + a_k[it], a_klim, k_ones); };
-    auto cut_b = [&](int k0, int ks, RawB &r) { cut(r.x[ks], k0 + 16 * (wk + ks * WK) + 8 * q, k_end, -1); };
+    auto cut_a = [&](int slab, int it, RawA &r) { cut(r.x[it], start(slab) + a_k[it], k_begin + slab * BK, a_klim, k_ones); };
+    auto cut_b = [&](int slab, int ks, RawB &r) { cut(r.x[ks], start(slab) + 16 * (wk + ks * WK) + 8 * q, k_begin + slab * BK, k_end, -1); };
     auto a_here = [&](int it) { return T::UNITS % 256 == 0 || tid + it * 256 < T::UNITS; };
     auto put_ones = [&](int it, RawA &r) {
         if (A_LAYOUT == MN_CONTIG) {
@@ -243,13 +247,13 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
 #pragma unroll
     for (int u = 0; u < IT; ++u) {
         SplitFrag f;
-        if (0 >= n_fast) cut_a(k_begin, u, ra);
+        if (!whole(0)) cut_a(0, u, ra);
         put_ones(u, ra);
         split8(ra.x[u], f);
         store_a(0, u, f);
         load_a(1, std::false_type{}, u, ra);
     }
-    if (0 >= n_fast) cut_b(k_begin, 0, rb);
+    if (!whole(0)) cut_b(0, 0, rb);
     split8(rb.x[0], fb[0]);
     load_b_step(1, std::false_type{}, 0, rb);
     __syncthreads();
@@ -267,18 +271,19 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
             const int ks = it / TM, i = it % TM;
             if (it + 1 < ITEMS) fetch(buf, (it + 1) / TM, (it + 1) % TM, fa[(it + 1) & 1]);
             const bool b1 = KS == 2 && it == 0, b0 = it == (KS == 2 ? TM : ITEMS - 1);      // which split of B runs here
-            if (LAST && b1 && s >= n_fast) cut_b(k_begin + s * BK, 1, rb);
-            if (LAST && b0 && s + 1 >= n_fast) cut_b(k_begin + (s + 1) * BK, 0, rb);
+            if (LAST && b1 && !whole(s)) cut_b(s, 1, rb);
+            if (LAST && b0 && !whole(s + 1)) cut_b(s + 1, 0, rb);
             auto a_unit = [&](int u) { return it == (ITEMS >= 4 ? 1 + u % 2 : 0); };        // which units of A
 #pragma unroll
             for (int u = 0; u < IT; ++u)
                 if (a_unit(u)) {
-                    if (LAST && s + 1 >= n_fast) cut_a(k_begin + (s + 1) * BK, u, ra);
+                    if (LAST && !whole(s + 1)) cut_a(s + 1, u, ra);
                     put_ones(u, ra);
                 }
             __builtin_amdgcn_sched_barrier(0);
-            // a step that lies beyond the K range holds zeros only
-            const bool live = !LAST || k_begin + s * BK + 16 * (wk + ks * WK) < k_end;      // uniform
+            // a step without a k of its own holds zeros only
+            const int k_step = start(s) + 16 * (wk + ks * WK);
+            const bool live = !LAST || (k_step < k_end && k_step + 16 > k_begin + s * BK);  // uniform
 #pragma unroll
             for (int part = 0; part < 6; ++part) {
                 if (live) multiply(part, i, fa[it & 1], fb[ks == 0 ? F0 : 1]);
@@ -431,8 +436,11 @@ __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_ker
     __shared__ u32x4 lds[SplitTile<TM, WN, WK>::LDS_VECS];
     if (p.ctr.blocks > 0 && blockIdx.x >= p.ctr.first_block) {         // uniform for the block
         const size_t b = blockIdx.x - p.ctr.first_block;
-        if (p.ctr.vec) center_rule_block<f32x4>(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
-        else center_rule_block<float>(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
+        center_rule_block(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
+        return;
+    }
+    if (p.mean.blocks > 0 && blockIdx.x >= p.mean.first_block) {
+        mean_loss_block(p.mean, blockIdx.x - p.mean.first_block);
         return;
     }
     split_block<TM, WN, WK, A_LAYOUT, B_LAYOUT, EPI>(p, blockIdx.x, lds);
@@ -443,18 +451,20 @@ template <int TM, int WN, int WK, int EPI>
 __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_dw_pair_kernel(GemmArgs p0, GemmArgs p1, unsigned n0)
 {
     __shared__ u32x4 lds[SplitTile<TM, WN, WK>::LDS_VECS];
-    if (blockIdx.x < n0) split_block<TM, WN, WK, MN_CONTIG, MN_CONTIG, EPI>(p0, blockIdx.x, lds);
+    if (p0.mean.blocks > 0 && blockIdx.x >= p0.mean.first_block) mean_loss_block(p0.mean, blockIdx.x - p0.mean.first_block);
+    else if (blockIdx.x < n0) split_block<TM, WN, WK, MN_CONTIG, MN_CONTIG, EPI>(p0, blockIdx.x, lds);
     else split_block<TM, WN, WK, MN_CONTIG, MN_CONTIG, EPI>(p1, blockIdx.x - n0, lds);
 }
 
 // An input-gradient product with the weight-gradient product of a narrow layer, whose few blocks come first: they are a
 // chain of round trips to memory, which the blocks of the other product cover.
 template <int TM, int WN, int WK, int EPI>
-__global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_da_narrow_dw_kernel(GemmArgs da, GemmArgs dw, unsigned n_dw)
+__global__ __launch_bounds__(256, TM <= 2 ? 3 : 2) void gemm_split_da_narrow_dw_kernel(GemmArgs da, GemmArgs dw, unsigned n_dw)
 {
     constexpr int NARROW = gemm_lds_floats<128, 32, 32, MN_CONTIG, MN_CONTIG>() / 4, SPLIT = SplitTile<TM, WN, WK>::LDS_VECS;
     __shared__ u32x4 lds[NARROW > SPLIT ? NARROW : SPLIT];
-    if (blockIdx.x < n_dw) gemm_block<128, 32, 32, 4, 1, MN_CONTIG, MN_CONTIG, false, EPI>(dw, blockIdx.x, reinterpret_cast<float *>(lds));
+    if (dw.mean.blocks > 0 && blockIdx.x >= dw.mean.first_block) mean_loss_block(dw.mean, blockIdx.x - dw.mean.first_block);
+    else if (blockIdx.x < n_dw) gemm_block<128, 32, 32, 4, 1, MN_CONTIG, MN_CONTIG, false, EPI>(dw, blockIdx.x, reinterpret_cast<float *>(lds));
     else split_block<TM, WN, WK, K_CONTIG, K_CONTIG, EPI_MASK>(da, blockIdx.x - n_dw, lds);
 }
 

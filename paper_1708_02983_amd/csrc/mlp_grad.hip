@@ -145,17 +145,6 @@ __global__ __launch_bounds__(256) void softmax_xent_kernel(const float *__restri
     if (lane == 0) row_loss[row] = logf(sum) - zlabel;
 }
 
-// loss[w] = mean of the worker's b row losses: lane l adds rows l, l+64, ... in order, then a fixed shuffle tree.
-__global__ __launch_bounds__(64) void mean_loss_kernel(const float *__restrict__ row_loss, float *__restrict__ loss, int b)
-{
-    const int w = blockIdx.x, lane = threadIdx.x;
-    float acc = 0.f;
-    for (int r = lane; r < b; r += 64) acc += row_loss[(size_t)w * b + r];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if (lane == 0) loss[w] = acc / (float)b;
-}
-
 // One launch for the head of the network; the grid may be extended by blocks that run the center rule (h.ctr).
 template <int ROWS, int CP, bool ONE_PASS, int NT = 4>
 __global__ __launch_bounds__(256) void mlp_head_kernel(HeadArgs h)
@@ -164,8 +153,7 @@ __global__ __launch_bounds__(256) void mlp_head_kernel(HeadArgs h)
     __shared__ float dzs[ROWS][CP];
     if (h.ctr.blocks > 0 && blockIdx.x >= h.ctr.first_block) {         // uniform for the block
         const size_t cb = blockIdx.x - h.ctr.first_block;
-        if (h.ctr.vec) center_rule_block<f32x4>(h.ctr.W, h.ctr.Wc, h.ctr.old, h.ctr.P, h.ctr.N, h.ctr.ld, h.ctr.alpha, cb, h.ctr.blocks, threadIdx.x);
-        else center_rule_block<float>(h.ctr.W, h.ctr.Wc, h.ctr.old, h.ctr.P, h.ctr.N, h.ctr.ld, h.ctr.alpha, cb, h.ctr.blocks, threadIdx.x);
+        center_rule_block(h.ctr.W, h.ctr.Wc, h.ctr.old, h.ctr.P, h.ctr.N, h.ctr.ld, h.ctr.alpha, cb, h.ctr.blocks, threadIdx.x);
         return;
     }
     head_block<ROWS, CP, ONE_PASS, false, NT>(h, blockIdx.x, part, dzs);
@@ -243,9 +231,10 @@ template <int EPI>
 static void launch_pair_dw_dw(GemmArgs d0, GemmArgs d1, hipStream_t s)
 {
     const unsigned n0 = place_blocks<64, 64>(d0), n1 = place_blocks<64, 64>(d1);
+    d0.mean.first_block = n0 + n1;
     EASGD_LAUNCH((gemm_pair_kernel<64, 64, 32, 2, 2, MN_CONTIG, MN_CONTIG, true, EPI,
                                          64, 64, 32, 2, 2, MN_CONTIG, MN_CONTIG, true, EPI>),
-                       dim3(n0 + n1), dim3(256), 0, s, d0, d1, n0);
+                       dim3(n0 + n1 + d0.mean.blocks), dim3(256), 0, s, d0, d1, n0);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int AL, int BL, int EPI, int MT = 32>
@@ -258,6 +247,8 @@ static void launch_tile(const GemmArgs &a_in, bool vec, hipStream_t s)
         a.ctr.first_block = (unsigned)total;
         total += a.ctr.blocks;
     }
+    a.mean.first_block = (unsigned)total;
+    total += a.mean.blocks;
     const dim3 grid((unsigned)total), block(WM * WN * 64);
     if (vec) EASGD_LAUNCH((gemm_mfma_kernel<BM, BN, BK, WM, WN, AL, BL, true, EPI, MT>), grid, block, 0, s, a);
     else EASGD_LAUNCH((gemm_mfma_kernel<BM, BN, BK, WM, WN, AL, BL, false, EPI, MT>), grid, block, 0, s, a);
@@ -304,6 +295,8 @@ static void launch_split(const GemmArgs &a_in, hipStream_t s)
         a.ctr.first_block = (unsigned)total;
         total += a.ctr.blocks;
     }
+    a.mean.first_block = (unsigned)total;
+    total += a.mean.blocks;
     EASGD_LAUNCH((gemm_split_kernel<TM, WN, WK, AL, BL, EPI>), dim3((unsigned)total), dim3(256), 0, s, a);
 }
 
@@ -321,7 +314,8 @@ template <int EPI>
 static void launch_split_pair_dw_dw(GemmArgs d0, GemmArgs d1, hipStream_t s)
 {
     const unsigned n0 = place_blocks<64, 128>(d0), n1 = place_blocks<64, 128>(d1);
-    EASGD_LAUNCH((gemm_split_dw_pair_kernel<2, 4, 1, EPI>), dim3(n0 + n1), dim3(256), 0, s, d0, d1, n0);
+    d0.mean.first_block = n0 + n1;
+    EASGD_LAUNCH((gemm_split_dw_pair_kernel<2, 4, 1, EPI>), dim3(n0 + n1 + d0.mean.blocks), dim3(256), 0, s, d0, d1, n0);
 }
 
 // An input-gradient product and the weight-gradient product of a narrow layer in one launch; false: this tile has none.
@@ -331,13 +325,16 @@ static bool launch_split_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, SplitPick p
     const unsigned n_dw = place_blocks<128, 32>(dw);
     if (pick == SPLIT_64x128) {
         const unsigned n = place_blocks<64, 128>(da);
-        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<2, 4, 1, EPI>), dim3(n + n_dw), dim3(256), 0, s, da, dw, n_dw);
+        dw.mean.first_block = n + n_dw;
+        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<2, 4, 1, EPI>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
     } else if (pick == SPLIT_64x64) {
         const unsigned n = place_blocks<64, 64>(da);
-        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<2, 2, 2, EPI>), dim3(n + n_dw), dim3(256), 0, s, da, dw, n_dw);
+        dw.mean.first_block = n + n_dw;
+        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<2, 2, 2, EPI>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
     } else if (pick == SPLIT_32x32) {
         const unsigned n = place_blocks<32, 32>(da);
-        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<1, 1, 4, EPI>), dim3(n + n_dw), dim3(256), 0, s, da, dw, n_dw);
+        dw.mean.first_block = n + n_dw;
+        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<1, 1, 4, EPI>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
     } else return false;
     return true;
 }
@@ -651,11 +648,10 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     // ---- forward propagation ----
     CenterJob center_job = {};           // rides on the first launch of forward propagation when attach_center
     if (attach_center) {
-        const bool cvec = aligned16(step->W) && aligned16(step->Wc) && aligned16(old_center) && (ld % 4 == 0);
-        const size_t cblocks = (cvec ? pl.N / 4 : pl.N) / 256 + 1;
+        const size_t cblocks = pl.N / 4 / 256 + 1;
         if (cblocks > 0x3fffffffu) return fail(EASGD_ERANGE, "%s: N too large", name);
         center_job.W = step->W; center_job.Wc = step->Wc; center_job.old = old_center;
-        center_job.N = pl.N; center_job.ld = ld; center_job.P = P; center_job.vec = cvec ? 1 : 0;
+        center_job.N = pl.N; center_job.ld = ld; center_job.P = P;
         center_job.alpha = step->eta * step->rho; center_job.blocks = (unsigned)cblocks;
     }
     for (int l = 0; l < (head ? L - 1 : L); ++l) {
@@ -687,7 +683,6 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         EASGD_LAUNCH(softmax_xent_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, logits, y, dz[(L - 1) % 3], row_loss,
                            rows, b, dims[L], pl.splits, (size_t)rows * dims[L]);
     }
-    if (loss) EASGD_LAUNCH(mean_loss_kernel, dim3(P), dim3(64), 0, s, row_loss, loss, b);
 
     // ---- backward propagation ----
     // The weight-gradient product of a layer is held back until the next product is known, because two
@@ -756,6 +751,9 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         d.C16 = G16 ? G16 + pl.off[l] : nullptr;
         d.M = d_in + 1; d.N = d_out; d.K = b; d.P = P;
         d.splits = 1; d.k_per_split = (d.K + 63) / 64 * 64;
+        if (loss && l == L - 1) {            // the first weight-gradient launch also sums the losses up
+            d.mean.row_loss = row_loss; d.mean.loss = loss; d.mean.b = b; d.mean.P = P; d.mean.blocks = (unsigned)((P + 3) / 4);
+        }
         if (step) {
             d.Wt = step->W + pl.off[l];
             d.Vt = step->V ? step->V + pl.off[l] : nullptr;

@@ -31,8 +31,6 @@
 
 namespace easgd {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 static constexpr int XS_FLOATS = 6144;       // LDS for the [X 1] slices of a pass (24 KiB)
 static constexpr int DS_FLOATS = 6144;       // LDS for the dZ rows of a pass (24 KiB)
 static constexpr int MAX_PASS_WORKERS = 8;   // workers whose replica values a thread holds in registers per pass
