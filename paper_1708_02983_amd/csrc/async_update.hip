@@ -21,18 +21,33 @@
 
 namespace easgd {
 
+
 // the schedule travels in the kernel arguments
 struct Schedule {
     int n;
     unsigned char worker[EASGD_MAX_SCHEDULE];
 };
 
+template <bool NT, typename T>
+__device__ __forceinline__ T ld_stream(const T *p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+template <bool NT, typename T>
+__device__ __forceinline__ void st_stream(T *p, T v)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // One tile of the 128-bit path (the structure of the synchronous kernel's tile: thread-owned groups
 // j0 + q*STRIDE; FULL = every group of the block lies inside the row; no load is guarded in either form: lanes
 // past the end of the row read its last group and store nothing).
 template <bool MOM, int GROUPS, size_t STRIDE, bool FULL>
-__device__ __forceinline__ void async_tile(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
-                                           float *__restrict__ Wc, const Schedule &sch, size_t n4, size_t ld, size_t j0,
+__device__ __forceinline__ void async_tile(f32x4 *__restrict__ W, f32x4 *__restrict__ V, const f32x4 *__restrict__ G,
+                                           f32x4 *__restrict__ Wc, const Schedule &sch, size_t n4, size_t ld4, size_t j0,
                                            float eta, float rho, float alpha, float delta)
 {
     f32x4 c[GROUPS];
@@ -40,17 +55,17 @@ __device__ __forceinline__ void async_tile(float *__restrict__ W, float *__restr
 #pragma unroll
     for (int q = 0; q < GROUPS; ++q) {
         const size_t j = j0 + (size_t)q * STRIDE;
-        jl[q] = 4 * ((FULL || j < n4) ? j : n4 - 1);
-        c[q] = load4<false>(Wc + jl[q]);
+        jl[q] = (FULL || j < n4) ? j : n4 - 1;
+        c[q] = Wc[jl[q]];
     }
     for (int t = 0; t < sch.n; ++t) {                    // the master's turns, one worker each, in schedule order
-        const size_t row = (size_t)sch.worker[t] * ld;
+        const size_t row = (size_t)sch.worker[t] * ld4;
         f32x4 w[GROUPS], g[GROUPS], v[GROUPS];
 #pragma unroll
         for (int q = 0; q < GROUPS; ++q) {
-            w[q] = load4<true>(W + row + jl[q]);
-            g[q] = load4<true>(G + row + jl[q]);
-            if constexpr (MOM) v[q] = load4<true>(V + row + jl[q]);
+            w[q] = ld_stream<true>(W + row + jl[q]);
+            g[q] = ld_stream<true>(G + row + jl[q]);
+            if constexpr (MOM) v[q] = ld_stream<true>(V + row + jl[q]);
         }
         if constexpr (!FULL) {
 #pragma unroll
@@ -70,8 +85,8 @@ __device__ __forceinline__ void async_tile(float *__restrict__ W, float *__restr
 #pragma unroll
         for (int q = 0; q < GROUPS; ++q) {
             if (FULL || j0 + (size_t)q * STRIDE < n4) {
-                store4<true>(W + row + jl[q], w[q]);
-                if constexpr (MOM) store4<true>(V + row + jl[q], v[q]);
+                st_stream<true>(W + row + jl[q], w[q]);
+                if constexpr (MOM) st_stream<true>(V + row + jl[q], v[q]);
             }
         }
         // a worker that comes up again later in the schedule must find these stores done
@@ -79,10 +94,10 @@ __device__ __forceinline__ void async_tile(float *__restrict__ W, float *__restr
     }
 #pragma unroll
     for (int q = 0; q < GROUPS; ++q)
-        if (FULL || j0 + (size_t)q * STRIDE < n4) store4<false>(Wc + jl[q], c[q]);
+        if (FULL || j0 + (size_t)q * STRIDE < n4) Wc[jl[q]] = c[q];
 }
 
-// One parameter, every turn (the N % 4 tail).
+// One parameter, every turn (the scalar path and the N % 4 tail).
 template <bool MOM>
 __device__ __forceinline__ void async_scalar(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
                                              float *__restrict__ Wc, const Schedule &sch, size_t j, size_t ld,
@@ -101,21 +116,25 @@ __device__ __forceinline__ void async_scalar(float *__restrict__ W, float *__res
 }
 
 template <bool MOM, int GROUPS, bool DIES>
-__device__ __forceinline__ void async_vec4_body(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
-                                                float *__restrict__ Wc, const Schedule &sch, size_t N, size_t ld,
+__device__ __forceinline__ void async_vec4_body(float *__restrict__ Wp, float *__restrict__ Vp, const float *__restrict__ Gp,
+                                                float *__restrict__ Wcp, const Schedule &sch, size_t N, size_t ld,
                                                 float eta, float rho, float alpha, float delta)
 {
     typedef TileMap<GROUPS, DIES> Map;
-    const size_t n4 = N / 4;
+    f32x4 *__restrict__ W = (f32x4 *)Wp;
+    f32x4 *__restrict__ V = (f32x4 *)Vp;
+    const f32x4 *__restrict__ G = (const f32x4 *)Gp;
+    f32x4 *__restrict__ Wc = (f32x4 *)Wcp;
+    const size_t n4 = N / 4, ld4 = ld / 4;
     const size_t n_tiles = Map::tiles(n4);
     for (size_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const size_t j0 = Map::first(t, threadIdx.x);
-        if (Map::last(t) < n4) async_tile<MOM, GROUPS, Map::STRIDE, true>(W, V, G, Wc, sch, n4, ld, j0, eta, rho, alpha, delta);
-        else async_tile<MOM, GROUPS, Map::STRIDE, false>(W, V, G, Wc, sch, n4, ld, j0, eta, rho, alpha, delta);
+        if (Map::last(t) < n4) async_tile<MOM, GROUPS, Map::STRIDE, true>(W, V, G, Wc, sch, n4, ld4, j0, eta, rho, alpha, delta);
+        else async_tile<MOM, GROUPS, Map::STRIDE, false>(W, V, G, Wc, sch, n4, ld4, j0, eta, rho, alpha, delta);
     }
     const size_t tail = N - n4 * 4;
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x < tail)
-        async_scalar<MOM>(W, V, G, Wc, sch, n4 * 4 + threadIdx.x, ld, eta, rho, alpha, delta);
+        async_scalar<MOM>(Wp, Vp, Gp, Wcp, sch, n4 * 4 + threadIdx.x, ld, eta, rho, alpha, delta);
 }
 
 template <bool MOM, int GROUPS>
@@ -134,6 +153,15 @@ void async_vec4_dies_kernel(float *__restrict__ W, float *__restrict__ V, const 
                             float eta, float rho, float alpha, float delta)
 {
     async_vec4_body<MOM, GROUPS, true>(W, V, G, Wc, sch, N, ld, eta, rho, alpha, delta);
+}
+
+template <bool MOM>
+__global__ __launch_bounds__(256) void async_scalar_kernel(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
+                                                           float *__restrict__ Wc, Schedule sch, size_t N, size_t ld,
+                                                           float eta, float rho, float alpha, float delta)
+{
+    for (size_t j = (size_t)blockIdx.x * 256 + threadIdx.x; j < N; j += (size_t)gridDim.x * 256)
+        async_scalar<MOM>(W, V, G, Wc, sch, j, ld, eta, rho, alpha, delta);
 }
 
 template <bool MOM>
@@ -159,14 +187,18 @@ static int async_round(float *W, float *V, const float *G, float *Wc, int P, siz
     if (n_order == 0) return EASGD_OK;                   // nobody is served: nothing to do
     hipStream_t s = static_cast<hipStream_t>(stream);
     const float alpha = eta * rho;
+    const bool vec = aligned16(W) && aligned16(G) && aligned16(Wc) && (!MOM || aligned16(V)) && (ld % 4 == 0);
     const UpdateShape shape = update_shape(N, MOM);
-    const dim3 grid((unsigned)shape.blocks);             // grid-stride loops cover what exceeds it
+    size_t blocks = vec ? shape.blocks : (N + 255) / 256;
+    if (blocks > 0x7fffffffu) blocks = 0x7fffffffu;      // grid-stride loops cover the rest
+    const dim3 grid((unsigned)blocks);
 #define EASGD_ASYNC(GR)                                                                                                       \
     do {                                                                                                                      \
         if (shape.dies) EASGD_LAUNCH((async_vec4_dies_kernel<MOM, GR>), grid, dim3(256), 0, s, W, V, G, Wc, sch, N, ld, eta, rho, alpha, delta); \
         else EASGD_LAUNCH((async_vec4_kernel<MOM, GR>), grid, dim3(256), 0, s, W, V, G, Wc, sch, N, ld, eta, rho, alpha, delta);               \
     } while (0)
-    if (shape.groups >= 4) EASGD_ASYNC(4);
+    if (!vec) EASGD_LAUNCH((async_scalar_kernel<MOM>), grid, dim3(256), 0, s, W, V, G, Wc, sch, N, ld, eta, rho, alpha, delta);
+    else if (shape.groups >= 4) EASGD_ASYNC(4);
     else if (shape.groups == 2) EASGD_ASYNC(2);
     else EASGD_ASYNC(1);
 #undef EASGD_ASYNC
@@ -177,27 +209,30 @@ static int async_round(float *W, float *V, const float *G, float *Wc, int P, siz
 // Block (worker i, tile): 256 threads, GROUPS 128-bit groups each.  Blocks are numbered worker-fastest, so the
 // blocks that work on the same tile of the center at the same time are those of different workers.
 template <bool MOM, int GROUPS>
-__global__ __launch_bounds__(256) void hogwild_vec4_kernel(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
-                                                           float *__restrict__ Wc, int P, size_t N, size_t ld,
+__global__ __launch_bounds__(256) void hogwild_vec4_kernel(float *__restrict__ Wp, float *__restrict__ Vp, const float *__restrict__ Gp,
+                                                           float *__restrict__ Wcp, int P, size_t N, size_t ld,
                                                            float eta, float rho, float alpha, float delta)
 {
-    const size_t n4 = N / 4;
+    f32x4 *__restrict__ W = (f32x4 *)Wp;
+    f32x4 *__restrict__ V = (f32x4 *)Vp;
+    const f32x4 *__restrict__ G = (const f32x4 *)Gp;
+    const size_t n4 = N / 4, ld4 = ld / 4;
     const size_t n_tiles = (n4 + (size_t)GROUPS * 256 - 1) / ((size_t)GROUPS * 256) + 1;   // the last tile is the scalar tail's
     const size_t total = n_tiles * (size_t)P;
     for (size_t id = blockIdx.x; id < total; id += gridDim.x) {
         const size_t tile = id / (size_t)P;
         const int i = (int)(id - tile * (size_t)P);
-        const size_t row = (size_t)i * ld;
+        const size_t row = (size_t)i * ld4;
         if (tile + 1 == n_tiles) {                       // N % 4 tail elements
             const size_t j = n4 * 4 + threadIdx.x;
             if (j < N) {
                 const size_t k = (size_t)i * ld + j;
-                float w = W[k], v = MOM ? V[k] : 0.f;
-                const float c = __hip_atomic_load(&Wc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const float d = worker_rule<MOM>(w, v, G[k], c, eta, rho, alpha, delta);
-                W[k] = w;
-                if constexpr (MOM) V[k] = v;
-                (void)unsafeAtomicAdd(&Wc[j], alpha * d);
+                float w = Wp[k], v = MOM ? Vp[k] : 0.f;
+                const float c = __hip_atomic_load(&Wcp[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const float d = worker_rule<MOM>(w, v, Gp[k], c, eta, rho, alpha, delta);
+                Wp[k] = w;
+                if constexpr (MOM) Vp[k] = v;
+                (void)unsafeAtomicAdd(&Wcp[j], alpha * d);
             }
             continue;
         }
@@ -205,21 +240,39 @@ __global__ __launch_bounds__(256) void hogwild_vec4_kernel(float *__restrict__ W
         for (int q = 0; q < GROUPS; ++q) {
             const size_t j = tile * ((size_t)GROUPS * 256) + (size_t)q * 256 + threadIdx.x;
             if (j < n4) {
-                f32x4 w = load4<true>(W + row + 4 * j), g = load4<true>(G + row + 4 * j), v = w, c;
-                if constexpr (MOM) v = load4<true>(V + row + 4 * j);
+                f32x4 w = ld_stream<true>(W + row + j), g = ld_stream<true>(G + row + j), v = w, c;
+                if constexpr (MOM) v = ld_stream<true>(V + row + j);
                 // the center as this worker finds it: whatever the other workers have added so far
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    c[e] = __hip_atomic_load(&Wc[4 * j + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    c[e] = __hip_atomic_load(&Wcp[4 * j + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const f32x4 d = worker_rule<MOM>(w, v, g, c, eta, rho, alpha, delta);
-                store4<true>(W + row + 4 * j, w);
-                if constexpr (MOM) store4<true>(V + row + 4 * j, v);
+                st_stream<true>(W + row + j, w);
+                if constexpr (MOM) st_stream<true>(V + row + j, v);
                 // lock-free master: the one-worker form of Eq. (2) as an atomic addition, no lock around read and add
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    (void)unsafeAtomicAdd(&Wc[4 * j + e], alpha * d[e]);      // the hardware's fp32 add at the L2 / memory side
+                    (void)unsafeAtomicAdd(&Wcp[4 * j + e], alpha * d[e]);      // the hardware's fp32 add at the L2 / memory side
             }
         }
+    }
+}
+
+template <bool MOM>
+__global__ __launch_bounds__(256) void hogwild_scalar_kernel(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
+                                                             float *__restrict__ Wc, int P, size_t N, size_t ld,
+                                                             float eta, float rho, float alpha, float delta)
+{
+    const size_t total = N * (size_t)P;
+    for (size_t id = (size_t)blockIdx.x * 256 + threadIdx.x; id < total; id += (size_t)gridDim.x * 256) {
+        const size_t j = id % N;
+        const size_t k = (id / N) * ld + j;
+        float w = W[k], v = MOM ? V[k] : 0.f;
+        const float c = __hip_atomic_load(&Wc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float d = worker_rule<MOM>(w, v, G[k], c, eta, rho, alpha, delta);
+        W[k] = w;
+        if constexpr (MOM) V[k] = v;
+        (void)unsafeAtomicAdd(&Wc[j], alpha * d);
     }
 }
 
@@ -237,10 +290,17 @@ static int hogwild_round(float *W, float *V, const float *G, float *Wc, int P, s
     clear_error();
     hipStream_t s = static_cast<hipStream_t>(stream);
     const float alpha = eta * rho;
-    constexpr int GROUPS = 2;
-    size_t blocks = ((N / 4 + (size_t)GROUPS * 256 - 1) / ((size_t)GROUPS * 256) + 1) * (size_t)P;
-    if (blocks > 0x7fffffffu) blocks = 0x7fffffffu;
-    EASGD_LAUNCH((hogwild_vec4_kernel<MOM, GROUPS>), dim3((unsigned)blocks), dim3(256), 0, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
+    const bool vec = aligned16(W) && aligned16(G) && aligned16(Wc) && (!MOM || aligned16(V)) && (ld % 4 == 0);
+    if (vec) {
+        constexpr int GROUPS = 2;
+        size_t blocks = ((N / 4 + (size_t)GROUPS * 256 - 1) / ((size_t)GROUPS * 256) + 1) * (size_t)P;
+        if (blocks > 0x7fffffffu) blocks = 0x7fffffffu;
+        EASGD_LAUNCH((hogwild_vec4_kernel<MOM, GROUPS>), dim3((unsigned)blocks), dim3(256), 0, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
+    } else {
+        size_t blocks = (N * (size_t)P + 255) / 256;
+        if (blocks > 0x7fffffffu) blocks = 0x7fffffffu;
+        EASGD_LAUNCH((hogwild_scalar_kernel<MOM>), dim3((unsigned)blocks), dim3(256), 0, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
+    }
     return check_launch(name);
 }
 

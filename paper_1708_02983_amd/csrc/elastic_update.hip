@@ -21,20 +21,53 @@
 
 namespace easgd {
 
-// One parameter (the N % 4 tail).
-template <bool MOM>
-__device__ __forceinline__ void elastic_scalar(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
-                                               float *__restrict__ Wc, int P, size_t j, size_t ld,
-                                               float eta, float rho, float alpha, float delta)
+template <bool NT, typename T>
+__device__ __forceinline__ T stream_load(const T *p)
 {
-    const float c = Wc[j];
-    float acc = 0.f;
-    for (int i = 0; i < P; ++i) {             // ascending worker order
-        const size_t k = (size_t)i * ld + j;
-        float w = W[k], v = MOM ? V[k] : 0.f;
-        acc += worker_rule<MOM>(w, v, G[k], c, eta, rho, alpha, delta);
-        W[k] = w;
-        if constexpr (MOM) V[k] = v;
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+template <bool NT, typename T>
+__device__ __forceinline__ void stream_store(T *p, T v)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
+// T-wide groups [0, n_groups) of every row; rows are `ld_groups` groups apart.
+template <bool MOM, bool NT, int UNROLL, typename T>
+__device__ __forceinline__ void elastic_group(T *__restrict__ W, T *__restrict__ V, const T *__restrict__ G,
+                                              T *__restrict__ Wc, int P, size_t j, size_t ld_groups,
+                                              float eta, float rho, float alpha, float delta)
+{
+    const T c = Wc[j];
+    T acc = c - c;                            // zero of type T
+    int i = 0;
+    for (; i + UNROLL <= P; i += UNROLL) {
+        T w[UNROLL], g[UNROLL], v[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const size_t k = (size_t)(i + u) * ld_groups + j;
+            w[u] = stream_load<NT>(W + k);
+            g[u] = stream_load<NT>(G + k);
+            if constexpr (MOM) v[u] = stream_load<NT>(V + k);
+        }
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const size_t k = (size_t)(i + u) * ld_groups + j;
+            acc += worker_rule<MOM>(w[u], v[u], g[u], c, eta, rho, alpha, delta);   // ascending i
+            stream_store<NT>(W + k, w[u]);
+            if constexpr (MOM) stream_store<NT>(V + k, v[u]);
+        }
+    }
+    for (; i < P; ++i) {
+        const size_t k = (size_t)i * ld_groups + j;
+        T w = stream_load<NT>(W + k), g = stream_load<NT>(G + k), v = w;
+        if constexpr (MOM) v = stream_load<NT>(V + k);
+        acc += worker_rule<MOM>(w, v, g, c, eta, rho, alpha, delta);
+        stream_store<NT>(W + k, w);
+        if constexpr (MOM) stream_store<NT>(V + k, v);
     }
     Wc[j] = fma_s(alpha, acc, c);                 // Eq. (2)
 }
@@ -46,32 +79,32 @@ __device__ __forceinline__ void elastic_scalar(float *__restrict__ W, float *__r
 // for at the merge: one round trip to memory per group and worker, in a block that the whole launch then waits
 // for when N is small enough that every block is resident at once.)
 template <bool MOM, bool NT, int GROUPS, size_t STRIDE, bool FULL>
-__device__ __forceinline__ void elastic_tile(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
-                                             float *__restrict__ Wc, int P, size_t n4, size_t ld, size_t j0,
+__device__ __forceinline__ void elastic_tile(f32x4 *__restrict__ W, f32x4 *__restrict__ V, const f32x4 *__restrict__ G,
+                                             f32x4 *__restrict__ Wc, int P, size_t n4, size_t ld4, size_t j0,
                                              float eta, float rho, float alpha, float delta)
 {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 c[GROUPS], acc[GROUPS];
-    size_t jl[GROUPS];                                // first parameter of the group this lane loads: its own, or the row's last one
+    size_t jl[GROUPS];                                // the group this lane loads: its own, or the row's last one
 #pragma unroll
     for (int q = 0; q < GROUPS; ++q) {
         const size_t j = j0 + (size_t)q * STRIDE;
-        jl[q] = 4 * ((FULL || j < n4) ? j : n4 - 1);
-        c[q] = load4<false>(Wc + jl[q]);                             // the "broadcast" of the center, once per parameter
+        jl[q] = (FULL || j < n4) ? j : n4 - 1;
+        c[q] = Wc[jl[q]];                             // the "broadcast" of the center, once per parameter
         acc[q] = zero;
     }
     for (int i = 0; i < P; ++i) {                     // ascending worker order: fixed summation order
-        const size_t row = (size_t)i * ld;
+        const size_t row = (size_t)i * ld4;
         f32x4 w[GROUPS], g[GROUPS], v[GROUPS];
         // stream by stream (the gradients, then the replica, then the momentum buffer; the stores likewise), not group
         // by group: consecutive requests of a wavefront then walk one array, 0.5-0.9 % faster at N = 61 M
 #pragma unroll
-        for (int q = 0; q < GROUPS; ++q) g[q] = load4<NT>(G + row + jl[q]);
+        for (int q = 0; q < GROUPS; ++q) g[q] = stream_load<NT>(G + row + jl[q]);
 #pragma unroll
-        for (int q = 0; q < GROUPS; ++q) w[q] = load4<NT>(W + row + jl[q]);
+        for (int q = 0; q < GROUPS; ++q) w[q] = stream_load<NT>(W + row + jl[q]);
         if constexpr (MOM) {
 #pragma unroll
-            for (int q = 0; q < GROUPS; ++q) v[q] = load4<NT>(V + row + jl[q]);
+            for (int q = 0; q < GROUPS; ++q) v[q] = stream_load<NT>(V + row + jl[q]);
         }
         if constexpr (!FULL) {
 #pragma unroll
@@ -91,46 +124,50 @@ __device__ __forceinline__ void elastic_tile(float *__restrict__ W, float *__res
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (FULL) {
 #pragma unroll
-            for (int q = 0; q < GROUPS; ++q) store4<NT>(W + row + jl[q], w[q]);
+            for (int q = 0; q < GROUPS; ++q) stream_store<NT>(W + row + jl[q], w[q]);
             if constexpr (MOM) {
 #pragma unroll
-                for (int q = 0; q < GROUPS; ++q) store4<NT>(V + row + jl[q], v[q]);
+                for (int q = 0; q < GROUPS; ++q) stream_store<NT>(V + row + jl[q], v[q]);
             }
         } else {
 #pragma unroll
             for (int q = 0; q < GROUPS; ++q) {
                 if (j0 + (size_t)q * STRIDE < n4) {
-                    store4<NT>(W + row + jl[q], w[q]);
-                    if constexpr (MOM) store4<NT>(V + row + jl[q], v[q]);
+                    stream_store<NT>(W + row + jl[q], w[q]);
+                    if constexpr (MOM) stream_store<NT>(V + row + jl[q], v[q]);
                 }
             }
         }
     }
 #pragma unroll
     for (int q = 0; q < GROUPS; ++q)
-        if (FULL || j0 + (size_t)q * STRIDE < n4) store4<false>(Wc + jl[q], fma_s(alpha, acc[q], c[q]));   // Eq. (2)
+        if (FULL || j0 + (size_t)q * STRIDE < n4) Wc[jl[q]] = fma_s(alpha, acc[q], c[q]);   // Eq. (2)
 }
 
 // 128-bit path.  The N % 4 tail elements are handled as scalars by the last block.
 template <bool MOM, bool NT, int GROUPS, bool DIES>
-__device__ __forceinline__ void elastic_vec4_body(float *__restrict__ W, float *__restrict__ V,
-                                                  const float *__restrict__ G, float *__restrict__ Wc,
+__device__ __forceinline__ void elastic_vec4_body(float *__restrict__ Wp, float *__restrict__ Vp,
+                                                  const float *__restrict__ Gp, float *__restrict__ Wcp,
                                                   int P, size_t N, size_t ld,
                                                   float eta, float rho, float alpha, float delta)
 {
     typedef TileMap<GROUPS, DIES> Map;
-    const size_t n4 = N / 4;
+    f32x4 *__restrict__ W = (f32x4 *)Wp;
+    f32x4 *__restrict__ V = (f32x4 *)Vp;
+    const f32x4 *__restrict__ G = (const f32x4 *)Gp;
+    f32x4 *__restrict__ Wc = (f32x4 *)Wcp;
+    const size_t n4 = N / 4, ld4 = ld / 4;
     const size_t n_tiles = Map::tiles(n4);
     for (size_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const size_t j0 = Map::first(t, threadIdx.x);
         if (Map::last(t) < n4)                        // uniform for the block
-            elastic_tile<MOM, NT, GROUPS, Map::STRIDE, true>(W, V, G, Wc, P, n4, ld, j0, eta, rho, alpha, delta);
+            elastic_tile<MOM, NT, GROUPS, Map::STRIDE, true>(W, V, G, Wc, P, n4, ld4, j0, eta, rho, alpha, delta);
         else
-            elastic_tile<MOM, NT, GROUPS, Map::STRIDE, false>(W, V, G, Wc, P, n4, ld, j0, eta, rho, alpha, delta);
+            elastic_tile<MOM, NT, GROUPS, Map::STRIDE, false>(W, V, G, Wc, P, n4, ld4, j0, eta, rho, alpha, delta);
     }
     const size_t tail = N - n4 * 4;
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x < tail)
-        elastic_scalar<MOM>(W, V, G, Wc, P, n4 * 4 + threadIdx.x, ld, eta, rho, alpha, delta);
+        elastic_group<MOM, false, 1, float>(Wp, Vp, Gp, Wcp, P, n4 * 4 + threadIdx.x, ld, eta, rho, alpha, delta);
 }
 
 // Contiguous tiles (small N, or by option).
@@ -162,38 +199,54 @@ void elastic_vec4_dies_kernel(float *__restrict__ W, float *__restrict__ V, cons
 // W_i - Wc in registers; the partial sums meet in LDS and wavefront 0 adds them in the fixed order
 // v = 0, 1, 2, 3 before it applies Eq. (2).  The result is reproducible from run to run.
 template <bool MOM>
-__global__ __launch_bounds__(256) void elastic_split_kernel(float *__restrict__ W, float *__restrict__ V,
-                                                            const float *__restrict__ G, float *__restrict__ Wc,
+__global__ __launch_bounds__(256) void elastic_split_kernel(float *__restrict__ Wp, float *__restrict__ Vp,
+                                                            const float *__restrict__ Gp, float *__restrict__ Wcp,
                                                             int P, size_t N, size_t ld,
                                                             float eta, float rho, float alpha, float delta)
 {
     __shared__ f32x4 partial[4][64];
-    const size_t n4 = N / 4;
+    f32x4 *__restrict__ W = (f32x4 *)Wp;
+    f32x4 *__restrict__ V = (f32x4 *)Vp;
+    const f32x4 *__restrict__ G = (const f32x4 *)Gp;
+    f32x4 *__restrict__ Wc = (f32x4 *)Wcp;
+    const size_t n4 = N / 4, ld4 = ld / 4;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t j = (size_t)blockIdx.x * 64 + lane;
     const bool live = j < n4;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    const f32x4 c = live ? load4<false>(Wc + 4 * j) : zero;
+    const f32x4 c = live ? Wc[j] : zero;
     f32x4 acc = zero;
     if (live) {
         for (int i = wave; i < P; i += 4) {
-            const size_t k = (size_t)i * ld + 4 * j;
-            f32x4 w = load4<false>(W + k), g = load4<false>(G + k), v = w;
-            if constexpr (MOM) v = load4<false>(V + k);
+            const size_t k = (size_t)i * ld4 + j;
+            f32x4 w = W[k], g = G[k], v = w;
+            if constexpr (MOM) v = V[k];
             acc += worker_rule<MOM>(w, v, g, c, eta, rho, alpha, delta);
-            store4<false>(W + k, w);
-            if constexpr (MOM) store4<false>(V + k, v);
+            W[k] = w;
+            if constexpr (MOM) V[k] = v;
         }
     }
     partial[wave][lane] = acc;
     __syncthreads();
     if (wave == 0 && live) {
         const f32x4 sum = ((partial[0][lane] + partial[1][lane]) + partial[2][lane]) + partial[3][lane];
-        store4<false>(Wc + 4 * j, fma_s(alpha, sum, c));      // Eq. (2)
+        Wc[j] = fma_s(alpha, sum, c);             // Eq. (2)
     }
     const size_t tail = N - n4 * 4;
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x < tail)
-        elastic_scalar<MOM>(W, V, G, Wc, P, n4 * 4 + threadIdx.x, ld, eta, rho, alpha, delta);
+        elastic_group<MOM, false, 1, float>(Wp, Vp, Gp, Wcp, P, n4 * 4 + threadIdx.x, ld, eta, rho, alpha, delta);
+}
+
+// Scalar path for operands that are not 16-byte aligned or ld % 4 != 0.
+template <bool MOM>
+__global__ __launch_bounds__(256) void elastic_scalar_kernel(float *__restrict__ W, float *__restrict__ V,
+                                                             const float *__restrict__ G, float *__restrict__ Wc,
+                                                             int P, size_t N, size_t ld,
+                                                             float eta, float rho, float alpha, float delta)
+{
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x; j < N; j += stride)
+        elastic_group<MOM, false, 4, float>(W, V, G, Wc, P, j, ld, eta, rho, alpha, delta);
 }
 
 template <bool MOM, bool NT, bool DIES>
@@ -229,21 +282,26 @@ static int elastic_round(float *W, float *V, const float *G, float *Wc, int P, s
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const float alpha = eta * rho;            // elastic coefficient of workers and center
-    // groups per thread, tile map and grid (the scalar tail rides on the last block)
+    const bool vec = aligned16(W) && aligned16(G) && aligned16(Wc) && (!MOM || aligned16(V)) && (ld % 4 == 0);
+    // vector path: groups per thread, tile map and grid (the scalar tail rides on the last block)
     const UpdateShape shape = update_shape(N, MOM);
-    const dim3 grid((unsigned)shape.blocks);           // grid-stride loops cover what exceeds it
+    size_t blocks = vec ? shape.blocks : (N + 255) / 256;
+    if (blocks > 0x7fffffffu) blocks = 0x7fffffffu;    // grid-stride loop covers the rest
+    const dim3 grid((unsigned)blocks);
     const int groups = shape.groups;
     // few parameters and several workers: split the workers over the wavefronts of a block
-    const bool split = P >= 4 && (N / 4 + 255) / 256 < (size_t)(2 * num_cus());
+    const bool split = vec && P >= 4 && (N / 4 + 255) / 256 < (size_t)(2 * num_cus());
     if (split) {
         const dim3 split_grid((unsigned)((N / 4 + 63) / 64 > 0 ? (N / 4 + 63) / 64 : 1));
         EASGD_LAUNCH((elastic_split_kernel<MOM>), split_grid, dim3(256), 0, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
-    } else {
+    } else if (vec) {
         const bool nt = update_nontemporal(N * ((MOM ? 20 : 12) * (size_t)P + 8));
         if (shape.dies && nt) launch_vec4<MOM, true, true>(groups, grid, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
         else if (shape.dies) launch_vec4<MOM, false, true>(groups, grid, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
         else if (nt) launch_vec4<MOM, true, false>(groups, grid, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
         else launch_vec4<MOM, false, false>(groups, grid, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
+    } else {
+        EASGD_LAUNCH((elastic_scalar_kernel<MOM>), grid, dim3(256), 0, s, W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
     }
     return check_launch(name);
 }
@@ -303,8 +361,8 @@ __device__ __forceinline__ void sgd_rule(T &w, T &v, T s, float eta, float mu)
 
 // One tile of the 128-bit path (FULL as in elastic_tile).
 template <bool MOM, bool NT, int GROUPS, size_t STRIDE, bool FULL>
-__device__ __forceinline__ void sync_sgd_tile(float *__restrict__ W, float *__restrict__ V, const float *__restrict__ G,
-                                              int P, size_t n4, size_t ld, size_t j0, float eta, float mu)
+__device__ __forceinline__ void sync_sgd_tile(f32x4 *__restrict__ W, f32x4 *__restrict__ V, const f32x4 *__restrict__ G,
+                                              int P, size_t n4, size_t ld4, size_t j0, float eta, float mu)
 {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 s[GROUPS];
@@ -312,25 +370,25 @@ __device__ __forceinline__ void sync_sgd_tile(float *__restrict__ W, float *__re
 #pragma unroll
     for (int q = 0; q < GROUPS; ++q) {
         const size_t j = j0 + (size_t)q * STRIDE;
-        jl[q] = 4 * ((FULL || j < n4) ? j : n4 - 1);
+        jl[q] = (FULL || j < n4) ? j : n4 - 1;
         s[q] = zero;
     }
     for (int i = 0; i < P; ++i) {                     // ascending worker order: fixed summation order
-        const size_t row = (size_t)i * ld;
+        const size_t row = (size_t)i * ld4;
         f32x4 g[GROUPS];
 #pragma unroll
-        for (int q = 0; q < GROUPS; ++q) g[q] = load4<NT>(G + row + jl[q]);
+        for (int q = 0; q < GROUPS; ++q) g[q] = stream_load<NT>(G + row + jl[q]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < GROUPS; ++q) s[q] += g[q];
     }
     for (int i = 0; i < P; ++i) {
-        const size_t row = (size_t)i * ld;
+        const size_t row = (size_t)i * ld4;
         f32x4 w[GROUPS], v[GROUPS];
 #pragma unroll
         for (int q = 0; q < GROUPS; ++q) {
-            w[q] = load4<NT>(W + row + jl[q]);
-            if constexpr (MOM) v[q] = load4<NT>(V + row + jl[q]);
+            w[q] = stream_load<NT>(W + row + jl[q]);
+            if constexpr (MOM) v[q] = stream_load<NT>(V + row + jl[q]);
         }
         if constexpr (!FULL) {
 #pragma unroll
@@ -345,17 +403,17 @@ __device__ __forceinline__ void sync_sgd_tile(float *__restrict__ W, float *__re
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (FULL) {
 #pragma unroll
-            for (int q = 0; q < GROUPS; ++q) store4<NT>(W + row + jl[q], w[q]);
+            for (int q = 0; q < GROUPS; ++q) stream_store<NT>(W + row + jl[q], w[q]);
             if constexpr (MOM) {
 #pragma unroll
-                for (int q = 0; q < GROUPS; ++q) store4<NT>(V + row + jl[q], v[q]);
+                for (int q = 0; q < GROUPS; ++q) stream_store<NT>(V + row + jl[q], v[q]);
             }
         } else {
 #pragma unroll
             for (int q = 0; q < GROUPS; ++q) {
                 if (j0 + (size_t)q * STRIDE < n4) {
-                    store4<NT>(W + row + jl[q], w[q]);
-                    if constexpr (MOM) store4<NT>(V + row + jl[q], v[q]);
+                    stream_store<NT>(W + row + jl[q], w[q]);
+                    if constexpr (MOM) stream_store<NT>(V + row + jl[q], v[q]);
                 }
             }
         }
@@ -363,28 +421,31 @@ __device__ __forceinline__ void sync_sgd_tile(float *__restrict__ W, float *__re
 }
 
 template <bool MOM, bool NT, int GROUPS, bool DIES>
-__device__ __forceinline__ void sync_sgd_vec4_body(float *__restrict__ W, float *__restrict__ V,
-                                                   const float *__restrict__ G, int P, size_t N, size_t ld,
+__device__ __forceinline__ void sync_sgd_vec4_body(float *__restrict__ Wp, float *__restrict__ Vp,
+                                                   const float *__restrict__ Gp, int P, size_t N, size_t ld,
                                                    float eta, float mu)
 {
     typedef TileMap<GROUPS, DIES> Map;
-    const size_t n4 = N / 4;
+    f32x4 *__restrict__ W = (f32x4 *)Wp;
+    f32x4 *__restrict__ V = (f32x4 *)Vp;
+    const f32x4 *__restrict__ G = (const f32x4 *)Gp;
+    const size_t n4 = N / 4, ld4 = ld / 4;
     const size_t n_tiles = Map::tiles(n4);
     for (size_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const size_t j0 = Map::first(t, threadIdx.x);
-        if (Map::last(t) < n4) sync_sgd_tile<MOM, NT, GROUPS, Map::STRIDE, true>(W, V, G, P, n4, ld, j0, eta, mu);
-        else sync_sgd_tile<MOM, NT, GROUPS, Map::STRIDE, false>(W, V, G, P, n4, ld, j0, eta, mu);
+        if (Map::last(t) < n4) sync_sgd_tile<MOM, NT, GROUPS, Map::STRIDE, true>(W, V, G, P, n4, ld4, j0, eta, mu);
+        else sync_sgd_tile<MOM, NT, GROUPS, Map::STRIDE, false>(W, V, G, P, n4, ld4, j0, eta, mu);
     }
     const size_t tail = N - n4 * 4;
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x < tail) {
         const size_t k = n4 * 4 + threadIdx.x;
         float s = 0.f;
-        for (int i = 0; i < P; ++i) s += G[(size_t)i * ld + k];
+        for (int i = 0; i < P; ++i) s += Gp[(size_t)i * ld + k];
         for (int i = 0; i < P; ++i) {
-            float w = W[(size_t)i * ld + k], v = MOM ? V[(size_t)i * ld + k] : 0.f;
+            float w = Wp[(size_t)i * ld + k], v = MOM ? Vp[(size_t)i * ld + k] : 0.f;
             sgd_rule<MOM>(w, v, s, eta, mu);
-            W[(size_t)i * ld + k] = w;
-            if constexpr (MOM) V[(size_t)i * ld + k] = v;
+            Wp[(size_t)i * ld + k] = w;
+            if constexpr (MOM) Vp[(size_t)i * ld + k] = v;
         }
     }
 }
@@ -404,6 +465,24 @@ void sync_sgd_vec4_dies_kernel(float *__restrict__ W, float *__restrict__ V, con
                                int P, size_t N, size_t ld, float eta, float mu)
 {
     sync_sgd_vec4_body<MOM, NT, GROUPS, true>(W, V, G, P, N, ld, eta, mu);
+}
+
+// Any alignment: one thread per parameter.
+template <bool MOM>
+__global__ __launch_bounds__(256) void sync_sgd_scalar_kernel(float *__restrict__ W, float *__restrict__ V,
+                                                              const float *__restrict__ G, int P, size_t N, size_t ld,
+                                                              float eta, float mu)
+{
+    for (size_t k = (size_t)blockIdx.x * 256 + threadIdx.x; k < N; k += (size_t)gridDim.x * 256) {
+        float s = 0.f;
+        for (int i = 0; i < P; ++i) s += G[(size_t)i * ld + k];
+        for (int i = 0; i < P; ++i) {
+            float w = W[(size_t)i * ld + k], v = MOM ? V[(size_t)i * ld + k] : 0.f;
+            sgd_rule<MOM>(w, v, s, eta, mu);
+            W[(size_t)i * ld + k] = w;
+            if constexpr (MOM) V[(size_t)i * ld + k] = v;
+        }
+    }
 }
 
 template <bool MOM, bool NT, bool DIES>
@@ -434,10 +513,14 @@ static int sync_sgd(float *W, float *V, const float *G, int P, size_t N, size_t 
         return fail(EASGD_EINVAL, "%s: fp32 pointers must be 4-byte aligned", name);
     clear_error();
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const bool vec = aligned16(W) && aligned16(G) && (!MOM || aligned16(V)) && (ld % 4 == 0);
     const UpdateShape shape = update_shape(N, MOM);
-    const dim3 grid((unsigned)shape.blocks);           // grid-stride loops cover what exceeds it
+    size_t blocks = vec ? shape.blocks : (N + 255) / 256;
+    if (blocks > 0x7fffffffu) blocks = 0x7fffffffu;    // grid-stride loops cover the rest
+    const dim3 grid((unsigned)blocks);
     const bool nt = update_nontemporal(N * (MOM ? 20 : 12) * (size_t)P);
-    if (shape.dies && nt) launch_sync_sgd<MOM, true, true>(shape.groups, grid, s, W, V, G, P, N, ld, eta, mu);
+    if (!vec) EASGD_LAUNCH((sync_sgd_scalar_kernel<MOM>), grid, dim3(256), 0, s, W, V, G, P, N, ld, eta, mu);
+    else if (shape.dies && nt) launch_sync_sgd<MOM, true, true>(shape.groups, grid, s, W, V, G, P, N, ld, eta, mu);
     else if (shape.dies) launch_sync_sgd<MOM, false, true>(shape.groups, grid, s, W, V, G, P, N, ld, eta, mu);
     else if (nt) launch_sync_sgd<MOM, true, false>(shape.groups, grid, s, W, V, G, P, N, ld, eta, mu);
     else launch_sync_sgd<MOM, false, false>(shape.groups, grid, s, W, V, G, P, N, ld, eta, mu);

@@ -16,7 +16,6 @@
 namespace easgd {
 
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
-typedef unsigned short u16x4_any __attribute__((ext_vector_type(4), aligned(4)));     // at any even element of an aligned array
 
 // A gradient element as fp32: GT = unsigned short (bfloat16 storage) or float.
 __device__ __forceinline__ float grad_value(unsigned short g) { return bf16_widen(g); }
@@ -41,18 +40,18 @@ __device__ __forceinline__ void scalar_param(float *__restrict__ W, unsigned sho
     Wc[j] = fma_s(alpha, acc, c);                 // Eq. (2)
 }
 
-template <bool NT>
-__device__ __forceinline__ u16x4 load4(const unsigned short *p)
+template <bool NT, typename T>
+__device__ __forceinline__ T lp_load(const T *p)
 {
-    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u16x4_any *>(p));
-    else return *reinterpret_cast<const u16x4_any *>(p);
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
 }
 
-template <bool NT>
-__device__ __forceinline__ void store4(unsigned short *p, u16x4 v)
+template <bool NT, typename T>
+__device__ __forceinline__ void lp_store(T *p, T v)
 {
-    if constexpr (NT) __builtin_nontemporal_store((u16x4_any)v, reinterpret_cast<u16x4_any *>(p));
-    else *reinterpret_cast<u16x4_any *>(p) = v;
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
 
 template <typename T> struct Vec4;
@@ -65,9 +64,9 @@ template <> struct Vec4<unsigned short> { typedef u16x4 type; };
 // of two widths the stream-by-stream order of elastic_tile measured 1 % slower.
 // GT: storage type of the gradients (unsigned short = bfloat16, or float when only V is stored in 16 bits).
 template <bool MOM, bool NT, int GROUPS, size_t STRIDE, bool FULL, typename GT>
-__device__ __forceinline__ void elastic_bf16_tile(float *__restrict__ W, unsigned short *__restrict__ V,
-                                                  const GT *__restrict__ G, float *__restrict__ Wc,
-                                                  int P, size_t n4, size_t ld, size_t j0,
+__device__ __forceinline__ void elastic_bf16_tile(f32x4 *__restrict__ W, u16x4 *__restrict__ V,
+                                                  const typename Vec4<GT>::type *__restrict__ G, f32x4 *__restrict__ Wc,
+                                                  int P, size_t n4, size_t ld4, size_t j0,
                                                   float eta, float rho, float alpha, float delta)
 {
     typedef typename Vec4<GT>::type g4;
@@ -77,20 +76,20 @@ __device__ __forceinline__ void elastic_bf16_tile(float *__restrict__ W, unsigne
 #pragma unroll
     for (int q = 0; q < GROUPS; ++q) {
         const size_t j = j0 + (size_t)q * STRIDE;
-        jl[q] = 4 * ((FULL || j < n4) ? j : n4 - 1);
-        c[q] = load4<false>(Wc + jl[q]);
+        jl[q] = (FULL || j < n4) ? j : n4 - 1;
+        c[q] = Wc[jl[q]];
         acc[q] = zero;
     }
     for (int i = 0; i < P; ++i) {
-        const size_t row = (size_t)i * ld;
+        const size_t row = (size_t)i * ld4;
         f32x4 w[GROUPS];
         g4 g[GROUPS];
         u16x4 v[GROUPS];
 #pragma unroll
         for (int q = 0; q < GROUPS; ++q) {
-            w[q] = load4<NT>(W + row + jl[q]);
-            g[q] = load4<NT>(G + row + jl[q]);
-            if constexpr (MOM) v[q] = load4<NT>(V + row + jl[q]);
+            w[q] = lp_load<NT>(W + row + jl[q]);
+            g[q] = lp_load<NT>(G + row + jl[q]);
+            if constexpr (MOM) v[q] = lp_load<NT>(V + row + jl[q]);
         }
         if constexpr (!FULL) {
 #pragma unroll
@@ -117,36 +116,41 @@ __device__ __forceinline__ void elastic_bf16_tile(float *__restrict__ W, unsigne
 #pragma unroll
         for (int q = 0; q < GROUPS; ++q) {
             if (FULL || j0 + (size_t)q * STRIDE < n4) {
-                store4<NT>(W + row + jl[q], w[q]);
-                if constexpr (MOM) store4<NT>(V + row + jl[q], v[q]);
+                lp_store<NT>(W + row + jl[q], w[q]);
+                if constexpr (MOM) lp_store<NT>(V + row + jl[q], v[q]);
             }
         }
     }
 #pragma unroll
     for (int q = 0; q < GROUPS; ++q)
-        if (FULL || j0 + (size_t)q * STRIDE < n4) store4<false>(Wc + jl[q], fma_s(alpha, acc[q], c[q]));   // Eq. (2)
+        if (FULL || j0 + (size_t)q * STRIDE < n4) Wc[jl[q]] = fma_s(alpha, acc[q], c[q]);   // Eq. (2)
 }
 
 // The N % 4 tail rides on the last block.
 template <bool MOM, bool NT, int GROUPS, bool DIES, typename GT>
-__device__ __forceinline__ void elastic_bf16_vec4_body(float *__restrict__ W, unsigned short *__restrict__ V,
-                                                       const GT *__restrict__ G,
-                                                       float *__restrict__ Wc, int P, size_t N, size_t ld,
+__device__ __forceinline__ void elastic_bf16_vec4_body(float *__restrict__ Wp, unsigned short *__restrict__ Vp,
+                                                       const GT *__restrict__ Gp,
+                                                       float *__restrict__ Wcp, int P, size_t N, size_t ld,
                                                        float eta, float rho, float alpha, float delta)
 {
+    typedef typename Vec4<GT>::type g4;
     typedef TileMap<GROUPS, DIES> Map;
-    const size_t n4 = N / 4;
+    f32x4 *__restrict__ W = (f32x4 *)Wp;
+    u16x4 *__restrict__ V = (u16x4 *)Vp;
+    const g4 *__restrict__ G = (const g4 *)Gp;
+    f32x4 *__restrict__ Wc = (f32x4 *)Wcp;
+    const size_t n4 = N / 4, ld4 = ld / 4;
     const size_t n_tiles = Map::tiles(n4);
     for (size_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const size_t j0 = Map::first(t, threadIdx.x);
         if (Map::last(t) < n4)
-            elastic_bf16_tile<MOM, NT, GROUPS, Map::STRIDE, true, GT>(W, V, G, Wc, P, n4, ld, j0, eta, rho, alpha, delta);
+            elastic_bf16_tile<MOM, NT, GROUPS, Map::STRIDE, true, GT>(W, V, G, Wc, P, n4, ld4, j0, eta, rho, alpha, delta);
         else
-            elastic_bf16_tile<MOM, NT, GROUPS, Map::STRIDE, false, GT>(W, V, G, Wc, P, n4, ld, j0, eta, rho, alpha, delta);
+            elastic_bf16_tile<MOM, NT, GROUPS, Map::STRIDE, false, GT>(W, V, G, Wc, P, n4, ld4, j0, eta, rho, alpha, delta);
     }
     const size_t tail = N - n4 * 4;
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x < tail)
-        scalar_param<MOM, GT>(W, V, G, Wc, P, n4 * 4 + threadIdx.x, ld, eta, rho, alpha, delta);
+        scalar_param<MOM, GT>(Wp, Vp, Gp, Wcp, P, n4 * 4 + threadIdx.x, ld, eta, rho, alpha, delta);
 }
 
 template <bool MOM, bool NT, int GROUPS, typename GT>
@@ -168,7 +172,7 @@ void elastic_bf16_vec4_dies_kernel(float *__restrict__ W, unsigned short *__rest
     elastic_bf16_vec4_body<MOM, NT, GROUPS, true, GT>(W, V, G, Wc, P, N, ld, eta, rho, alpha, delta);
 }
 
-// 16-bit rows that start at odd halves of a 32-bit word: one thread per parameter.
+// Any alignment: one thread per parameter.
 template <bool MOM, typename GT>
 __global__ __launch_bounds__(256) void elastic_bf16_scalar_kernel(float *__restrict__ W, unsigned short *__restrict__ V,
                                                                   const GT *__restrict__ G,
@@ -198,6 +202,8 @@ static void launch_bf16(int groups, dim3 grid, hipStream_t s, float *W, unsigned
 #undef EASGD_BF16
 }
 
+inline bool aligned8(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; }
+
 template <bool MOM, typename GT>
 static int elastic_round_bf16(const char *name, float *W, unsigned short *V, const GT *G, float *Wc, int P, size_t N,
                               size_t ld, float eta, float rho, float delta, void *stream)
@@ -212,8 +218,8 @@ static int elastic_round_bf16(const char *name, float *W, unsigned short *V, con
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const float alpha = eta * rho;
-    // four 16-bit elements are one 64-bit access wherever their rows start on 32-bit words
-    const bool vec = aligned_to(G, 4) && (!MOM || aligned_to(V, 4)) && ((sizeof(GT) == 4 && !MOM) || ld % 2 == 0);
+    const bool g_aligned = sizeof(GT) == 4 ? aligned16(G) : aligned8(G);
+    const bool vec = aligned16(W) && aligned16(Wc) && g_aligned && (!MOM || aligned8(V)) && (ld % 4 == 0);
     const UpdateShape shape = update_shape(N, MOM);
     size_t blocks = vec ? shape.blocks : (N + 255) / 256;
     if (blocks > 0x7fffffffu) blocks = 0x7fffffffu;    // grid-stride loops cover the rest
