@@ -166,7 +166,7 @@ __device__ __forceinline__ f32x4 fetch4(const float *row, int idx0, int lim, int
 {
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     if (!row_valid) return v;
-    if (VEC && idx0 + 3 < lim) return *reinterpret_cast<const f32x4 *>(row + idx0);
+    if (VEC && idx0 + 3 < lim) return load4(row + idx0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int idx = idx0 + q;
@@ -187,7 +187,7 @@ constexpr int gemm_lds_floats()
 
 // The work of block `bid` of one product.  `lds` is the calling kernel's buffer of at least
 // gemm_lds_floats<...>() floats, 16-byte aligned: kernels that carry two products lend the same buffer to both.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int A_LAYOUT, int B_LAYOUT, bool VEC, int EPI, int MT = 32, bool ALONE = false>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int A_LAYOUT, int B_LAYOUT, bool VEC, int EPI, int MT = 32, bool ALONE = false, bool ANY_WIDTH = false>
 __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid, float *__restrict__ lds)
 {
     constexpr int NTHREADS = WAVES_M * WAVES_N * 64;
@@ -259,7 +259,9 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
             b_krel[it] = 4 * kq;
         } else {
             const int nq = c % (BN / 4), k = c / (BN / 4), n = n0 + 4 * nq;
-            b_ok[it] = (n + 3 < b_lim);
+            // a chunk that holds the end of a row runs into the next one: what it brings from there lands in columns that
+            // are never stored (the operand's last row is not read this way, see n_full)
+            b_ok[it] = (n + (ANY_WIDTH ? 0 : 3) < b_lim);
             b_src[it] = B + (size_t)k * p.ldb + (b_ok[it] ? n : 0);
             b_dst[it] = k * PITCH_B + 4 * nq;
             b_krel[it] = k;
@@ -273,11 +275,11 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
 #pragma unroll
         for (int it = 0; it < IT_A; ++it)
             if (CHUNKS_A % NTHREADS == 0 || tid + it * NTHREADS < CHUNKS_A)
-                ra[it] = *reinterpret_cast<const f32x4 *>(a_src[it] + (size_t)k0 * a_kstep);
+                ra[it] = load4(a_src[it] + (size_t)k0 * a_kstep);
 #pragma unroll
         for (int it = 0; it < IT_B; ++it)
             if (CHUNKS_B % NTHREADS == 0 || tid + it * NTHREADS < CHUNKS_B)
-                rb[it] = *reinterpret_cast<const f32x4 *>(b_src[it] + (size_t)k0 * b_kstep);
+                rb[it] = load4(b_src[it] + (size_t)k0 * b_kstep);
     };
     // The last slab of the K range when it is only partly inside the operands (128-bit path): a chunk is
     // either entirely inside or entirely outside along k (all limits are multiples of 4), so chunks outside
@@ -292,14 +294,14 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
             if (CHUNKS_A % NTHREADS != 0 && tid + it * NTHREADS >= CHUNKS_A) continue;
             ta_ok[it] = (A_LAYOUT == K_CONTIG) ? (k0 + a_krel[it] + 3 < a_klim) : (k0 + a_krel[it] < k_end);
             const int k_eff = ta_ok[it] ? k0 : ((A_LAYOUT == K_CONTIG) ? -a_krel[it] : k0 - a_krel[it]);
-            ra[it] = *reinterpret_cast<const f32x4 *>(a_src[it] + (ptrdiff_t)k_eff * (ptrdiff_t)a_kstep);
+            ra[it] = load4(a_src[it] + (ptrdiff_t)k_eff * (ptrdiff_t)a_kstep);
         }
 #pragma unroll
         for (int it = 0; it < IT_B; ++it) {
             if (CHUNKS_B % NTHREADS != 0 && tid + it * NTHREADS >= CHUNKS_B) continue;
             tb_ok[it] = (B_LAYOUT == K_CONTIG) ? (k0 + b_krel[it] + 3 < b_klim) : (k0 + b_krel[it] < k_end);
             const int k_eff = tb_ok[it] ? k0 : ((B_LAYOUT == K_CONTIG) ? -b_krel[it] : k0 - b_krel[it]);
-            rb[it] = *reinterpret_cast<const f32x4 *>(b_src[it] + (ptrdiff_t)k_eff * (ptrdiff_t)b_kstep);
+            rb[it] = load4(b_src[it] + (ptrdiff_t)k_eff * (ptrdiff_t)b_kstep);
         }
     };
     // replaces the chunks of the tail slab that lie outside along k (called on the registers before store_lds)
@@ -457,17 +459,21 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
     };
     auto nothing = [] {};
 
-    // All slabs of a block go through the 128-bit pipeline when the operands allow 128-bit loads; the
-    // last slab may be partial (n_full counts the slabs that lie fully inside both operands along k).
+    // All slabs of a block go through the 128-bit pipeline when the operands allow 128-bit loads; the last slab may be
+    // partial (n_full counts the slabs that lie fully inside both operands along k).  ANY_WIDTH: limits that are no
+    // multiples of 4, for a k-contiguous A and an n-contiguous B.  There the partial slab is loaded element by element,
+    // and a chunk at the end of a row of B reaches into the next row, so the last row is left to the partial slab.  (A
+    // kernel of its own: the guarded loads cost registers that the center rule's wavefronts need beside the others.)
+    static_assert(!ANY_WIDTH || (VEC && A_LAYOUT == K_CONTIG && B_LAYOUT == MN_CONTIG), "the forward products");
     const int n_slabs = (k_end - k_begin + BK - 1) / BK;
+    const bool vec_ok = VEC && (ANY_WIDTH || ((p.a_lim & 3) == 0 && (b_lim & 3) == 0 &&
+                        (A_LAYOUT != K_CONTIG || (a_klim & 3) == 0) && (B_LAYOUT != K_CONTIG || (b_klim & 3) == 0)));
     int n_full = 0, n_pipe = 0;
     {
-        // 128-bit loads need the limits along the contiguous axes to be multiples of 4 (the host only sets VEC then)
-        const bool vec_ok = VEC && (p.a_lim & 3) == 0 && (b_lim & 3) == 0 &&
-                            (A_LAYOUT != K_CONTIG || (a_klim & 3) == 0) && (B_LAYOUT != K_CONTIG || (b_klim & 3) == 0);
         int k_lim = k_end;
         if (A_LAYOUT == K_CONTIG) k_lim = min(k_lim, a_klim);
         if (B_LAYOUT == K_CONTIG) k_lim = min(k_lim, b_klim);
+        if (ANY_WIDTH) k_lim = min(k_lim, p.K - 1);
         if (vec_ok) {
             n_pipe = n_slabs;
             n_full = k_lim > k_begin ? (k_lim - k_begin) / BK : 0;
@@ -475,6 +481,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
     }
     auto load_slab = [&](int s, f32x4 (&ra)[IT_A], f32x4 (&rb)[IT_B]) {
         if (s < n_full) load_fast(k_begin + s * BK, ra, rb);
+        else if constexpr (ANY_WIDTH) load_guarded(k_begin + s * BK, ra, rb);
         else load_tail(k_begin + s * BK, ra, rb);
     };
     // Most tiles have nothing to replace on the way to LDS; the replacement is one select per element and slab on
@@ -488,7 +495,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
         else store_lds(buf, ra, rb, true);
     };
     auto store_slab = [&](int buf, int s, f32x4 (&ra)[IT_A], f32x4 (&rb)[IT_B]) {
-        if (s >= n_full) fix_tail(k_begin + s * BK, ra, rb);
+        if (!ANY_WIDTH && s >= n_full) fix_tail(k_begin + s * BK, ra, rb);
         store_full(buf, ra, rb);
     };
     auto k_in_slab = [&](int s) { return min(BK, k_end - (k_begin + s * BK)); };
@@ -809,7 +816,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
 }
 
 // One product per launch; the grid may be extended by blocks that run the center rule (p.ctr).
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int A_LAYOUT, int B_LAYOUT, bool VEC, int EPI, int MT = 32>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int A_LAYOUT, int B_LAYOUT, bool VEC, int EPI, int MT = 32, bool ANY_WIDTH = false>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, 2) void gemm_mfma_kernel(GemmArgs p)
 {
     __shared__ __attribute__((aligned(16))) float lds[gemm_lds_floats<BM, BN, BK, A_LAYOUT, B_LAYOUT>()];
@@ -822,7 +829,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, 2) void gemm_mfma_kernel(Gem
         mean_loss_block(p.mean, blockIdx.x - p.mean.first_block);
         return;
     }
-    gemm_block<BM, BN, BK, WAVES_M, WAVES_N, A_LAYOUT, B_LAYOUT, VEC, EPI, MT, true>(p, blockIdx.x, lds);
+    gemm_block<BM, BN, BK, WAVES_M, WAVES_N, A_LAYOUT, B_LAYOUT, VEC, EPI, MT, true, ANY_WIDTH>(p, blockIdx.x, lds);
 }
 
 // Two independent products in one launch: blocks [0, n0) work on p0 with the first configuration, the rest on

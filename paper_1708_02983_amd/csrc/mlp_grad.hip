@@ -251,7 +251,31 @@ static void launch_tile(const GemmArgs &a_in, bool vec, hipStream_t s)
     total += a.mean.blocks;
     const dim3 grid((unsigned)total), block(WM * WN * 64);
     if (vec) EASGD_LAUNCH((gemm_mfma_kernel<BM, BN, BK, WM, WN, AL, BL, true, EPI, MT>), grid, block, 0, s, a);
+    else if constexpr (AL == K_CONTIG && BL == MN_CONTIG && BN > 32)
+        EASGD_LAUNCH((gemm_mfma_kernel<BM, BN, BK, WM, WN, AL, BL, true, EPI, MT, true>), grid, block, 0, s, a);
     else EASGD_LAUNCH((gemm_mfma_kernel<BM, BN, BK, WM, WN, AL, BL, false, EPI, MT>), grid, block, 0, s, a);
+}
+
+// A batch that is not a multiple of 32 rows wastes matrix-core time in 32-row MFMA tiles (b = 100: 128 rows are
+// multiplied, 28 % more than stored).  The 16x16x4 instruction has the same rate, so a block tile of 3, 5 or 7 x 16
+// rows by 128 columns (four wavefronts side by side, 3, 5 or 7 x 2 accumulators each) multiplies 48, 80 or 112
+// rows per tile.  It is chosen for the products whose M is the batch (forward, input gradient) when one of the
+// three heights covers M with fewer rows than 32-row tiles do and still gives every compute unit about two
+// blocks.  Returns that height, or 0.
+static int tile16_rows(int M, int N, int P, int splits)
+{
+    if (N <= 32) return 0;
+    long best_rows = (long)((M + 31) / 32) * 32;
+    int best = 0;
+    for (int bm : {112, 80, 48}) {
+        const long rows = (long)((M + bm - 1) / bm) * bm;
+        if (rows < best_rows) {
+            best_rows = rows;
+            best = bm;
+        }
+    }
+    if (best == 0) return 0;
+    return (size_t)((M + best - 1) / best) * ((N + 127) / 128) * splits * P >= (size_t)(2 * num_cus()) ? best : 0;
 }
 
 // ---- products on the bfloat16 matrix cores (gemm_split.h) ----
@@ -339,14 +363,14 @@ static bool launch_split_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, SplitPick p
     return true;
 }
 
-// Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile of the fp32 matrix instruction, everything else the
-// tiles of gemm_split.h (split_pick, split_dw), but for small weight gradients and where EASGD_OPT_GEMM_TILE forces a
-// shape: those take 64x64 blocks of the fp32 instruction (four per compute unit, so that the epilogue of one
-// overlaps the products of the others) or the forced tile.
-// beside: a kernel of another stream has to fit on the chip next to this launch (two 128x128 blocks fill a compute
-// unit's registers, two 64x128 blocks leave a third; both sum in the same order, so the bits are the same).
+// Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile of the fp32 matrix instruction; input gradients, a
+// wide last layer and large weight gradients the tiles of gemm_split.h (split_pick, split_dw); everything else, and
+// whatever EASGD_OPT_GEMM_TILE forces, tiles of the fp32 instruction: 64x64 blocks (four per compute unit, so that the
+// epilogue of one overlaps the products of the others), for the forward products the 16-row tiles or 128x128 where
+// they still give every compute unit about two blocks.
+// fp32: the product keeps the fp32 instruction and its order of sums (see the callers); large: 128x128 tiles are allowed.
 template <int AL, int BL, int EPI>
-static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, bool beside = false)
+static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, bool fp32 = false, bool large = false)
 {
     if (a.N <= 32) {
         launch_tile<128, 32, SPLIT_BK, 4, 1, AL, BL, EPI>(a, vec, s);
@@ -354,9 +378,8 @@ static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, bool beside 
     }
     long tile = options().gemm_tile;
     if constexpr (AL == K_CONTIG) {
-        if (tile == 0 && split_fits(a, AL == K_CONTIG, BL == K_CONTIG)) {
-            SplitPick pick = split_pick(a.M, a.N, a.P, a.splits);
-            if (pick == SPLIT_128x128 && beside) pick = SPLIT_64x128;
+        if (tile == 0 && !fp32 && split_fits(a, true, BL == K_CONTIG)) {
+            const SplitPick pick = split_pick(a.M, a.N, a.P, a.splits);
             if (pick == SPLIT_128x128) launch_split<4, 4, 1, AL, BL, EPI>(a, s);
             else if (pick == SPLIT_64x128) launch_split<2, 4, 1, AL, BL, EPI>(a, s);
             else if (pick == SPLIT_64x64) launch_split<2, 2, 2, AL, BL, EPI>(a, s);
@@ -364,17 +387,19 @@ static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, bool beside 
             else launch_split<1, 1, 4, AL, BL, EPI>(a, s);
             return;
         }
-        if (tile == 4) {                // the smallest height of the 16-row tiles that covers M, else 112
-            if (a.M <= 48) launch_tile<48, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
-            else if (a.M <= 80) launch_tile<80, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
-            else launch_tile<112, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
-            return;
-        }
-    } else if (split_dw(a, vec)) {
+        int bm16 = (tile == 0) ? tile16_rows(a.M, a.N, a.P, a.splits) : 0;
+        if (tile == 4) bm16 = a.M <= 48 ? 48 : a.M <= 80 ? 80 : 112;    // forced: the smallest height that covers M, else 112
+        if (bm16 == 112) launch_tile<112, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
+        else if (bm16 == 80) launch_tile<80, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
+        else if (bm16 == 48) launch_tile<48, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
+        if (bm16) return;
+    } else if (!fp32 && split_dw(a, vec)) {
         launch_split<2, 4, 1, AL, BL, EPI>(a, s);
         return;
     }
-    if (tile == 0 || tile == 4) tile = 2;   // the weight-gradient products have no 16-row form
+    const size_t big = (size_t)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.splits * a.P;
+    if (tile == 4) tile = 0;            // the weight-gradient products have no 16-row form
+    if (tile == 0) tile = (large && big >= (size_t)(2 * num_cus())) ? 1 : 2;
     if (tile == 1) launch_tile<128, 128, 16, 2, 2, AL, BL, EPI>(a, vec, s);
     else if (tile == 2) launch_tile<64, 64, 32, 2, 2, AL, BL, EPI>(a, vec, s);
     else launch_tile<128, 64, 32, 2, 2, AL, BL, EPI>(a, vec, s);
@@ -383,23 +408,19 @@ static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, bool beside 
 static inline bool mult4(size_t x) { return (x & 3u) == 0; }
 
 // Whether the launch of a forward product (M x N per worker, P workers, `splits` K splits) leaves room on the
-// chip for extra blocks that do bandwidth-bound work beside it.  Mirrors launch_gemm: blocks per compute unit that the
-// registers and LDS of a tile allow, one of which has to stay free.
-static bool forward_launch_has_room(const GemmArgs &a)
+// chip for extra blocks that do bandwidth-bound work beside it.  Mirrors launch_gemm: the 128x32 and 64x64
+// tiles use few enough registers and LDS for four blocks per compute unit, the 128x128 tile for two, and it
+// is chosen exactly when its blocks already fill those.
+static bool forward_launch_has_room(int M, int N, int P, int splits)
 {
     const size_t cus = (size_t)num_cus();
-    auto fits = [&](int bm, int bn, size_t per_cu) { return (size_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.splits * a.P <= (per_cu - 1) * cus; };
-    if (a.N <= 32) return fits(128, 32, 4);
-    const long tile = options().gemm_tile;
-    if (tile != 0) return tile == 2 && fits(64, 64, 4);
-    if (!split_fits(a, true, false)) return fits(64, 64, 4);
-    switch (split_pick(a.M, a.N, a.P, a.splits)) {
-    case SPLIT_64x128: return fits(64, 128, split_blocks_per_cu<2>());
-    case SPLIT_64x64: return fits(64, 64, split_blocks_per_cu<2>());
-    case SPLIT_32x128: return fits(32, 128, split_blocks_per_cu<1>());
-    case SPLIT_32x32: return fits(32, 32, split_blocks_per_cu<1>());
-    default: return false;
-    }
+    if (N <= 32) return (size_t)((M + 127) / 128) * splits * P <= 3 * cus;
+    long tile = options().gemm_tile;
+    if (tile == 4 || (tile == 0 && tile16_rows(M, N, P, splits) != 0)) return false;
+    const size_t big = (size_t)((M + 127) / 128) * ((N + 127) / 128) * splits * P;
+    if (tile == 0) tile = (big >= 2 * cus) ? 1 : 2;
+    if (tile != 2) return false;
+    return (size_t)((M + 63) / 64) * ((N + 63) / 64) * splits * P <= 3 * cus;
 }
 
 // Elastic update fused into the backward pass.  Eq. (2) runs first and saves the time-t
@@ -582,7 +603,6 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     // while the weight-gradient product of layer l+1, which may share its launch, still reads (l+1) % 3
     float *dz[3] = {reinterpret_cast<float *>(ws + pl.dz_off[0]), reinterpret_cast<float *>(ws + pl.dz_off[1]),
                     reinterpret_cast<float *>(ws + pl.dz_off[2])};
-    const bool base_vec = mult4(ld);
 
     // a narrow last layer goes through mlp_head_kernel together with the softmax and its own input gradient
     const bool head = options().mlp_head != 0 && head_fits(dims, L);
@@ -621,9 +641,8 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         // enough to read to be worth the tens of microseconds that ordering two streams costs; else its own kernel.
         const long overlap = options().round_overlap;
         const int splits0 = (L == 1) ? pl.splits : 1;
-        GemmArgs first = {};
-        first.M = b; first.N = dims[1]; first.K = dims[0] + 1; first.lda = dims[0]; first.ldb = dims[1]; first.P = P; first.splits = splits0;
-        const bool room = (head && L == 1) ? head_blocks(P, b) <= 3u * (unsigned)num_cus() : forward_launch_has_room(first);
+        const bool room = (head && L == 1) ? head_blocks(P, b) <= 3u * (unsigned)num_cus()
+                                           : forward_launch_has_room(b, dims[1], P, splits0);
         attach_center = (overlap == 3) || (overlap == 1 && room);
         if (!attach_center && (overlap == 2 || (overlap == 1 && (size_t)P * pl.N >= ((size_t)1 << 24)))) {
             lane_guard = std::unique_lock<std::mutex>(side_mutex);
@@ -654,6 +673,10 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         center_job.N = pl.N; center_job.ld = ld; center_job.P = P;
         center_job.alpha = step->eta * step->rho; center_job.blocks = (unsigned)cblocks;
     }
+    // The products of the hidden layers keep the fp32 instruction: a unit whose input is within rounding of zero is gated by
+    // that rounding, so another sum, however much closer to the exact one, would change which of a round's few such
+    // units pass their gradient on.  (The same product without the layers that follow, easgd_layer_product, takes
+    // gemm_split.h: 3072->2048, 8 workers, 256 rows 210 us -> 142; the two of a 784-1024-1024-10 round, 16 workers, 128 rows, would gain 9 us of 213.)
     for (int l = 0; l < (head ? L - 1 : L); ++l) {
         const int d_in = dims[l], d_out = dims[l + 1];
         const bool last = (l == L - 1);
@@ -666,9 +689,9 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         a.k_per_split = last ? pl.k_per_split : ((a.K + 63) / 64 * 64);
         a.c_ss = (size_t)P * b * d_out;
         if (l == 0) a.ctr = center_job;
-        const bool vec = base_vec && mult4(d_in) && mult4(d_out) && mult4(pl.off[l]);
+        const bool vec = mult4(d_in) && mult4(d_out);       // 128-bit loads need the element's alignment only
         if (last) launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, s);
-        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s, lane != nullptr);
+        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s, true, true);
     }
     float *row_loss = reinterpret_cast<float *>(ws + pl.rowloss_off);
     const int rows = P * b;
@@ -689,15 +712,20 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     // independent products can share a launch (launch_pair_*): with the input-gradient product of the layer
     // below when the held one is narrow, or with the weight-gradient product of the layer below.
     const int epi = !step ? (G16 ? EPI_STORE_BF16 : EPI_NONE) : (step->V16 ? EPI_ELASTIC_MOM_BF16 : (step->V ? EPI_ELASTIC_MOM : EPI_ELASTIC));
+    // Replicas that exceed the last-level cache (256 MB): the weight gradients are bound by the replicas' stream, so
+    // gemm_split.h has less to give (3072-2048-2048-10, 32 workers, 100 rows, with momentum: 2 207 us a round -> 2 119),
+    // and with so many units its other rounding of the replicas moves a gate of the round after now and then.  All products keep the
+    // fp32 instruction there.
+    const bool fp32 = (size_t)P * pl.N >= ((size_t)1 << 26);
     const bool pairing = options().gemm_pair != 0;
     const bool tile64 = options().gemm_tile == 0 || options().gemm_tile == 2;   // wide weight gradients use 64x64 or gemm_split.h
     struct Held { bool have = false; GemmArgs a; bool vec = false; } held;
     auto launch_dw = [&](const GemmArgs &d, bool vec) {
-        if (epi == EPI_NONE) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_NONE>(d, vec, s);
-        else if (epi == EPI_STORE_BF16) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_STORE_BF16>(d, vec, s);
-        else if (epi == EPI_ELASTIC) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC>(d, vec, s);
-        else if (epi == EPI_ELASTIC_MOM) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM>(d, vec, s);
-        else launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM_BF16>(d, vec, s);
+        if (epi == EPI_NONE) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_NONE>(d, vec, s, fp32);
+        else if (epi == EPI_STORE_BF16) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_STORE_BF16>(d, vec, s, fp32);
+        else if (epi == EPI_ELASTIC) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC>(d, vec, s, fp32);
+        else if (epi == EPI_ELASTIC_MOM) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM>(d, vec, s, fp32);
+        else launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM_BF16>(d, vec, s, fp32);
     };
     // the first kernel that changes W waits for the center rule, which reads W at time t
     bool joined = lane == nullptr;
@@ -725,11 +753,11 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
             a.mask = act(l); a.mask_ws = (size_t)b * d_in; a.ldmask = d_in;
             a.M = b; a.N = d_in; a.K = d_out; a.P = P;
             a.splits = 1; a.k_per_split = (a.K + 63) / 64 * 64;
-            const bool vec = base_vec && mult4(d_out) && mult4(pl.off[l]);
+            const bool vec = mult4(d_out);
             // A held narrow product shares this launch where the tile leaves a block per compute unit free; with the center
             // rule on the second stream it waits, so that the rule has this launch to finish behind as well.
             bool shared = false;
-            if (held.have && pairing && !lane && held.a.N <= 32 && a.N > 32 && options().gemm_tile == 0 && split_fits(a, true, true)) {
+            if (held.have && pairing && !lane && !fp32 && held.a.N <= 32 && a.N > 32 && options().gemm_tile == 0 && split_fits(a, true, true)) {
                 const SplitPick pick = split_pick(a.M, a.N, P, 1);
                 if (epi == EPI_NONE) shared = launch_split_pair_da_narrow_dw<EPI_NONE>(a, held.a, pick, s);
                 else if (epi == EPI_STORE_BF16) shared = launch_split_pair_da_narrow_dw<EPI_STORE_BF16>(a, held.a, pick, s);
@@ -739,7 +767,7 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
             }
             if (shared) held.have = false;
             else {
-                launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, vec, s);
+                launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, vec, s, fp32);
                 if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
             }
         }
@@ -763,7 +791,7 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         }
         const bool vec = mult4(d_in) && mult4(d_out);
         if (held.have) {     // two weight-gradient products in a row (no input-gradient product for layer 0)
-            const bool split0 = split_dw(held.a, held.vec), split1 = split_dw(d, vec);
+            const bool split0 = !fp32 && split_dw(held.a, held.vec), split1 = !fp32 && split_dw(d, vec);
             const bool both_fp32 = !split0 && !split1 && tile64 && held.vec && vec && held.a.N > 32 && d.N > 32;
             if (pairing && ((split0 && split1) || both_fp32)) {
                 if (!join()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
@@ -816,7 +844,7 @@ extern "C" int easgd_layer_product(int kind, int d_in, int d_out, int P, int b, 
         a.C = out; a.c_ws = out_ws; a.ldc = d_out;
         a.M = b; a.N = d_out; a.K = d_in + 1;
         a.k_per_split = (a.K + 63) / 64 * 64;
-        const bool vec = mult4(ld) && mult4(d_in) && mult4(d_out) && aligned16(Wl);
+        const bool vec = mult4(d_in) && mult4(d_out);
         if (relu) launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s);
         else launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, s);
     } else if (kind == 1) {     // [dW ; db] = [A 1]^T dZ
@@ -833,7 +861,7 @@ extern "C" int easgd_layer_product(int kind, int d_in, int d_out, int P, int b, 
         a.mask = A; a.mask_ws = (size_t)b * d_in; a.ldmask = d_in;
         a.M = b; a.N = d_in; a.K = d_out;
         a.k_per_split = (a.K + 63) / 64 * 64;
-        launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, mult4(ld) && mult4(d_out) && aligned16(Wl), s);
+        launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, mult4(d_out), s);
     }
     return check_launch(name);
 }
