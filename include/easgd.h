@@ -32,6 +32,10 @@
  *     what easgd_mlp_round and easgd_grad_static create on first use (described there);
  *   - all floating point is IEEE fp32 (storage and arithmetic), except the *_bf16 / *_bf16v entry points,
  *     which keep fp32 arithmetic and store gradients and momentum buffers as bfloat16;
+ *   - matrix products accumulate in fp32, either with the fp32 matrix instruction or with bfloat16 ones on operands that
+ *     are split into three bfloat16 parts without loss (six products of parts, the small ones summed apart; at least as
+ *     close to the exact sums).  In the split form an operand beyond the largest finite bfloat16 (3.39e38) counts as
+ *     infinite, and parts below 2^-133 are lost.  Infinities and NaN give what the fp32 products would;
  *   - replica matrices are [P][ld] row-major: row i is worker i, its first N
  *     entries are the parameters, entries [N, ld) are padding that is never
  *     read or written.
@@ -332,8 +336,9 @@ int easgd_mlp_round_bf16v(const int *dims, int n_layers,
 
 /*
  * One matrix product of forward / backward propagation (Section 2.2) alone, for all P workers, through the
- * tile selection and the MFMA kernels that easgd_grad uses for it (a testing aid: integer-valued operands
- * make every product and partial sum exact in fp32, so the result can be checked bit for bit).
+ * tile selection and the MFMA kernels that easgd_grad uses for it, except that kind 0 takes the split form (see the
+ * conventions), which the hidden layers of a network do not, unless EASGD_OPT_GEMM_TILE forces a tile (a testing aid:
+ * integer-valued operands make every product and partial sum exact in fp32, so the result can be checked bit for bit).
  * For one layer with d_in inputs and d_out outputs, [W ; b] its packed (d_in+1) x d_out block:
  *
  *   kind 0  forward           out[w] = [A[w] 1] [W[w] ; b[w]]          b x d_out   (max(., 0) when relu != 0)
@@ -370,6 +375,7 @@ typedef enum {
     EASGD_OPT_UPDATE_GROUPS        = 3,  /* 128-bit groups per thread and worker: 1, 2, 4 or 8; 0 = chosen per call (default): 4, fewer
                                             when N is small */
     EASGD_OPT_GEMM_TILE            = 4,  /* block tile of the wide matrix products of easgd_grad: 0 = chosen per product (default),
+                                            split operands (see the conventions) included; the others force the fp32 instruction:
                                             1 = 128x128, 2 = 64x64, 3 = 128x64, 4 = 48, 80 or 112 rows by 128 columns in 16x16x4 matrix
                                             instructions for the products whose rows are the minibatch (chosen by default when
                                             one of these heights covers b with fewer rows than b rounded up to 32, e.g. b = 100) */

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void softmax_round_kernel(HeadArgs h, SoftmaxR
 
     const bool passed = grid_barrier(words, target, spin_limit);
 
-    // the workers' mean losses (the order of mean_loss_kernel): wavefront 0 of block w, lanes over rows
+    // the workers' mean losses (the order of mean_loss_block): wavefront 0 of block w, lanes over rows
     if (u.loss && tid < 64) {
         for (int w = blockIdx.x; w < P; w += gridDim.x) {
             float acc = 0.f;

@@ -1,0 +1,114 @@
+"""Matrix products on split operands (three bfloat16 parts, six products, two accumulators) at the edges of their tiles and
+slabs, element by element against 64 bits; infinities and NaN; and forward propagation of any width and row stride."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from gpu_util import to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+F = np.float32
+
+# (d_in, d_out, P, b): the 128x128, 64x128, 64x64, 32x128 and 32x32 tiles of 256 compute units, rows, columns and sums one
+# below, at and one above a tile, a step (16) or a slab (32, 64); one row, one column of a tile, a sum of one
+SHAPES = [
+    (63, 2048, 16, 70), (64, 2047, 17, 128), (2048, 65, 16, 129),         # 128x128 forward; input gradient for the last
+    (31, 2048, 16, 64), (2049, 33, 16, 33),                               # 64x128
+    (32, 1024, 16, 40), (1023, 47, 16, 63),                               # 64x64
+    (16, 2048, 16, 32), (2048, 100, 17, 1),                               # 32x128
+    (1, 33, 2, 1), (15, 40, 3, 31), (65, 34, 2, 17), (300, 97, 5, 65),    # 32x32
+    (127, 128, 40, 31), (128, 255, 33, 96), (515, 100, 32, 100),          # weight gradients with 64x128 tiles, sums ragged
+]
+
+
+def _operands(d_in, d_out, P, b, seed=7):
+    rng = np.random.default_rng(seed)
+    block = (d_in + 1) * d_out
+    ld = block + (3 if d_in % 2 else 0)                                   # rows that start at any element
+    # a wide range of magnitudes, so that a part that is dropped or put to the wrong place shows in some element
+    A = (rng.standard_normal((P, b, d_in)) * np.exp2(rng.integers(-6, 7, (P, b, d_in)))).astype(F)
+    W = (rng.standard_normal((P, ld)) * np.exp2(rng.integers(-6, 7, (P, ld)))).astype(F)
+    Z = (rng.standard_normal((P, b, d_out)) * 1e-3).astype(F)
+    return A, W, Z, ld
+
+
+def _products(kind, A, W, Z, d_in, d_out):
+    """The product and the sum of absolute products per element, in 64 bits."""
+    P, b = A.shape[:2]
+    a, z = A.astype(np.float64), Z.astype(np.float64)
+    w = W[:, :(d_in + 1) * d_out].reshape(P, d_in + 1, d_out).astype(np.float64)
+    one = np.concatenate([a, np.ones((P, b, 1))], axis=2)
+    if kind == 0:
+        return one @ w, np.abs(one) @ np.abs(w), d_in + 1
+    if kind == 1:
+        t = one.transpose(0, 2, 1)
+        return t @ z, np.abs(t) @ np.abs(z), b
+    t = w[:, :d_in].transpose(0, 2, 1)
+    gate = a > 0
+    return (z @ t) * gate, (np.abs(z) @ np.abs(t)) * gate, d_out
+
+
+def _run(hip, kind, A, W, Z, d_in, d_out, ld, width):
+    P = A.shape[0]
+    out = torch.full((P, width + 5), float("nan"), device="cuda")
+    hip.easgd_layer_product(kind, d_in, d_out, to_dev(A), out, Wl=to_dev(W), dZ=to_dev(Z), ld=ld, out_ws=width + 5)
+    got = to_host(out)
+    assert np.isnan(got[:, width:]).all()
+    return got[:, :width]
+
+
+@pytest.mark.parametrize("d_in,d_out,P,b", SHAPES, ids=lambda v: str(v))
+def test_every_element_against_64_bits(d_in, d_out, P, b):
+    import paper_1708_02983_amd as hip
+    A, W, Z, ld = _operands(d_in, d_out, P, b)
+    for kind in (0, 1, 2):
+        ref, mag, K = _products(kind, A, W, Z, d_in, d_out)
+        got = _run(hip, kind, A, W, Z, d_in, d_out, ld, ref[0].size).reshape(ref.shape)
+        # fp32 sums: at most K additions (the fp32 instruction, where a rule keeps it; one per sixteen and product in the
+        # split form), each off by half an ulp of a partial sum; dropped products below 2^-24 of each term
+        bound = (K + 8) * 2.0 ** -24 * mag
+        worst = np.abs(got - ref) - bound
+        assert (worst <= 0).all(), (kind, float((np.abs(got - ref) / np.maximum(mag, 1e-30)).max()))
+
+
+@pytest.mark.parametrize("d_in,d_out,P,b", [(70, 2048, 16, 70), (65, 34, 2, 17)], ids=lambda v: str(v))
+def test_infinities_and_nan_give_what_fp32_products_give(d_in, d_out, P, b):
+    import paper_1708_02983_amd as hip
+    A, W, Z, ld = _operands(d_in, d_out, P, b)
+    A[0, 3, 5], A[0, 4, 64], A[1, 2, 0] = np.inf, -np.inf, np.nan
+    W[0, 7 * d_out + 9] = np.inf
+    W[1, (d_in - 1) * d_out + 33] = np.nan
+    A[0, 5, 7] = 0.0                                                      # 0 * inf
+    with np.errstate(invalid="ignore"):
+        ref, _, _ = _products(0, A, W, Z, d_in, d_out)
+    got = _run(hip, 0, A, W, Z, d_in, d_out, ld, ref[0].size).reshape(ref.shape)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    np.testing.assert_array_equal(got[inf], ref[inf].astype(F))
+    assert np.isfinite(got[np.isfinite(ref)]).all()
+
+
+@pytest.mark.parametrize("dims,P,b", [((63, 37, 41, 10), 3, 20), ((64, 65, 130, 20), 2, 33), ((33, 2048, 10), 16, 33)],
+                         ids=lambda v: str(v).replace(" ", ""))
+def test_row_stride_does_not_change_a_bit(dims, P, b):
+    """Replicas packed back to back, so that rows and layers start at any element, against padded ones."""
+    import paper_1708_02983_amd as hip
+    N = workloads.mlp_num_params(dims)
+    rng = np.random.default_rng(3)
+    rows = (rng.standard_normal((P, N)) * 0.1).astype(F)
+    X = to_dev(rng.standard_normal((P, b, dims[0])).astype(F))
+    y = to_dev(rng.integers(0, dims[-1], (P, b)).astype(np.int32))
+    got = []
+    for ld in (N, N + 1, (N + 255) // 256 * 256):
+        W = np.full((P, ld), np.nan, dtype=F)
+        W[:, :N] = rows
+        G = torch.full((P, ld), float("nan"), device="cuda")
+        loss = torch.empty(P, device="cuda")
+        hip.easgd_grad(dims, to_dev(W), X, y, G, loss)
+        g = to_host(G)
+        assert np.isnan(g[:, N:]).all()
+        got.append((g[:, :N], to_host(loss)))
+    for g, l in got[1:]:
+        np.testing.assert_array_equal(g, got[0][0])
+        np.testing.assert_array_equal(l, got[0][1])
