@@ -564,10 +564,11 @@ def training_report(hip, wl, steps, warmup, name, full):
     # the dominant kernels are the matrix products.  `roofline`: all products of one easgd_grad call of the two-call
     # path (matrix products, softmax and nothing else), useful flops over the call's duration from HIP events.
     # `roofline_one_call`: the same useful flops over the duration of the whole easgd_mlp_round call, whose
-    # products also apply the elastic update in their epilogues -- the path `value` times.
-    out["roofline"] = mfma_roofline(hip, "gemm_mfma_kernel (all products of easgd_grad, two-call path)",
+    # products also apply the elastic update in their epilogues -- the path `value` times.  The peak is that of the fp32
+    # matrix instruction; products on operands split into bfloat16 parts are not bound by it.
+    out["roofline"] = mfma_roofline(hip, "gemm_mfma_kernel, gemm_split_kernel (all products of easgd_grad, two-call path)",
                                     ("grad", name), grad_flops(wl), r["grad_ms"])
-    out["roofline_one_call"] = mfma_roofline(hip, "gemm_mfma_kernel + elastic epilogues (all launches of easgd_mlp_round)",
+    out["roofline_one_call"] = mfma_roofline(hip, "gemm_mfma_kernel, gemm_split_kernel + elastic epilogues (all launches of easgd_mlp_round)",
                                              ("round", name), grad_flops(wl), r1["grad_ms"])
     out["update_in_round"] = {"GBs_algorithmic": round(update_bytes(wl) / (r["update_ms"] * 1e-3) / 1e9, 1),
                               "note": "elastic update of the two-call path; replicas of this size are served partly "
