@@ -34,8 +34,8 @@
  *     which keep fp32 arithmetic and store gradients and momentum buffers as bfloat16;
  *   - matrix products accumulate in fp32, either with the fp32 matrix instruction or with bfloat16 ones on operands that
  *     are split into three bfloat16 parts without loss (six products of parts, the small ones summed apart; at least as
- *     close to the exact sums).  In the split form an operand beyond the largest finite bfloat16 (3.39e38) counts as
- *     infinite, and parts below 2^-133 are lost.  Infinities and NaN give what the fp32 products would;
+ *     close to the exact sums).  Results that meet an infinity, a NaN, a finite operand from 2^96 on or a sum from 2^64 on
+ *     come from the fp32 instruction in either form;
  *   - replica matrices are [P][ld] row-major: row i is worker i, its first N
  *     entries are the parameters, entries [N, ld) are padding that is never
  *     read or written.

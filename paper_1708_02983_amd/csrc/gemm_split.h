@@ -1,18 +1,24 @@
 // Batched fp32 matrix products on the bfloat16 matrix cores, without giving up fp32 accuracy.
 //
 // Every fp32 operand is the exact sum of three bfloat16 numbers, x = h + m + l (h = x rounded to nearest, m = x - h
-// rounded, l = the rest: 8 + 8 + 8 significant bits; exact for |x| >= 2^-110, an error below 2^-133 otherwise).  Of
-// the nine products of two such sums the six that matter are taken,
+// rounded, l = the rest: 8 + 8 + 8 significant bits), a published method: G. Henry, P. T. P. Tang, A. Heinecke,
+// "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019.  Of the nine
+// products of two such sums the six that matter are taken,
 //     x*y = hh + (hm + mh) + (mm + hl + lh)      what is left out is below 2^-24 of |x*y|
 // each exact in fp32, accumulated in fp32 by v_mfma_f32_32x32x16_bf16.  The large products hh and the small rest go
 // to two accumulators that meet once at the end, so that a rounding of the large sum happens once per 16 values of k
-// (the fp32 instruction rounds at every one): against 64-bit sums the result is two to three times closer than that
-// of v_mfma_f32_32x32x2_f32 (relative error of a sum of 1 024: 1.9e-7 against 5.7e-7, of 64: 4.9e-8 against 1.4e-7).
-// The bfloat16 instruction has sixteen times the fp32 one's rate, so six of them still leave 2.7 times; the 5.5 vector
-// instructions per operand element that split it run beside the matrix instructions of the same SIMD for free
-// (measured: 24 matrix instructions with six vector instructions behind each take 3 % longer than without).
-// An operand beyond the largest finite bfloat16 (3.39e38) counts as infinite.  An infinity or a NaN makes the small
-// sums NaN; the result then is the sum of the large products alone, which holds what the fp32 product would.
+// (the fp32 instruction rounds at every one): against 64-bit sums the result is two and a half to three times closer than
+// that of v_mfma_f32_32x32x2_f32 (relative error of a sum of 1 024: 1.9e-7 against 5.7e-7, of 64: 4.9e-8 against 1.4e-7).
+// The bfloat16 instruction has sixteen times the fp32 one's rate, so six of them still leave 2.7 times; the 6.5 vector
+// instructions per operand element that scale and split it run beside the matrix instructions of the same SIMD (24 matrix
+// instructions with six vector instructions behind each take 3 % longer than without).
+// Range: every operand is multiplied by 2^32 on its way into the split, every result by 2^-64.  A bfloat16 has fp32's
+// exponents but its last part lies 16 bits below the number, so without that an operand below 2^-110 would lose bits;
+// with it every fp32 number, denormal ones included, is split exactly into normal bfloat16 numbers.  Finite operands from
+// 2^96 on, sums from 2^64 on, infinities and NaN make a sum that is not finite; a wavefront that finds one computes its
+// tiles again with the fp32 instruction, whose result (finite, infinite or NaN) stands.  (The multiplication costs 2 to 3 %:
+// 3072->2048 forward, 8 workers, 256 rows 148 us -> 152, 2048->2048 input gradient, 32 workers, 100 rows 197 -> 201.  The
+// second computation costs as much as the fp32 kernels' or more, but only where values are that far out.)
 //
 #pragma once
 #include "gemm_mfma.h"
@@ -24,6 +30,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
+constexpr float SPLIT_SCALE = 0x1p32f, SPLIT_UNSCALE = 0x1p-64f;     // of an operand, of a product (head of the file)
+
 struct SplitFrag { u32x4 h, m, l; };       // eight values of k: three bfloat16 planes of 16 bytes
 
 // two floats rounded to nearest even, a in the low half
@@ -33,37 +41,33 @@ __device__ __forceinline__ unsigned bf16_pack(float a, float b)
     return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));      // v_cvt_pk_bf16_f32
 }
 
-// The split of eight values in six parts of four to eight independent instructions each (x is used up): a part fits
-// behind one matrix instruction, and no instruction waits for the one before it.
-__device__ __forceinline__ void split_part(int part, f32x8 &x, SplitFrag &f, u32x4 &t)
+// The split of eight values in six parts of eight to ten independent instructions each (x is used up): a part fits
+// behind one matrix instruction, and no instruction waits for the one before it.  ONES: x * mul + add is split, which
+// puts ones in the place of x (mul = 0) at no cost; otherwise x alone.
+template <bool ONES = false>
+__device__ __forceinline__ void split_part(int part, f32x8 &x, SplitFrag &f, u32x4 &t, float mul = SPLIT_SCALE, float add = 0.f)
 {
-    auto low = [](unsigned d) { return __uint_as_float(d << 16); };
-    auto high = [](unsigned d) { return __uint_as_float(d & 0xffff0000u); };
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if (part == 0) f.h[e] = bf16_pack(x[2 * e], x[2 * e + 1]);
-        if (part == 1) { f.l[e] = __float_as_uint(low(f.h[e])); t[e] = __float_as_uint(high(f.h[e])); }
-        if (part == 2) { x[2 * e] -= __uint_as_float(f.l[e]); x[2 * e + 1] -= __uint_as_float(t[e]); }
-        if (part == 3) f.m[e] = bf16_pack(x[2 * e], x[2 * e + 1]);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if ((part == 3 && e < 2) || (part == 4 && e >= 2)) { f.l[e] = __float_as_uint(low(f.m[e])); t[e] = __float_as_uint(high(f.m[e])); }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if ((part == 4 && e < 2) || (part == 5 && e >= 2)) { x[2 * e] -= __uint_as_float(f.l[e]); x[2 * e + 1] -= __uint_as_float(t[e]); }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (part == 5) f.l[e] = bf16_pack(x[2 * e], x[2 * e + 1]);
+    auto low = [](unsigned d) { return d << 16; };                       // the two numbers of a pair as fp32 bits
+    auto high = [](unsigned d) { return d & 0xffff0000u; };
+    auto scale1 = [&](float v) { return ONES ? fmaf(v, mul, add) : v * SPLIT_SCALE; };
+    auto scale = [&](int e) { x[2 * e] = scale1(x[2 * e]); x[2 * e + 1] = scale1(x[2 * e + 1]); };
+    auto take = [&](u32x4 &plane, int e) { plane[e] = bf16_pack(x[2 * e], x[2 * e + 1]); };
+    auto widen = [&](const u32x4 &plane, int e) { f.l[e] = low(plane[e]); t[e] = high(plane[e]); };
+    auto rest = [&](int e) { x[2 * e] -= __uint_as_float(f.l[e]); x[2 * e + 1] -= __uint_as_float(t[e]); };
+    if (part == 0) { scale(0); scale(1); scale(2); scale(3); }
+    if (part == 1) { take(f.h, 0); take(f.h, 1); take(f.h, 2); take(f.h, 3); widen(f.h, 0); widen(f.h, 1); }
+    if (part == 2) { widen(f.h, 2); widen(f.h, 3); rest(0); rest(1); }
+    if (part == 3) { rest(2); rest(3); take(f.m, 0); take(f.m, 1); widen(f.m, 0); }
+    if (part == 4) { take(f.m, 2); take(f.m, 3); widen(f.m, 1); widen(f.m, 2); widen(f.m, 3); rest(0); }
+    if (part == 5) { rest(1); rest(2); rest(3); take(f.l, 0); take(f.l, 1); take(f.l, 2); take(f.l, 3); }
 }
 
-__device__ __forceinline__ void split8(f32x8 &x, SplitFrag &f)
+template <bool ONES = false>
+__device__ __forceinline__ void split8(f32x8 &x, SplitFrag &f, float mul = SPLIT_SCALE, float add = 0.f)
 {
     u32x4 t;
 #pragma unroll
-    for (int part = 0; part < 6; ++part) split_part(part, x, f, t);
+    for (int part = 0; part < 6; ++part) split_part<ONES>(part, x, f, t, mul, add);
 }
 
 // Tile configuration: a block of four wavefronts, WN side by side along n and WK along k, owns a (TM*32) x (WN*32)
@@ -113,14 +117,19 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     const auto bb = rsrc(B, (unsigned)(B_LAYOUT == K_CONTIG ? p.N : p.K) * (unsigned)p.ldb);
     unsigned a_off[IT];
     int a_dst[IT], a_k[IT];
-    bool a_one[IT];                                                  // the row of C that multiplies by ones
+    // The row of C that multiplies by ones has no row of A; what the clamped address brings is multiplied by 0.  (A value
+    // that is not finite makes a sum that is not, see the head of the file.)
+    constexpr bool ONES = A_LAYOUT == MN_CONTIG;
+    float a_mul[IT], a_add[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const int u = tid + it * 256;
         const int row = (A_LAYOUT == K_CONTIG) ? u / K8 : u % BM, k8 = (A_LAYOUT == K_CONTIG) ? u % K8 : u / BM;
         const int swz = (A_LAYOUT == K_CONTIG) ? k8 * (8 / K8) : 0;
         const int m = min(m0 + row, a_rows - 1);
-        a_one[it] = A_LAYOUT == MN_CONTIG && m0 + row == p.a_ones;
+        const bool one = ONES && m0 + row == p.a_ones;
+        a_mul[it] = one ? 0.f : SPLIT_SCALE;
+        a_add[it] = one ? SPLIT_SCALE : 0.f;
         a_k[it] = 8 * k8;
         a_off[it] = (A_LAYOUT == K_CONTIG) ? 4u * ((unsigned)m * (unsigned)p.lda + 8u * k8) : 4u * (8u * k8 * (unsigned)p.lda + (unsigned)m);
         a_dst[it] = ((k8 >> 1) * 3 * TM + (row >> 5)) * 64 + (((row & 31) ^ swz) + 32 * (k8 & 1));
@@ -190,12 +199,6 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     auto cut_a = [&](int slab, int it, RawA &r) { cut(r.x[it], start(slab) + a_k[it], k_begin + slab * BK, a_klim, k_ones); };
     auto cut_b = [&](int slab, int ks, RawB &r) { cut(r.x[ks], start(slab) + 16 * (wk + ks * WK) + 8 * q, k_begin + slab * BK, k_end, -1); };
     auto a_here = [&](int it) { return T::UNITS % 256 == 0 || tid + it * 256 < T::UNITS; };
-    auto put_ones = [&](int it, RawA &r) {
-        if (A_LAYOUT == MN_CONTIG) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) r.x[it][e] = a_one[it] ? 1.f : r.x[it][e];
-        }
-    };
     auto store_a = [&](int buf, int it, const SplitFrag &f) {
         if (!a_here(it)) return;
         u32x4 *dst = lds + buf * T::SLAB_VECS + a_dst[it];
@@ -248,8 +251,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     for (int u = 0; u < IT; ++u) {
         SplitFrag f;
         if (!whole(0)) cut_a(0, u, ra);
-        put_ones(u, ra);
-        split8(ra.x[u], f);
+        split8<ONES>(ra.x[u], f, a_mul[u], a_add[u]);
         store_a(0, u, f);
         load_a(1, std::false_type{}, u, ra);
     }
@@ -276,10 +278,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
             auto a_unit = [&](int u) { return it == (ITEMS >= 4 ? 1 + u % 2 : 0); };        // which units of A
 #pragma unroll
             for (int u = 0; u < IT; ++u)
-                if (a_unit(u)) {
-                    if (LAST && !whole(s + 1)) cut_a(s + 1, u, ra);
-                    put_ones(u, ra);
-                }
+                if (LAST && a_unit(u) && !whole(s + 1)) cut_a(s + 1, u, ra);
             __builtin_amdgcn_sched_barrier(0);
             // a step without a k of its own holds zeros only
             const int k_step = start(s) + 16 * (wk + ks * WK);
@@ -291,7 +290,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
                 if (b0) split_part(part, rb.x[0], fb[F1], t[IT]);
 #pragma unroll
                 for (int u = 0; u < IT; ++u)
-                    if (a_unit(u)) split_part(part, ra.x[u], fs[u], t[u]);
+                    if (a_unit(u)) split_part<ONES>(part, ra.x[u], fs[u], t[u], a_mul[u], a_add[u]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (b1) load_b_step(s + 1, inner, 1, rb);
@@ -318,15 +317,54 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
         slab(s + 1, odd, std::true_type{});
     }
 
-    // ---- the two sums meet (the small one is NaN where an operand was not finite: see the head of the file) ----
+    // ---- the two sums meet; what went out of the scaled range is summed again (head of the file) ----
     f32x16 acc[TM];
+    f32x8 bad = {};                                      // eight chains: NaN as soon as one of a chain's sums is not finite
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float c = lo[i][r];
-            acc[i][r] = hi[i][r] + (fabsf(c) <= 3.402823466e38f ? c : 0.f);
+            const float c = hi[i][r] + lo[i][r];
+            bad[r % 8] = fmaf(c, 0.f, bad[r % 8]);
+            acc[i][r] = c * SPLIT_UNSCALE;
         }
+    const float not_finite = ((bad[0] + bad[1]) + (bad[2] + bad[3])) + ((bad[4] + bad[5]) + (bad[6] + bad[7]));
+    if (__builtin_expect(__any(not_finite != 0.f), 0)) {  // uniform for the wavefront
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+        // the wavefront's steps of every slab, in pairs of k: lane l holds A[m = l%32][k = l/32] and B[k = l/32][n = l%32]
+        for (int st = 0; st < n_slabs * KS; ++st) {
+            const int sl = st / KS, kb = start(sl) + 16 * (wk + (st % KS) * WK), first = k_begin + sl * BK;
+#pragma unroll 1
+            for (int half = 0; half < 16; half += 8) {
+                float x[4][TM], y[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = kb + half + 2 * u + q;
+                    const bool in = k >= first && k < k_end;
+                    const unsigned ka = (unsigned)max(min(k, a_klim - 1), 0), kc = (unsigned)min(k, k_end - 1);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const int row = m0 + 32 * i + l32;
+                        const unsigned m = (unsigned)min(row, a_rows - 1);
+                        const unsigned off = 4u * (A_LAYOUT == K_CONTIG ? m * (unsigned)p.lda + ka : kc * (unsigned)p.lda + m);
+                        const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)off, 0, 0));
+                        const bool one = A_LAYOUT == K_CONTIG ? k == k_ones : row == p.a_ones;
+                        x[u][i] = !in ? 0.f : one ? 1.f : A_LAYOUT == K_CONTIG && k >= a_klim ? 0.f : v;
+                    }
+                    const unsigned off = 4u * (B_LAYOUT == K_CONTIG ? (unsigned)bn * (unsigned)p.ldb + kc : kc * (unsigned)p.ldb + (unsigned)bn);
+                    const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bb, (int)off, 0, 0));
+                    y[u] = in ? v : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u][i], y[u], acc[i], 0, 0, 0);
+            }
+        }
+    }
 
     // ---- epilogue ----
     // Register r of lane l is C[8*(r/4) + 4*q + r%4][l%32] of its 32x32 tile.  Where WK wavefronts share a tile,

@@ -89,6 +89,72 @@ def test_infinities_and_nan_give_what_fp32_products_give(d_in, d_out, P, b):
     assert np.isfinite(got[np.isfinite(ref)]).all()
 
 
+RANGE_SHAPES = [(300, 2048, 16, 70), (2048, 100, 17, 40), (65, 34, 2, 17), (127, 128, 40, 31)]
+
+
+def _scaled_operands(d_in, d_out, P, b, kind, sx, sy):
+    """Operands of ordinary values times sx (the operand that is summed along its rows first) and sy; no bias."""
+    A, W, Z, ld = _operands(d_in, d_out, P, b)
+    W[:, d_in * d_out:(d_in + 1) * d_out] = 0.0
+    Z *= F(1e3)
+    with np.errstate(over="ignore"):
+        if kind == 0:
+            A, W = A * F(sx), W * F(sy)
+        elif kind == 1:
+            A, Z = A * F(sx), Z * F(sy)
+        else:
+            Z, W = Z * F(sx), W * F(sy)
+    return A, W, Z, ld
+
+
+@pytest.mark.parametrize("sx,sy", [(2.0 ** -120, 2.0 ** 60), (2.0 ** 60, 2.0 ** -120), (2.0 ** -138, 2.0 ** 100),
+                                   (2.0 ** 100, 2.0 ** -40), (2.0 ** 30, 2.0 ** 70)], ids=lambda v: "2^%d" % np.log2(v))
+@pytest.mark.parametrize("d_in,d_out,P,b", RANGE_SHAPES, ids=lambda v: str(v))
+def test_small_and_large_operands_lose_nothing(d_in, d_out, P, b, sx, sy):
+    """Down to denormal operands (whose products are not) and up to sums that only just are finite."""
+    import paper_1708_02983_amd as hip
+    for kind in (0, 1, 2):
+        A, W, Z, ld = _scaled_operands(d_in, d_out, P, b, kind, sx, sy)
+        ref, mag, K = _products(kind, A, W, Z, d_in, d_out)
+        got = _run(hip, kind, A, W, Z, d_in, d_out, ld, ref[0].size).reshape(ref.shape)
+        worst = np.abs(got - ref) - ((K + 8) * 2.0 ** -24 * mag + K * 2.0 ** -149)
+        assert (worst <= 0).all(), (kind, float(np.nanmax(np.abs(got - ref) / np.maximum(mag, 1e-300))))
+
+
+@pytest.mark.parametrize("d_in,d_out,P,b", RANGE_SHAPES, ids=lambda v: str(v))
+def test_values_at_the_ends_of_the_range(d_in, d_out, P, b):
+    """Finite values beyond the largest bfloat16 in either operand, times zeros and small values; infinities times denormal
+    ones; NaN: all three products give what sums of fp32 products give."""
+    import paper_1708_02983_amd as hip
+    top, tiny = F(3.4e38), F(2.0 ** -140)
+    for kind in (0, 1, 2):
+        A, W, Z, ld = _scaled_operands(d_in, d_out, P, b, kind, 1.0, 1.0)
+        w = W[:, :(d_in + 1) * d_out].reshape(P, d_in + 1, d_out)          # a view when the rows are packed, else a copy
+        x, y = {0: (A, w), 1: (A.transpose(0, 2, 1), Z), 2: (Z, w.transpose(0, 2, 1))}[kind]    # x (P, M, K), y (P, K, N)
+        y[0, 1, :] *= F(2.0 ** -40)
+        x[0, 1, 1] = top                                                   # times small values: finite
+        y[0, 2, 3] = top
+        x[0, :, 2] = 0.0                                                   # times zero: nothing
+        y[0, 4, 5] = tiny
+        y[0, 4, 6] = -tiny
+        x[0, 0, 4] = np.inf
+        x[1, 3, 5] = np.nan
+        x[1, 2, 0] = -np.inf
+        W[:, :(d_in + 1) * d_out] = w.reshape(P, -1)
+        with np.errstate(invalid="ignore"):
+            ref, mag, K = _products(kind, A, W, Z, d_in, d_out)
+            if kind == 2:                                                  # the gate replaces, it does not multiply
+                z, t = Z.astype(np.float64), w[:, :d_in].transpose(0, 2, 1).astype(np.float64)
+                ref, mag = np.where(A > 0, z @ t, 0.0), np.where(A > 0, np.abs(z) @ np.abs(t), 0.0)
+        got = _run(hip, kind, A, W, Z, d_in, d_out, ld, ref[0].size).reshape(ref.shape)
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(ref), err_msg=str(kind))
+        inf, fin = np.isinf(ref), np.isfinite(ref)
+        np.testing.assert_array_equal(got[inf], ref[inf].astype(F), err_msg=str(kind))
+        with np.errstate(invalid="ignore"):
+            bound = (K + 8) * 2.0 ** -24 * mag
+        assert (np.abs(got[fin] - ref[fin]) <= bound[fin]).all(), kind
+
+
 @pytest.mark.parametrize("dims,P,b", [((63, 37, 41, 10), 3, 20), ((64, 65, 130, 20), 2, 33), ((33, 2048, 10), 16, 33)],
                          ids=lambda v: str(v).replace(" ", ""))
 def test_row_stride_does_not_change_a_bit(dims, P, b):
