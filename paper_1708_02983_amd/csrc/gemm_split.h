@@ -116,7 +116,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     const auto ab = rsrc(A, (unsigned)(A_LAYOUT == K_CONTIG ? p.M : p.K) * (unsigned)p.lda);
     const auto bb = rsrc(B, (unsigned)(B_LAYOUT == K_CONTIG ? p.N : p.K) * (unsigned)p.ldb);
     unsigned a_off[IT];
-    int a_dst[IT], a_k[IT];
+    int a_dst[IT], a_kept[IT];                                       // a_kept: the unit's first k inside its slab
     // The row of C that multiplies by ones has no row of A; what the clamped address brings is multiplied by 0.  (A value
     // that is not finite makes a sum that is not, see the head of the file.)
     constexpr bool ONES = A_LAYOUT == MN_CONTIG;
@@ -130,12 +130,23 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
         const bool one = ONES && m0 + row == p.a_ones;
         a_mul[it] = one ? 0.f : SPLIT_SCALE;
         a_add[it] = one ? SPLIT_SCALE : 0.f;
-        a_k[it] = 8 * k8;
         a_off[it] = (A_LAYOUT == K_CONTIG) ? 4u * ((unsigned)m * (unsigned)p.lda + 8u * k8) : 4u * (8u * k8 * (unsigned)p.lda + (unsigned)m);
+        a_kept[it] = 8 * k8;
         a_dst[it] = ((k8 >> 1) * 3 * TM + (row >> 5)) * 64 + (((row & 31) ^ swz) + 32 * (k8 & 1));
     }
     const int bn = min(n0 + l32, p.N - 1);
     const unsigned b_off = (B_LAYOUT == K_CONTIG) ? 4u * ((unsigned)bn * (unsigned)p.ldb + 8u * q) : 4u * (8u * q * (unsigned)p.ldb + (unsigned)bn);
+
+    // What only the last slabs and the epilogue need is worked out there in the forward products, from a thread index that
+    // the compiler cannot look through: kept over the loop it costs registers that their kernels would have to spill (up to
+    // ten; 256->128, 4 workers, 64 rows 7.4 us -> 7.0 without).
+    constexpr bool LATE = A_LAYOUT == K_CONTIG && B_LAYOUT == MN_CONTIG;
+    auto thread = [&] {
+        int t = tid;
+        if constexpr (LATE) keep_loaded(t);
+        return t;
+    };
+    auto a_k = [&](int it) { return LATE ? 8 * ((thread() + it * 256) % K8) : a_kept[it]; };
 
     struct RawA { f32x8 x[IT]; };
     struct RawB { f32x8 x[KS]; };
@@ -170,11 +181,12 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
                 for (int e = 0; e < 8; ++e)
                     r.x[it][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)a_off[it], (int)(4u * (unsigned)(k0 + e) * (unsigned)p.lda), 0));
         } else if (!early && slab < n_slabs) {
+            const int ku = a_k(it);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const unsigned k = (unsigned)min(k0 + a_k[it] + e, a_klim - 1);
-                const unsigned off = (A_LAYOUT == K_CONTIG) ? a_off[it] - 4u * (unsigned)a_k[it] + 4u * k
-                                                            : a_off[it] + 4u * (k - (unsigned)a_k[it]) * (unsigned)p.lda;
+                const unsigned k = (unsigned)min(k0 + ku + e, a_klim - 1);
+                const unsigned off = (A_LAYOUT == K_CONTIG) ? a_off[it] - 4u * (unsigned)ku + 4u * k
+                                                            : a_off[it] + 4u * (k - (unsigned)ku) * (unsigned)p.lda;
                 r.x[it][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)off, 0, 0));
             }
         }
@@ -196,7 +208,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
             }
         }
     };
-    auto cut_a = [&](int slab, int it, RawA &r) { cut(r.x[it], start(slab) + a_k[it], k_begin + slab * BK, a_klim, k_ones); };
+    auto cut_a = [&](int slab, int it, RawA &r) { cut(r.x[it], start(slab) + a_k(it), k_begin + slab * BK, a_klim, k_ones); };
     auto cut_b = [&](int slab, int ks, RawB &r) { cut(r.x[ks], start(slab) + 16 * (wk + ks * WK) + 8 * q, k_begin + slab * BK, k_end, -1); };
     auto a_here = [&](int it) { return T::UNITS % 256 == 0 || tid + it * 256 < T::UNITS; };
     auto store_a = [&](int buf, int it, const SplitFrag &f) {
@@ -318,6 +330,8 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     }
 
     // ---- the two sums meet; what went out of the scaled range is summed again (head of the file) ----
+    const int late = thread() & 63, c32 = late & 31, cq = late >> 5;         // lane, column and row group of C
+    const int n = n0 + c32, nc = min(n, p.N - 1);
     f32x16 acc[TM];
     f32x8 bad = {};                                      // eight chains: NaN as soon as one of a chain's sums is not finite
 #pragma unroll
@@ -342,19 +356,19 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
                 float x[4][TM], y[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int k = kb + half + 2 * u + q;
+                    const int k = kb + half + 2 * u + cq;
                     const bool in = k >= first && k < k_end;
                     const unsigned ka = (unsigned)max(min(k, a_klim - 1), 0), kc = (unsigned)min(k, k_end - 1);
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
-                        const int row = m0 + 32 * i + l32;
+                        const int row = m0 + 32 * i + c32;
                         const unsigned m = (unsigned)min(row, a_rows - 1);
                         const unsigned off = 4u * (A_LAYOUT == K_CONTIG ? m * (unsigned)p.lda + ka : kc * (unsigned)p.lda + m);
                         const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)off, 0, 0));
                         const bool one = A_LAYOUT == K_CONTIG ? k == k_ones : row == p.a_ones;
                         x[u][i] = !in ? 0.f : one ? 1.f : A_LAYOUT == K_CONTIG && k >= a_klim ? 0.f : v;
                     }
-                    const unsigned off = 4u * (B_LAYOUT == K_CONTIG ? (unsigned)bn * (unsigned)p.ldb + kc : kc * (unsigned)p.ldb + (unsigned)bn);
+                    const unsigned off = 4u * (B_LAYOUT == K_CONTIG ? (unsigned)nc * (unsigned)p.ldb + kc : kc * (unsigned)p.ldb + (unsigned)nc);
                     const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bb, (int)off, 0, 0));
                     y[u] = in ? v : 0.f;
                 }
@@ -382,16 +396,16 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                ex[((wk * TM + i) * 4 + g) * 64 + lane] = f32x4{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
+                ex[((wk * TM + i) * 4 + g) * 64 + late] = f32x4{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int gg = 0; gg < GROUPS; ++gg) {
                 const int g = gg * WK + wk;
-                f32x4 v = ex[(i * 4 + g) * 64 + lane];
+                f32x4 v = ex[(i * 4 + g) * 64 + late];
 #pragma unroll
-                for (int o = 1; o < WK; ++o) v += ex[((o * TM + i) * 4 + g) * 64 + lane];
+                for (int o = 1; o < WK; ++o) v += ex[((o * TM + i) * 4 + g) * 64 + late];
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr) val[i][gg][rr] = v[rr];
             }
@@ -411,13 +425,12 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     float *__restrict__ Vr = MOM ? p.Vt + (size_t)w * p.c_ws : nullptr;
     unsigned short *__restrict__ Vr16 = MOM16 ? p.Vt16 + (size_t)w * p.c_ws : nullptr;
     const float *__restrict__ Cc = ELASTIC ? p.center : nullptr;
-    const int n = n0 + l32, nc = min(n, p.N - 1);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int mt = m0 + 32 * i;                                                   // uniform
         if (mt >= p.M) break;
         const bool rows_in = mt + 32 <= p.M;
-        auto row = [&](int gg, int rr) { return mt + 8 * (gg * WK + wk) + 4 * q + rr; };
+        auto row = [&](int gg, int rr) { return mt + 8 * (gg * WK + wk) + 4 * cq + rr; };
         float wv[GROUPS][4], cv[GROUPS][4], vv[GROUPS][4], gate[GROUPS][4];
         unsigned short v16[GROUPS][4];
         (void)wv; (void)cv; (void)vv; (void)gate; (void)v16;
