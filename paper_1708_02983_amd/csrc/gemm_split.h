@@ -509,13 +509,13 @@ __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_dw_
 
 // An input-gradient product with the weight-gradient product of a narrow layer, whose few blocks come first: they are a
 // chain of round trips to memory, which the blocks of the other product cover.
-template <int TM, int WN, int WK, int EPI>
-__global__ __launch_bounds__(256, TM <= 2 ? 3 : 2) void gemm_split_da_narrow_dw_kernel(GemmArgs da, GemmArgs dw, unsigned n_dw)
+template <int TM, int WN, int WK, int EPI, bool VEC_DW>
+__global__ __launch_bounds__(256, 3) void gemm_split_da_narrow_dw_kernel(GemmArgs da, GemmArgs dw, unsigned n_dw)
 {
     constexpr int NARROW = gemm_lds_floats<128, 32, 32, MN_CONTIG, MN_CONTIG>() / 4, SPLIT = SplitTile<TM, WN, WK>::LDS_VECS;
     __shared__ u32x4 lds[NARROW > SPLIT ? NARROW : SPLIT];
     if (dw.mean.blocks > 0 && blockIdx.x >= dw.mean.first_block) mean_loss_block(dw.mean, blockIdx.x - dw.mean.first_block);
-    else if (blockIdx.x < n_dw) gemm_block<128, 32, 32, 4, 1, MN_CONTIG, MN_CONTIG, false, EPI>(dw, blockIdx.x, reinterpret_cast<float *>(lds));
+    else if (blockIdx.x < n_dw) gemm_block<128, 32, 32, 4, 1, MN_CONTIG, MN_CONTIG, VEC_DW, EPI>(dw, blockIdx.x, reinterpret_cast<float *>(lds));
     else split_block<TM, WN, WK, K_CONTIG, K_CONTIG, EPI_MASK>(da, blockIdx.x - n_dw, lds);
 }
 

@@ -342,25 +342,38 @@ static void launch_split_pair_dw_dw(GemmArgs d0, GemmArgs d1, hipStream_t s)
     EASGD_LAUNCH((gemm_split_dw_pair_kernel<2, 4, 1, EPI>), dim3(n0 + n1 + d0.mean.blocks), dim3(256), 0, s, d0, d1, n0);
 }
 
-// An input-gradient product and the weight-gradient product of a narrow layer in one launch; false: this tile has none.
-template <int EPI>
+// An input-gradient product and the weight-gradient product of a narrow layer in one launch, the first as split tiles of
+// `pick`'s shape; false: this tile has none.
+template <int EPI, bool VEC_DW>
 static bool launch_split_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, SplitPick pick, hipStream_t s)
 {
-    const unsigned n_dw = place_blocks<128, 32>(dw);
-    if (pick == SPLIT_64x128) {
-        const unsigned n = place_blocks<64, 128>(da);
+    auto launch = [&](auto tm, auto wn, auto wk) {
+        constexpr int TM = decltype(tm)::value, WN = decltype(wn)::value, WK = decltype(wk)::value;
+        const unsigned n_dw = place_blocks<128, 32>(dw), n = place_blocks<TM * 32, WN * 32>(da);
         dw.mean.first_block = n + n_dw;
-        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<2, 4, 1, EPI>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
-    } else if (pick == SPLIT_64x64) {
-        const unsigned n = place_blocks<64, 64>(da);
-        dw.mean.first_block = n + n_dw;
-        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<2, 2, 2, EPI>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
-    } else if (pick == SPLIT_32x32) {
-        const unsigned n = place_blocks<32, 32>(da);
-        dw.mean.first_block = n + n_dw;
-        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<1, 1, 4, EPI>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
-    } else return false;
-    return true;
+        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<TM, WN, WK, EPI, VEC_DW>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
+        return true;
+    };
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 4> four{};
+    if (pick == SPLIT_64x128) return launch(two, four, one);
+    if (pick == SPLIT_64x64) return launch(two, two, two);
+    if (pick == SPLIT_32x128) return launch(one, four, one);
+    if (pick == SPLIT_32x32) return launch(one, one, four);
+    return false;
+}
+
+// The same with 64x64 tiles of the fp32 instruction.
+template <int EPI, bool VEC_DW>
+static void launch_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, hipStream_t s)
+{
+    const unsigned n0 = place_blocks<64, 64>(da), n1 = place_blocks<128, 32>(dw);
+    da.mean = dw.mean;
+    da.mean.first_block = n0 + n1;
+    EASGD_LAUNCH((gemm_pair_kernel<64, 64, 32, 2, 2, K_CONTIG, K_CONTIG, true, EPI_MASK,
+                                         128, 32, SPLIT_BK, 4, 1, MN_CONTIG, MN_CONTIG, VEC_DW, EPI>),
+                       dim3(n0 + n1 + da.mean.blocks), dim3(256), 0, s, da, dw, n0);
 }
 
 // Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile of the fp32 matrix instruction; input gradients, a
@@ -720,12 +733,16 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     const bool pairing = options().gemm_pair != 0;
     const bool tile64 = options().gemm_tile == 0 || options().gemm_tile == 2;   // wide weight gradients use 64x64 or gemm_split.h
     struct Held { bool have = false; GemmArgs a; bool vec = false; } held;
+    // calls f with the epilogue of the weight gradients as a constant
+    auto by_rule = [&](auto f) {
+        if (epi == EPI_NONE) f(std::integral_constant<int, EPI_NONE>{});
+        else if (epi == EPI_STORE_BF16) f(std::integral_constant<int, EPI_STORE_BF16>{});
+        else if (epi == EPI_ELASTIC) f(std::integral_constant<int, EPI_ELASTIC>{});
+        else if (epi == EPI_ELASTIC_MOM) f(std::integral_constant<int, EPI_ELASTIC_MOM>{});
+        else f(std::integral_constant<int, EPI_ELASTIC_MOM_BF16>{});
+    };
     auto launch_dw = [&](const GemmArgs &d, bool vec) {
-        if (epi == EPI_NONE) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_NONE>(d, vec, s, fp32);
-        else if (epi == EPI_STORE_BF16) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_STORE_BF16>(d, vec, s, fp32);
-        else if (epi == EPI_ELASTIC) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC>(d, vec, s, fp32);
-        else if (epi == EPI_ELASTIC_MOM) launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM>(d, vec, s, fp32);
-        else launch_gemm<MN_CONTIG, MN_CONTIG, EPI_ELASTIC_MOM_BF16>(d, vec, s, fp32);
+        by_rule([&](auto e) { launch_gemm<MN_CONTIG, MN_CONTIG, decltype(e)::value>(d, vec, s, fp32); });
     };
     // the first kernel that changes W waits for the center rule, which reads W at time t
     bool joined = lane == nullptr;
@@ -754,16 +771,26 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
             a.M = b; a.N = d_in; a.K = d_out; a.P = P;
             a.splits = 1; a.k_per_split = (a.K + 63) / 64 * 64;
             const bool vec = mult4(d_out);
-            // A held narrow product shares this launch where the tile leaves a block per compute unit free; with the center
-            // rule on the second stream it waits, so that the rule has this launch to finish behind as well.
+            // A held narrow product shares this launch where the tile leaves a block per compute unit free: not with 128x128
+            // tiles, and with the fp32 instruction up to three of its four blocks per compute unit (gradient of 784-256-512-12,
+            // 16 workers, 128 rows 73.2 us -> 70.6 with the aligned loader for the narrow product; 784-1024-1024-12, 32, 24
+            // 194.6 -> 191.3; 3072-1024-2048-10, 16, 100, all on the fp32 instruction, 479 -> 471).  With the center rule on the
+            // second stream it waits, so that the rule has this launch to finish behind as well (rounds of 784-512-2048-12,
+            // 16, 128 201.0 us against 202.1, 784-1024-1024-12 206.7 against 207.3).
             bool shared = false;
-            if (held.have && pairing && !lane && !fp32 && held.a.N <= 32 && a.N > 32 && options().gemm_tile == 0 && split_fits(a, true, true)) {
-                const SplitPick pick = split_pick(a.M, a.N, P, 1);
-                if (epi == EPI_NONE) shared = launch_split_pair_da_narrow_dw<EPI_NONE>(a, held.a, pick, s);
-                else if (epi == EPI_STORE_BF16) shared = launch_split_pair_da_narrow_dw<EPI_STORE_BF16>(a, held.a, pick, s);
-                else if (epi == EPI_ELASTIC) shared = launch_split_pair_da_narrow_dw<EPI_ELASTIC>(a, held.a, pick, s);
-                else if (epi == EPI_ELASTIC_MOM) shared = launch_split_pair_da_narrow_dw<EPI_ELASTIC_MOM>(a, held.a, pick, s);
-                else shared = launch_split_pair_da_narrow_dw<EPI_ELASTIC_MOM_BF16>(a, held.a, pick, s);
+            if (held.have && pairing && !lane && held.a.N <= 32 && a.N > 32) {
+                const SplitPick pick = fp32 || options().gemm_tile != 0 || !split_fits(a, true, true) ? SPLIT_NONE : split_pick(a.M, a.N, P, 1);
+                const size_t blocks = (size_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * P;
+                const bool fp32_pair = pick == SPLIT_NONE && vec && tile64 && blocks <= (size_t)3 * num_cus();
+                if (fp32_pair || (pick != SPLIT_NONE && pick != SPLIT_128x128)) {
+                    if (!join()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
+                    by_rule([&](auto e) {
+                        constexpr int E = decltype(e)::value;
+                        if (fp32_pair) held.vec ? launch_pair_da_narrow_dw<E, true>(a, held.a, s) : launch_pair_da_narrow_dw<E, false>(a, held.a, s);
+                        else held.vec ? launch_split_pair_da_narrow_dw<E, true>(a, held.a, pick, s) : launch_split_pair_da_narrow_dw<E, false>(a, held.a, pick, s);
+                    });
+                    shared = true;
+                }
             }
             if (shared) held.have = false;
             else {
@@ -795,16 +822,10 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
             const bool both_fp32 = !split0 && !split1 && tile64 && held.vec && vec && held.a.N > 32 && d.N > 32;
             if (pairing && ((split0 && split1) || both_fp32)) {
                 if (!join()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
-                auto pair = [&](auto e) {
-                    constexpr int E = decltype(e)::value;
-                    if (both_fp32) launch_pair_dw_dw<E>(held.a, d, s);
-                    else launch_split_pair_dw_dw<E>(held.a, d, s);
-                };
-                if (epi == EPI_NONE) pair(std::integral_constant<int, EPI_NONE>{});
-                else if (epi == EPI_STORE_BF16) pair(std::integral_constant<int, EPI_STORE_BF16>{});
-                else if (epi == EPI_ELASTIC) pair(std::integral_constant<int, EPI_ELASTIC>{});
-                else if (epi == EPI_ELASTIC_MOM) pair(std::integral_constant<int, EPI_ELASTIC_MOM>{});
-                else pair(std::integral_constant<int, EPI_ELASTIC_MOM_BF16>{});
+                by_rule([&](auto e) {
+                    if (both_fp32) launch_pair_dw_dw<decltype(e)::value>(held.a, d, s);
+                    else launch_split_pair_dw_dw<decltype(e)::value>(held.a, d, s);
+                });
                 held.have = false;
                 continue;
             }
