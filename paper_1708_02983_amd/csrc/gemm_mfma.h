@@ -820,12 +820,12 @@ template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int A_LAYOUT, int B_
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, 2) void gemm_mfma_kernel(GemmArgs p)
 {
     __shared__ __attribute__((aligned(16))) float lds[gemm_lds_floats<BM, BN, BK, A_LAYOUT, B_LAYOUT>()];
-    if (p.ctr.blocks > 0 && blockIdx.x >= p.ctr.first_block) {         // uniform for the block
+    if (A_LAYOUT == K_CONTIG && B_LAYOUT == MN_CONTIG && p.ctr.blocks > 0 && blockIdx.x >= p.ctr.first_block) {         // uniform for the block
         const size_t b = blockIdx.x - p.ctr.first_block;
         center_rule_block(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
         return;
     }
-    if (p.mean.blocks > 0 && blockIdx.x >= p.mean.first_block) {
+    if (A_LAYOUT == MN_CONTIG && p.mean.blocks > 0 && blockIdx.x >= p.mean.first_block) {
         mean_loss_block(p.mean, blockIdx.x - p.mean.first_block);
         return;
     }

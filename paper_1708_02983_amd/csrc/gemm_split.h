@@ -485,12 +485,12 @@ template <int TM, int WN, int WK, int A_LAYOUT, int B_LAYOUT, int EPI>
 __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_kernel(GemmArgs p)
 {
     __shared__ u32x4 lds[SplitTile<TM, WN, WK>::LDS_VECS];
-    if (p.ctr.blocks > 0 && blockIdx.x >= p.ctr.first_block) {         // uniform for the block
+    if (A_LAYOUT == K_CONTIG && B_LAYOUT == MN_CONTIG && p.ctr.blocks > 0 && blockIdx.x >= p.ctr.first_block) {         // uniform for the block
         const size_t b = blockIdx.x - p.ctr.first_block;
         center_rule_block(p.ctr.W, p.ctr.Wc, p.ctr.old, p.ctr.P, p.ctr.N, p.ctr.ld, p.ctr.alpha, b, p.ctr.blocks, threadIdx.x);
         return;
     }
-    if (p.mean.blocks > 0 && blockIdx.x >= p.mean.first_block) {
+    if (A_LAYOUT == MN_CONTIG && p.mean.blocks > 0 && blockIdx.x >= p.mean.first_block) {
         mean_loss_block(p.mean, blockIdx.x - p.mean.first_block);
         return;
     }

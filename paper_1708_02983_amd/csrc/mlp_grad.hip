@@ -23,6 +23,7 @@
 #include "gemm_split.h"
 #include "mlp_head.h"
 #include "persistent_round.h"
+#include <algorithm>
 #include <mutex>
 
 // The workspace of easgd_grad_static: device memory that belongs to the library, one copy per GPU, held from
@@ -290,24 +291,74 @@ static bool split_fits(const GemmArgs &a, bool a_k_contig, bool b_k_contig)
     return (ra + 128) * (size_t)a.lda < lim && (rb + 128) * (size_t)a.ldb < lim;
 }
 
-// The products whose rows are the minibatch: the largest tile that still gives every compute unit a block.  The smaller
-// the grid, the more a block's own chain of slabs decides, and the more wavefronts share a tile along k (the last two
-// numbers of a tile's name in gemm_split.h).  Measured, us per product, 128x128 / 64x128 / 64x64 / 32x32, and the fp32
-// matrix instruction's best tile (forward: d_in -> d_out, workers, minibatch):
+// The products whose rows are the minibatch (forward, input gradient): the largest tile that still gives every compute unit
+// a block.  The smaller the grid, the more a block's own chain of slabs decides, and the more wavefronts share a tile along
+// k (the last two numbers of a tile's name in gemm_split.h).  Measured, us per product, 128x128 / 64x128 / 64x64 / 32x32, and
+// the fp32 instruction's best tile (forward: d_in -> d_out, workers, minibatch):
 //   3072->2048, 32, 100   276 / 291 / 359 / 521     365
 //   3072->2048,  8, 256   147 / 150 / 182 / 258     207
 //    784->1024, 16, 128    37 /  27 /  29 /  40      32
 //   1023-> 777,  6,  37    41 /  28 /  21 /  15      48 (no 128-bit loads)
 //    784-> 500,  8,  50    34 /  24 /  17 /  11      18
-static SplitPick split_pick(int M, int N, int P, int splits)
+// SPLIT_NONE where the fp32 instruction is faster: below a length of the sum that depends on the tile and on how full its
+// grid is (a block of the split form takes longer to start), and for small tiles whenever the 64x64 tiles of the fp32
+// instruction just fill the chip, since the split form then has to multiply in tiles that load more per product.  Time of
+// the fp32 instruction over that of the split form at sums of 64, 128, 256, 512 (first the shape as columns, workers, rows):
+//                              forward                    input gradient, 128-bit loads
+//   128x128  2048, 24, 128     0.90 1.02 1.19 1.22        0.94 1.16 1.27 1.24
+//   128x128  1024, 32, 128     0.76 0.88 1.06 1.25        0.80 0.93 1.11 1.29
+//   64x128   1024, 16, 128     0.74 0.82 0.91 1.05        0.80 0.87 1.00 1.12
+//   64x128   2048, 32,  64     1.26 1.49 1.79 1.98        0.92 1.06 1.19 1.11
+//   64x64     768, 12, 192     0.73 0.83 0.94 1.06        0.81 0.87 1.00 1.10
+//   64x64     512, 16, 128     0.67 0.72 0.78 0.87        0.73 0.79 0.84 0.87     (sum of 2048: 0.99, 0.96)
+//   32x128   2048, 16,  20     0.80 0.85 0.99 1.15        0.91 1.04 1.15 1.29
+//   32x32     512,  8,  50     0.86 0.93 1.10 1.37        1.01 1.10 1.30 1.54
+//   32x32     256, 16, 128     0.71 0.75 0.91 1.13        0.84 0.93 1.07 1.22
+//   32x32     500, 10, 100     0.66 0.71 0.81 0.94        0.81 0.87 0.94 1.04
+//   32x32     500, 15, 100     0.58 0.63 0.69 0.78        0.74 0.77 0.83 0.86     (sum of 2048: 0.92, 0.90)
+//   32x32     640, 32,  16     0.80 0.93 1.18 1.48        0.96 1.16 1.37 1.67
+// Input gradients whose widths rule out 128-bit loads on the fp32 path (301, 5, 90: 1.28 1.63 2.23; 257, 16, 127: 0.99 1.19
+// 1.53; 1023, 16, 128 1.01 at a sum of 49) take the split form from sums of 40 on, or 64 on a large grid of the smallest
+// tile; forward products of such widths, whose 128-bit loads straddle cache lines,
+// at nine sixteenths of the length (logits of 112 inputs, 106 classes, 3 workers, 162 rows: 8.4 us against 6.8; of 3072, 593,
+// 3, 124 in sums of 224: 22.7 against 18.4).  Where the fp32 instruction would multiply in 16-row tiles, whose start is slow,
+// the split form takes all but the shortest sums (2048, 32, 100: 1.06 and 1.26 at 48; input gradient of 1224, 18, 234, a sum of
+// 68: 28.4 us against 18.0).
+static SplitPick split_pick(const GemmArgs &a, bool forward, bool vec, bool any_length = false)
 {
+    if (options().gemm_tile != 0 || a.N <= 32 || !split_fits(a, true, !forward)) return SPLIT_NONE;
     const size_t cus = (size_t)num_cus();
-    auto blocks = [&](int bm, int bn) { return (size_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * (size_t)P * (size_t)splits; };
-    if (M > 64 && blocks(128, 128) >= cus) return SPLIT_128x128;
-    if (M > 32 && blocks(64, 128) >= cus) return SPLIT_64x128;
-    if (M > 32 && blocks(64, 64) >= cus) return SPLIT_64x64;
-    if (M <= 32 && blocks(32, 128) >= cus) return SPLIT_32x128;
-    return SPLIT_32x32;
+    auto blocks = [&](int bm, int bn) { return (size_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * (size_t)a.P * (size_t)a.splits; };
+    constexpr int NEVER = 0x7fffffff;
+    const size_t fp32 = blocks(64, 64);                      // the grid of the fp32 instruction's tile
+    SplitPick pick;
+    int least;                                               // shortest sum
+    if (a.M > 64 && blocks(128, 128) >= cus) {
+        pick = SPLIT_128x128;
+        least = 2 * blocks(128, 128) >= 3 * cus ? (forward ? 128 : 112) : (forward ? 192 : 160);
+    } else if (a.M > 32 && blocks(64, 128) >= cus) {
+        pick = SPLIT_64x128;
+        least = blocks(64, 128) >= 2 * cus ? (forward ? 0 : 96) : (forward ? 384 : 256);
+    } else if (a.M > 32 && blocks(64, 64) >= cus) {
+        pick = SPLIT_64x64;
+        least = fp32 <= cus ? NEVER : (forward ? 384 : 256);
+    } else if (a.M <= 32 && blocks(32, 128) >= cus) {
+        pick = SPLIT_32x128;
+        const size_t n = blocks(32, 128);
+        least = !forward ? 112 : n >= 2 * cus ? 0 : 2 * n >= 3 * cus ? 192 : 288;
+    } else {
+        pick = SPLIT_32x32;
+        const size_t n = blocks(32, 32);
+        if (n <= cus || fp32 > cus) least = forward ? 192 : 112;
+        else if (n <= 2 * cus) least = forward ? 384 : 192;
+        else least = 5 * fp32 > 4 * cus && a.M > 32 ? NEVER : (forward ? 768 : 384);
+    }
+    if (!vec) {
+        if (!forward) least = least == NEVER ? 128 : std::min(least, pick == SPLIT_32x32 && blocks(32, 32) > 2 * cus ? 64 : 40);
+        else if (least != NEVER) least = least / 16 * 9;
+    }
+    if (tile16_rows(a.M, a.N, a.P, a.splits) != 0) least = std::min(least, 32);
+    return any_length || std::min(a.K, a.k_per_split) >= least ? pick : SPLIT_NONE;
 }
 
 template <int TM, int WN, int WK, int AL, int BL, int EPI>
@@ -324,14 +375,66 @@ static void launch_split(const GemmArgs &a_in, hipStream_t s)
     EASGD_LAUNCH((gemm_split_kernel<TM, WN, WK, AL, BL, EPI>), dim3((unsigned)total), dim3(256), 0, s, a);
 }
 
-// Weight gradients: 64x128 tiles when they give every compute unit two blocks, or when the operands rule out the fp32
-// path's 128-bit loads.  Below that the 64x64 fp32 tiles win: their sums are so short that a block is its latency
-// (784 -> 500, 8 workers, minibatch 50: 10.2 us against 9.3; 1024 -> 1024, 16, 128: 39 against 48; 3072 -> 2048, 32, 100:
-// 390 against 420; 1023 -> 777, 6, 37, odd widths: 12.5 against 14.1).
-static bool split_dw(const GemmArgs &a, bool vec)
+// Weight gradients: whether 64x128 split tiles can take the product (not on grids of less than two blocks per compute unit
+// when the fp32 path has 128-bit loads: 784->500, 8 workers, 50 rows 10.2 us against 9.3).
+static size_t split_dw_blocks(const GemmArgs &a) { return (size_t)((a.M + 63) / 64) * ((a.N + 127) / 128) * (size_t)a.P; }
+
+static bool split_dw_fits(const GemmArgs &a, bool vec)
 {
-    if (options().gemm_tile != 0 || a.N <= 32 || !split_fits(a, false, false)) return false;
-    return !vec || (size_t)((a.M + 63) / 64) * ((a.N + 127) / 128) * (size_t)a.P >= (size_t)(2 * num_cus());
+    return options().gemm_tile == 0 && a.N > 32 && split_fits(a, false, false) && (!vec || split_dw_blocks(a) >= (size_t)(2 * num_cus()));
+}
+
+// ... and whether they are faster than the 64x64 tiles of the fp32 instruction: where the products that they multiply for
+// nothing, in half empty tiles of columns and in the last slab of 32 rows, leave them the advantage.  The same for all
+// epilogues, so that the gradient of a round is that of easgd_grad.  With 128-bit loads on the fp32 path, time of the fp32
+// instruction over that of the split form at 24, 32, 50, 64, 100, 128 rows (layer, workers), no worker rule:
+//   1024->1024, 16   1.08 1.16 1.00 1.14 1.16 1.29
+//   2048->2048,  2   0.97 1.03 0.92 1.04 1.07 1.21
+//   1024-> 160, 32   0.77 0.89 0.79 0.91 0.88 0.99
+//   1024->  48, 32   0.64 0.74 0.67 0.73 0.71 0.83
+// With the worker rule in the epilogue both move the replicas as well and there is less to gain; us a round gained or lost
+// (784-1024-10, 16 workers: -0.5 -1.4 +3.7 +2.7 +1.9 -1.8; 3072-2048-10, 8: -3.5 -0.0 +7.2 +4.4 +0.4 -16.4).
+// Without 128-bit loads (no worker rule):
+//   1023->1022, 16   1.16 1.32 1.37 1.57 1.68 1.99   (with the rule, at 40 rows: +2.2 us of 70)
+//    783->1024,  4   0.98 1.12 1.16 1.40 1.47 1.80   (416 blocks)
+//    601-> 641,  4   0.88 0.96 0.97 1.10 1.16 1.39   (240 blocks; with the rule +1.5 +1.0 +1.2 +0.2 -0.5 -2.5 us)
+//    255-> 500,  3   0.77 0.83 0.77 0.90 0.90 1.11   (48 blocks; with the rule +0.2 us at 128 rows)
+//    783->  35, 20   0.76 0.82 0.81 0.94 0.93 1.12   (260 blocks, the columns of half a tile)
+static bool split_dw_pays(const GemmArgs &a, bool vec)
+{
+    if (!split_dw_fits(a, vec)) return false;
+    const size_t cus = (size_t)num_cus(), blocks = split_dw_blocks(a);
+    if (vec) {
+        if (a.K > 32 && a.K <= 96) return false;
+        const long columns = (a.N + 127) / 128 * 2, needed = (a.N + 63) / 64;        // in tiles of 64
+        const long multiplied = (a.K + 31) / 32 * 32 * columns, useful = a.K * needed;
+        return 100 * multiplied <= (a.K > 96 ? 114 : 134) * useful;
+    }
+    if (a.N <= 64 || 2 * blocks < cus) return a.K >= 120;
+    if (blocks >= 2 * cus) return a.K >= 20 && !(a.K > 32 && a.K < 45);
+    return a.K >= (2 * blocks >= 3 * cus ? 44 : 64);
+}
+
+// In which form two weight gradients that follow one another are computed, so that they can share a launch; or each in the form
+// that pays for it, in a launch of its own.  Where both forms can take both, the form that pays for the larger one.  Where
+// only the fp32 form can take both, that one, up to the size at which the split form's gain on one of them makes up for a
+// launch (rounds of 3072-512-256-10, 128 rows, one launch / two: 4 workers 119.9 / 128.2 us, 8 140.9 / 145.8, 16
+// 184.6 / 181.7; 3072-768-128-10, 16: 265.5 / 256.3).  Where only the split form can take both, that one (gradient of
+// 1390-126-205-10, 7, 56: 59.6 us against 65.5 in two launches).  EASGD_OPT_GEMM_PAIR has no say: it changes no bit.
+enum Form { FORM_BY_SIZE, FORM_FP32, FORM_SPLIT };
+
+static Form dw_pair_form(const GemmArgs &a0, bool vec0, const GemmArgs &a1, bool vec1, bool fp32_only)
+{
+    const long tile = options().gemm_tile;
+    if (a0.N <= 32 || a1.N <= 32) return FORM_BY_SIZE;
+    const bool fp32 = (tile == 0 || tile == 2) && vec0 && vec1;
+    const bool split = !fp32_only && split_dw_fits(a0, vec0) && split_dw_fits(a1, vec1);
+    if (!fp32 || fp32_only) return split ? FORM_SPLIT : fp32 ? FORM_FP32 : FORM_BY_SIZE;
+    const bool pays0 = split_dw_pays(a0, vec0), pays1 = split_dw_pays(a1, vec1);
+    const double size0 = (double)a0.M * a0.N, size1 = (double)a1.M * a1.N;
+    if (split) return (size0 > size1 ? pays0 : pays1) ? FORM_SPLIT : FORM_FP32;
+    const double gain = (pays0 ? size0 * a0.K * a0.P : 0) + (pays1 ? size1 * a1.K * a1.P : 0);
+    return gain >= 3.0e9 ? FORM_BY_SIZE : FORM_FP32;
 }
 
 template <int EPI>
@@ -377,42 +480,41 @@ static void launch_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, hipStream_t s)
 }
 
 // Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile of the fp32 matrix instruction; input gradients, a
-// wide last layer and large weight gradients the tiles of gemm_split.h (split_pick, split_dw); everything else, and
+// wide last layer and weight gradients the tiles of gemm_split.h where split_pick and split_dw_pays say so; everything else, and
 // whatever EASGD_OPT_GEMM_TILE forces, tiles of the fp32 instruction: 64x64 blocks (four per compute unit, so that the
-// epilogue of one overlaps the products of the others), for the forward products the 16-row tiles or 128x128 where
-// they still give every compute unit about two blocks.
-// fp32: the product keeps the fp32 instruction and its order of sums (see the callers); large: 128x128 tiles are allowed.
+// epilogue of one overlaps the products of the others), for the products whose rows are the minibatch the 16-row tiles and
+// for the forward products 128x128 where they still give every compute unit about two blocks.
+// form: the caller's choice of the instruction (FORM_SPLIT where the product fits it).
 template <int AL, int BL, int EPI>
-static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, bool fp32 = false, bool large = false)
+static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, Form form = FORM_BY_SIZE)
 {
     if (a.N <= 32) {
         launch_tile<128, 32, SPLIT_BK, 4, 1, AL, BL, EPI>(a, vec, s);
         return;
     }
+    constexpr bool forward = AL == K_CONTIG && BL == MN_CONTIG;
     long tile = options().gemm_tile;
     if constexpr (AL == K_CONTIG) {
-        if (tile == 0 && !fp32 && split_fits(a, true, BL == K_CONTIG)) {
-            const SplitPick pick = split_pick(a.M, a.N, a.P, a.splits);
-            if (pick == SPLIT_128x128) launch_split<4, 4, 1, AL, BL, EPI>(a, s);
-            else if (pick == SPLIT_64x128) launch_split<2, 4, 1, AL, BL, EPI>(a, s);
-            else if (pick == SPLIT_64x64) launch_split<2, 2, 2, AL, BL, EPI>(a, s);
-            else if (pick == SPLIT_32x128) launch_split<1, 4, 1, AL, BL, EPI>(a, s);
-            else launch_split<1, 1, 4, AL, BL, EPI>(a, s);
-            return;
-        }
+        const SplitPick pick = form == FORM_FP32 ? SPLIT_NONE : split_pick(a, forward, vec, form == FORM_SPLIT);
+        if (pick == SPLIT_128x128) launch_split<4, 4, 1, AL, BL, EPI>(a, s);
+        else if (pick == SPLIT_64x128) launch_split<2, 4, 1, AL, BL, EPI>(a, s);
+        else if (pick == SPLIT_64x64) launch_split<2, 2, 2, AL, BL, EPI>(a, s);
+        else if (pick == SPLIT_32x128) launch_split<1, 4, 1, AL, BL, EPI>(a, s);
+        else if (pick == SPLIT_32x32) launch_split<1, 1, 4, AL, BL, EPI>(a, s);
+        if (pick != SPLIT_NONE) return;
         int bm16 = (tile == 0) ? tile16_rows(a.M, a.N, a.P, a.splits) : 0;
         if (tile == 4) bm16 = a.M <= 48 ? 48 : a.M <= 80 ? 80 : 112;    // forced: the smallest height that covers M, else 112
         if (bm16 == 112) launch_tile<112, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
         else if (bm16 == 80) launch_tile<80, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
         else if (bm16 == 48) launch_tile<48, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
         if (bm16) return;
-    } else if (!fp32 && split_dw(a, vec)) {
+    } else if (form == FORM_SPLIT ? split_dw_fits(a, vec) : form == FORM_BY_SIZE && split_dw_pays(a, vec)) {
         launch_split<2, 4, 1, AL, BL, EPI>(a, s);
         return;
     }
     const size_t big = (size_t)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.splits * a.P;
     if (tile == 4) tile = 0;            // the weight-gradient products have no 16-row form
-    if (tile == 0) tile = (large && big >= (size_t)(2 * num_cus())) ? 1 : 2;
+    if (tile == 0) tile = (forward && big >= (size_t)(2 * num_cus())) ? 1 : 2;
     if (tile == 1) launch_tile<128, 128, 16, 2, 2, AL, BL, EPI>(a, vec, s);
     else if (tile == 2) launch_tile<64, 64, 32, 2, 2, AL, BL, EPI>(a, vec, s);
     else launch_tile<128, 64, 32, 2, 2, AL, BL, EPI>(a, vec, s);
@@ -704,7 +806,7 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         if (l == 0) a.ctr = center_job;
         const bool vec = mult4(d_in) && mult4(d_out);       // 128-bit loads need the element's alignment only
         if (last) launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, s);
-        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s, true, true);
+        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s, FORM_FP32);
     }
     float *row_loss = reinterpret_cast<float *>(ws + pl.rowloss_off);
     const int rows = P * b;
@@ -730,9 +832,10 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     // and with so many units its other rounding of the replicas moves a gate of the round after now and then.  All products keep the
     // fp32 instruction there.
     const bool fp32 = (size_t)P * pl.N >= ((size_t)1 << 26);
+    const Form by_size = fp32 ? FORM_FP32 : FORM_BY_SIZE;
     const bool pairing = options().gemm_pair != 0;
     const bool tile64 = options().gemm_tile == 0 || options().gemm_tile == 2;   // wide weight gradients use 64x64 or gemm_split.h
-    struct Held { bool have = false; GemmArgs a; bool vec = false; } held;
+    struct Held { bool have = false; GemmArgs a; bool vec = false; Form form = FORM_BY_SIZE; } held;
     // calls f with the epilogue of the weight gradients as a constant
     auto by_rule = [&](auto f) {
         if (epi == EPI_NONE) f(std::integral_constant<int, EPI_NONE>{});
@@ -741,8 +844,8 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         else if (epi == EPI_ELASTIC_MOM) f(std::integral_constant<int, EPI_ELASTIC_MOM>{});
         else f(std::integral_constant<int, EPI_ELASTIC_MOM_BF16>{});
     };
-    auto launch_dw = [&](const GemmArgs &d, bool vec) {
-        by_rule([&](auto e) { launch_gemm<MN_CONTIG, MN_CONTIG, decltype(e)::value>(d, vec, s, fp32); });
+    auto launch_dw = [&](const Held &h) {
+        by_rule([&](auto e) { launch_gemm<MN_CONTIG, MN_CONTIG, decltype(e)::value>(h.a, h.vec, s, h.form); });
     };
     // the first kernel that changes W waits for the center rule, which reads W at time t
     bool joined = lane == nullptr;
@@ -754,7 +857,7 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     auto flush = [&]() {
         if (held.have) {
             if (!join()) return false;
-            launch_dw(held.a, held.vec);
+            launch_dw(held);
         }
         held.have = false;
         return true;
@@ -778,12 +881,15 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
             // second stream it waits, so that the rule has this launch to finish behind as well (rounds of 784-512-2048-12,
             // 16, 128 201.0 us against 202.1, 784-1024-1024-12 206.7 against 207.3).
             bool shared = false;
-            if (held.have && pairing && !lane && held.a.N <= 32 && a.N > 32) {
-                const SplitPick pick = fp32 || options().gemm_tile != 0 || !split_fits(a, true, true) ? SPLIT_NONE : split_pick(a.M, a.N, P, 1);
+            const bool narrow = held.have && held.a.N <= 32 && a.N > 32;
+            // without 128-bit loads only the split form can share: it is taken whatever the length of the sum (round of
+            // 784-254-57-10, 20, 19: 59.7 us against 66.6)
+            const Form form = by_size == FORM_BY_SIZE && narrow && !vec ? FORM_SPLIT : by_size;
+            if (narrow && pairing && !lane) {
+                const SplitPick pick = form == FORM_FP32 ? SPLIT_NONE : split_pick(a, false, vec, form == FORM_SPLIT);
                 const size_t blocks = (size_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * P;
                 const bool fp32_pair = pick == SPLIT_NONE && vec && tile64 && blocks <= (size_t)3 * num_cus();
                 if (fp32_pair || (pick != SPLIT_NONE && pick != SPLIT_128x128)) {
-                    if (!join()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
                     by_rule([&](auto e) {
                         constexpr int E = decltype(e)::value;
                         if (fp32_pair) held.vec ? launch_pair_da_narrow_dw<E, true>(a, held.a, s) : launch_pair_da_narrow_dw<E, false>(a, held.a, s);
@@ -794,7 +900,7 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
             }
             if (shared) held.have = false;
             else {
-                launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, vec, s, fp32);
+                launch_gemm<K_CONTIG, K_CONTIG, EPI_MASK>(a, vec, s, form);
                 if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
             }
         }
@@ -818,20 +924,26 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         }
         const bool vec = mult4(d_in) && mult4(d_out);
         if (held.have) {     // two weight-gradient products in a row (no input-gradient product for layer 0)
-            const bool split0 = !fp32 && split_dw(held.a, held.vec), split1 = !fp32 && split_dw(d, vec);
-            const bool both_fp32 = !split0 && !split1 && tile64 && held.vec && vec && held.a.N > 32 && d.N > 32;
-            if (pairing && ((split0 && split1) || both_fp32)) {
+            const Form form = dw_pair_form(held.a, held.vec, d, vec, fp32);
+            if (form != FORM_BY_SIZE && pairing) {
                 if (!join()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
                 by_rule([&](auto e) {
-                    if (both_fp32) launch_pair_dw_dw<decltype(e)::value>(held.a, d, s);
+                    if (form == FORM_FP32) launch_pair_dw_dw<decltype(e)::value>(held.a, d, s);
                     else launch_split_pair_dw_dw<decltype(e)::value>(held.a, d, s);
                 });
                 held.have = false;
                 continue;
             }
+            if (form != FORM_BY_SIZE) {
+                held.form = form;
+                if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
+                held = {true, d, vec, form};
+                if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
+                continue;
+            }
             if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
         }
-        held.have = true; held.a = d; held.vec = vec;
+        held = {true, d, vec, by_size};
     }
     if (!flush()) return fail(EASGD_ELAUNCH, "%s: stream join failed", name);
     return check_launch(name);

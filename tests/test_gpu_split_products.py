@@ -155,6 +155,27 @@ def test_values_at_the_ends_of_the_range(d_in, d_out, P, b):
         assert (np.abs(got[fin] - ref[fin]) <= bound[fin]).all(), kind
 
 
+@pytest.mark.parametrize("kind,d_in,d_out,P,b", [
+    (0, 64, 512, 8, 50), (0, 127, 1024, 8, 256), (0, 640, 500, 15, 100),         # short; a grid that the fp32 tiles fill
+    (2, 512, 64, 8, 50), (2, 1024, 100, 8, 256), (2, 500, 640, 15, 100),
+    (1, 1024, 48, 32, 100), (1, 1024, 1024, 16, 16), (1, 255, 500, 3, 40),       # half empty tiles; a short slab; few blocks
+], ids=lambda v: str(v))
+def test_products_that_the_split_form_would_slow_down_keep_the_fp32_instruction(kind, d_in, d_out, P, b):
+    """There the default gives the bits of the forced 64x64 tile."""
+    import paper_1708_02983_amd as hip
+    A, W, Z, ld = _operands(d_in, d_out, P, b)
+    width = (b * d_out, (d_in + 1) * d_out, b * d_in)[kind]
+    old = hip.get_option(hip.OPT_GEMM_TILE)
+    try:
+        got = []
+        for tile in (0, 2):
+            hip.set_option(hip.OPT_GEMM_TILE, tile)
+            got.append(_run(hip, kind, A, W, Z, d_in, d_out, ld, width))
+    finally:
+        hip.set_option(hip.OPT_GEMM_TILE, old)
+    np.testing.assert_array_equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("dims,P,b", [((63, 37, 41, 10), 3, 20), ((64, 65, 130, 20), 2, 33), ((33, 2048, 10), 16, 33)],
                          ids=lambda v: str(v).replace(" ", ""))
 def test_row_stride_does_not_change_a_bit(dims, P, b):
