@@ -719,6 +719,13 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     float *dz[3] = {reinterpret_cast<float *>(ws + pl.dz_off[0]), reinterpret_cast<float *>(ws + pl.dz_off[1]),
                     reinterpret_cast<float *>(ws + pl.dz_off[2])};
 
+    // Replicas that exceed the last-level cache (256 MB): the weight gradients are bound by the replicas' stream, so
+    // gemm_split.h has less to give (3072-2048-2048-10, 32 workers, 100 rows, with momentum: 2 207 us a round -> 2 119), and
+    // with so many units its other rounding of the replicas moves a gate of the round after now and then.  All products
+    // keep the fp32 instruction there, the logits included.
+    const bool fp32 = (size_t)P * pl.N >= ((size_t)1 << 26);
+    const Form by_size = fp32 ? FORM_FP32 : FORM_BY_SIZE;
+
     // a narrow last layer goes through mlp_head_kernel together with the softmax and its own input gradient
     const bool head = options().mlp_head != 0 && head_fits(dims, L);
     if (head && (size_t)P * ((b + HEAD_ROWS - 1) / HEAD_ROWS) > 0x3fffffffull) return fail(EASGD_ERANGE, "%s: P*b too large", name);
@@ -805,7 +812,7 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         a.c_ss = (size_t)P * b * d_out;
         if (l == 0) a.ctr = center_job;
         const bool vec = mult4(d_in) && mult4(d_out);       // 128-bit loads need the element's alignment only
-        if (last) launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, s);
+        if (last) launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, s, by_size);
         else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s, FORM_FP32);
     }
     float *row_loss = reinterpret_cast<float *>(ws + pl.rowloss_off);
@@ -827,12 +834,6 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     // independent products can share a launch (launch_pair_*): with the input-gradient product of the layer
     // below when the held one is narrow, or with the weight-gradient product of the layer below.
     const int epi = !step ? (G16 ? EPI_STORE_BF16 : EPI_NONE) : (step->V16 ? EPI_ELASTIC_MOM_BF16 : (step->V ? EPI_ELASTIC_MOM : EPI_ELASTIC));
-    // Replicas that exceed the last-level cache (256 MB): the weight gradients are bound by the replicas' stream, so
-    // gemm_split.h has less to give (3072-2048-2048-10, 32 workers, 100 rows, with momentum: 2 207 us a round -> 2 119),
-    // and with so many units its other rounding of the replicas moves a gate of the round after now and then.  All products keep the
-    // fp32 instruction there.
-    const bool fp32 = (size_t)P * pl.N >= ((size_t)1 << 26);
-    const Form by_size = fp32 ? FORM_FP32 : FORM_BY_SIZE;
     const bool pairing = options().gemm_pair != 0;
     const bool tile64 = options().gemm_tile == 0 || options().gemm_tile == 2;   // wide weight gradients use 64x64 or gemm_split.h
     struct Held { bool have = false; GemmArgs a; bool vec = false; Form form = FORM_BY_SIZE; } held;

@@ -199,3 +199,28 @@ def test_row_stride_does_not_change_a_bit(dims, P, b):
     for g, l in got[1:]:
         np.testing.assert_array_equal(g, got[0][0])
         np.testing.assert_array_equal(l, got[0][1])
+
+
+def test_logits_of_replicas_beyond_the_last_level_cache_keep_the_fp32_instruction():
+    """From 2^26 parameters in all replicas on every product does, the last layer's forward product included: the gradients
+    have the bits of the forced fp32 64x64 tile (whose sums run in the same order)."""
+    import paper_1708_02983_amd as hip
+    dims, P, b = (2048, 1000), 33, 64
+    N = workloads.mlp_num_params(dims)
+    assert P * N >= 2 ** 26 > (P - 1) * N
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    W = torch.empty((P, N), device="cuda").normal_(0.0, 0.03, generator=gen)
+    X = torch.rand((P, b, dims[0]), device="cuda", generator=gen)
+    y = torch.randint(0, dims[1], (P, b), dtype=torch.int32, device="cuda", generator=gen)
+    old = hip.get_option(hip.OPT_GEMM_TILE)
+    got = []
+    try:
+        for tile in (0, 2):
+            hip.set_option(hip.OPT_GEMM_TILE, tile)
+            G, loss = torch.full_like(W, float("nan")), torch.empty(P, device="cuda")
+            hip.easgd_grad(dims, W, X, y, G, loss)
+            got.append((G, loss))
+    finally:
+        hip.set_option(hip.OPT_GEMM_TILE, old)
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
