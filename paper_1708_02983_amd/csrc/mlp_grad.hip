@@ -522,20 +522,27 @@ static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, Form form = 
 
 static inline bool mult4(size_t x) { return (x & 3u) == 0; }
 
-// Whether the launch of a forward product (M x N per worker, P workers, `splits` K splits) leaves room on the
-// chip for extra blocks that do bandwidth-bound work beside it.  Mirrors launch_gemm: the 128x32 and 64x64
-// tiles use few enough registers and LDS for four blocks per compute unit, the 128x128 tile for two, and it
-// is chosen exactly when its blocks already fill those.
-static bool forward_launch_has_room(int M, int N, int P, int splits)
+// Whether the launch of a forward product leaves room on the chip for extra blocks that do bandwidth-bound work beside it.
+// Mirrors launch_gemm: the 128x32 and 64x64 tiles use few enough registers and LDS for four blocks per compute unit, the
+// 128x128 tile for two, and it is chosen exactly when its blocks already fill those; the split tiles of 32, 64 and 128 rows
+// four, three and two (split_blocks_per_cu).
+static bool forward_launch_has_room(const GemmArgs &a, bool vec, Form form)
 {
     const size_t cus = (size_t)num_cus();
-    if (N <= 32) return (size_t)((M + 127) / 128) * splits * P <= 3 * cus;
+    auto blocks = [&](int bm, int bn) { return (size_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * (size_t)a.splits * (size_t)a.P; };
+    if (a.N <= 32) return blocks(128, 32) <= 3 * cus;
+    switch (form == FORM_FP32 ? SPLIT_NONE : split_pick(a, true, vec, form == FORM_SPLIT)) {
+    case SPLIT_128x128: return blocks(128, 128) <= cus;
+    case SPLIT_64x128: return blocks(64, 128) <= 2 * cus;
+    case SPLIT_64x64: return blocks(64, 64) <= 2 * cus;
+    case SPLIT_32x128: return blocks(32, 128) <= 3 * cus;
+    case SPLIT_32x32: return blocks(32, 32) <= 3 * cus;
+    case SPLIT_NONE: break;
+    }
     long tile = options().gemm_tile;
-    if (tile == 4 || (tile == 0 && tile16_rows(M, N, P, splits) != 0)) return false;
-    const size_t big = (size_t)((M + 127) / 128) * ((N + 127) / 128) * splits * P;
-    if (tile == 0) tile = (big >= 2 * cus) ? 1 : 2;
-    if (tile != 2) return false;
-    return (size_t)((M + 63) / 64) * ((N + 63) / 64) * splits * P <= 3 * cus;
+    if (tile == 4 || (tile == 0 && tile16_rows(a.M, a.N, a.P, a.splits) != 0)) return false;
+    if (tile == 0) tile = (blocks(128, 128) >= 2 * cus) ? 1 : 2;
+    return tile == 2 && blocks(64, 64) <= 3 * cus;
 }
 
 // Elastic update fused into the backward pass.  Eq. (2) runs first and saves the time-t
@@ -746,6 +753,23 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         // otherwise (stream under capture, no barrier words left): the separate launches below
     }
 
+    // the product of layer l's forward propagation, its loads and its form
+    auto forward_args = [&](int l) {
+        const int d_in = dims[l], d_out = dims[l + 1];
+        const bool last = (l == L - 1);
+        GemmArgs a = {};
+        a.A = act(l); a.a_ws = (size_t)b * d_in; a.lda = d_in; a.a_lim = d_in; a.a_ones = d_in;
+        a.B = W + pl.off[l]; a.b_ws = ld; a.ldb = d_out;
+        a.C = last ? logits : const_cast<float *>(act(l + 1)); a.c_ws = (size_t)b * d_out; a.ldc = d_out;
+        a.M = b; a.N = d_out; a.K = d_in + 1; a.P = P;
+        a.splits = last ? pl.splits : 1;
+        a.k_per_split = last ? pl.k_per_split : ((a.K + 63) / 64 * 64);
+        a.c_ss = (size_t)P * b * d_out;
+        return a;
+    };
+    auto forward_vec = [&](int l) { return mult4(dims[l]) && mult4(dims[l + 1]); };     // 128-bit loads need the element's alignment only
+    auto forward_form = [&](int l) { return l == L - 1 ? by_size : FORM_FP32; };
+
     // ---- Eq. (2); beside forward propagation when the second stream is in use ----
     // rho == 0: a local step.  Eq. (2) leaves the center as it is and Eq. (1) is a plain (momentum) SGD step, so
     // the center rule is not launched at all and the worker rule reads the center in place (times zero).
@@ -762,9 +786,8 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
         // chip (they then fill idle wave slots, no stream is involved); else the second stream when the rule has
         // enough to read to be worth the tens of microseconds that ordering two streams costs; else its own kernel.
         const long overlap = options().round_overlap;
-        const int splits0 = (L == 1) ? pl.splits : 1;
         const bool room = (head && L == 1) ? head_blocks(P, b) <= 3u * (unsigned)num_cus()
-                                           : forward_launch_has_room(b, dims[1], P, splits0);
+                                           : forward_launch_has_room(forward_args(0), forward_vec(0), forward_form(0));
         attach_center = (overlap == 3) || (overlap == 1 && room);
         if (!attach_center && (overlap == 2 || (overlap == 1 && (size_t)P * pl.N >= ((size_t)1 << 24)))) {
             lane_guard = std::unique_lock<std::mutex>(side_mutex);
@@ -800,20 +823,10 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
     // units pass their gradient on.  (The same product without the layers that follow, easgd_layer_product, takes
     // gemm_split.h: 3072->2048, 8 workers, 256 rows 210 us -> 142; the two of a 784-1024-1024-10 round, 16 workers, 128 rows, would gain 9 us of 213.)
     for (int l = 0; l < (head ? L - 1 : L); ++l) {
-        const int d_in = dims[l], d_out = dims[l + 1];
-        const bool last = (l == L - 1);
-        GemmArgs a = {};
-        a.A = act(l); a.a_ws = (size_t)b * d_in; a.lda = d_in; a.a_lim = d_in; a.a_ones = d_in;
-        a.B = W + pl.off[l]; a.b_ws = ld; a.ldb = d_out;
-        a.C = last ? logits : const_cast<float *>(act(l + 1)); a.c_ws = (size_t)b * d_out; a.ldc = d_out;
-        a.M = b; a.N = d_out; a.K = d_in + 1; a.P = P;
-        a.splits = last ? pl.splits : 1;
-        a.k_per_split = last ? pl.k_per_split : ((a.K + 63) / 64 * 64);
-        a.c_ss = (size_t)P * b * d_out;
+        GemmArgs a = forward_args(l);
         if (l == 0) a.ctr = center_job;
-        const bool vec = mult4(d_in) && mult4(d_out);       // 128-bit loads need the element's alignment only
-        if (last) launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, vec, s, by_size);
-        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, vec, s, FORM_FP32);
+        if (l == L - 1) launch_gemm<K_CONTIG, MN_CONTIG, EPI_NONE>(a, forward_vec(l), s, forward_form(l));
+        else launch_gemm<K_CONTIG, MN_CONTIG, EPI_RELU>(a, forward_vec(l), s, forward_form(l));
     }
     float *row_loss = reinterpret_cast<float *>(ws + pl.rowloss_off);
     const int rows = P * b;

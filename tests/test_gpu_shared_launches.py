@@ -55,3 +55,34 @@ def test_narrow_weight_gradients_share_a_launch(dims, P, b, tile):
     for a, c in zip(*outs):
         assert np.isfinite(a).all()
         np.testing.assert_array_equal(a, c)
+
+
+@pytest.mark.parametrize("dims,P,b,rides", [((3072, 593), 3, 124, True), ((2048, 1000), 16, 128, False)],
+                         ids=lambda v: str(v).replace(" ", ""))
+def test_center_rule_rides_on_wide_logits_where_their_tile_leaves_room(dims, P, b, rides):
+    """One layer and more than 32 classes: the first forward product is the logits, as split tiles.  420 blocks of 64x128 fill
+    three quarters of the chip's places for them, so the center rule is on extra blocks and not a launch of its own; 128x128
+    tiles fill all of theirs.  The same bits either way."""
+    import paper_1708_02983_amd as hip
+    N = workloads.mlp_num_params(dims)
+    rng = np.random.default_rng(12)
+    W = to_dev((rng.standard_normal((P, N)) * 0.03).astype(F))
+    Wc = to_dev(to_host(W)[0].copy())
+    X = to_dev(rng.random((P, b, dims[0])).astype(F))
+    y = to_dev(rng.integers(0, dims[-1], (P, b)).astype(np.int32))
+    old = hip.get_option(hip.OPT_ROUND_OVERLAP)
+    launches, outs = {}, []
+    try:
+        for overlap in (0, 1, 3):                   # a launch of its own; chosen; extra blocks
+            hip.set_option(hip.OPT_ROUND_OVERLAP, overlap)
+            rW, rWc, loss = W.clone(), Wc.clone(), torch.empty(P, device="cuda")
+            before = hip.launch_count()
+            hip.easgd_mlp_round(dims, rW, rWc, X, y, 0.05, 0.05, loss=loss)
+            launches[overlap] = hip.launch_count() - before
+            outs.append([to_host(rW), to_host(rWc), to_host(loss)])
+    finally:
+        hip.set_option(hip.OPT_ROUND_OVERLAP, old)
+    assert launches[3] == launches[0] - 1 and (launches[1] == launches[3]) == rides, launches
+    for res in outs[1:]:
+        for a, c in zip(outs[0], res):
+            np.testing.assert_array_equal(a, c)
