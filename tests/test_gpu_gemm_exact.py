@@ -4,8 +4,10 @@ the k sum, so the MFMA kernels must reproduce a plain triple loop BIT FOR BIT.  
 twice or read past its end, a wrong ones row (bias), a transposed operand or a tile written to the wrong place
 cannot hide under a rounding tolerance here.  Every operand-layout combination (forward: k-contiguous x
 n-contiguous; weight gradient: m-contiguous x n-contiguous; input gradient: k-contiguous x k-contiguous), every
-tile shape (the 16x16x4 tiles in all three heights, forced and chosen by default), K not a multiple of the slab depth, ragged M and N, the tile that holds the ones row, operands that
-rule out 128-bit loads, and enough workers for the die-aware block order."""
+tile shape forced and the default choice (split operands included: small integers are their own first part), K not a
+multiple of the slab depth, ragged M and N, the tile that holds the ones row, operands that rule out 128-bit loads,
+and enough workers for the die-aware block order.  The hidden layers' own choice among the fp32 tiles is reached
+through easgd_grad (last test)."""
 import numpy as np
 import pytest
 import torch
@@ -17,16 +19,17 @@ F = np.float32
 # (d_in, d_out, P, b): K = d_in + 1 (forward), b (weight gradient), d_out (input gradient)
 SHAPES = [
     (64, 64, 1, 32),        # one tile, one slab pair; the ones row starts a tile of its own in the weight gradient
-    (70, 50, 3, 37),        # nothing a multiple of 4: guarded scalar loaders
+    (70, 50, 3, 37),        # nothing a multiple of 4: 128-bit loads at any width (forward), guarded scalar loaders
     (128, 96, 2, 100),      # ragged batch against the 32-row MFMA tile
     (257, 130, 9, 64),      # K = 258: partial last slab for both slab depths; ragged N
     (100, 10, 5, 128),      # narrow output: the 128x32 tile
     (36, 32, 4, 44),        # N = 32 exactly
     (512, 256, 8, 128),     # >= 64 tiles: die-aware renumbering; several k slabs per block
     (300, 260, 16, 70),     # many workers, ragged everything, multiples of 4
-    (64, 2048, 32, 40),     # enough blocks for the 16-row MFMA tiles to be chosen by default: 48 rows for b = 40,
+    (64, 2048, 32, 40),     # enough blocks for the 16-row MFMA tiles in a network: 48 rows for b = 40,
     (60, 2048, 32, 72),     # 80 rows for b = 72,
     (64, 2048, 32, 100),    # 112 rows for b = 100
+    (61, 2047, 32, 100),    # the same with odd widths
 ]
 
 
@@ -118,3 +121,40 @@ def test_each_product_is_exact_on_integers(d_in, d_out, P, b, tile):
             np.testing.assert_array_equal(got[:, :width].astype(np.float64), ref.reshape(P, width), err_msg=what)
     finally:
         hip.set_option(hip.OPT_GEMM_TILE, old)
+
+
+# (d_in, hidden, P, b): what the forward product of the hidden layer takes by default
+HIDDEN = [
+    (64, 2048, 32, 40), (60, 2048, 32, 72), (64, 2048, 32, 100),       # 16-row tiles: 48, 80, 112 rows
+    (61, 2047, 32, 40), (67, 2046, 32, 72), (63, 2047, 32, 100),       # the same with loads at any width
+    (96, 2048, 32, 128), (97, 2047, 32, 128),                          # 128x128
+    (200, 300, 6, 70), (201, 301, 6, 70),                              # 64x64
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d_in,hidden,P,b", HIDDEN, ids=lambda v: str(v))
+def test_hidden_layers_default_forward_tiles_on_integers(d_in, hidden, P, b):
+    """easgd_grad of a d_in-hidden-16 network on integers with a last layer of zeros: all classes have probability 1/16, so
+    dZ = (1/16 - hot)/b whatever the hidden layer holds, and the last layer's weight gradient [H 1]^T dZ shows the hidden
+    activations H, which are exact integers.  One wrong unit of one row moves an element by 1/(16 b) = 6e-4 or more; the
+    rounding of the sums stays far below half of that."""
+    import paper_1708_02983_amd as hip
+    C = 16
+    rng = np.random.default_rng(d_in + hidden)
+    N = (d_in + 1) * hidden + (hidden + 1) * C
+    X = _ints(rng, (P, b, d_in), -1, 1)
+    W = np.zeros((P, N), dtype=F)
+    n0 = (d_in + 1) * hidden
+    W[:, :n0] = _ints(rng, (P, n0), -2, 2)
+    y = rng.integers(0, C, (P, b)).astype(np.int32)
+    G, loss = torch.full((P, N), float("nan"), device="cuda"), torch.empty(P, device="cuda")
+    hip.easgd_grad((d_in, hidden, C), to_dev(W), to_dev(X), to_dev(y), G, loss)
+    g = to_host(G)[:, n0:].reshape(P, hidden + 1, C).astype(np.float64)
+    H = _reference(0, X, W, None, d_in, hidden, True)
+    dz = (1.0 / C - np.eye(C)[y]) / b
+    one = np.concatenate([H, np.ones((P, b, 1))], axis=2).transpose(0, 2, 1)
+    ref, mag = one @ dz, np.abs(one) @ np.abs(dz)
+    bound = (b + 8) * 2.0 ** -24 * mag                     # b additions; dZ itself is rounded once
+    assert bound.max() < 0.5 / (C * b)
+    assert (np.abs(g - ref) <= bound).all()

@@ -10,6 +10,7 @@ from gpu_util import to_dev, to_host
 pytestmark = pytest.mark.gpu
 F = np.float32
 
+# Short sums: what split_pick and split_dw_pays leave to the fp32 instruction is held to the same bound.
 # (d_in, d_out, P, b): the 128x128, 64x128, 64x64, 32x128 and 32x32 tiles of 256 compute units, rows, columns and sums one
 # below, at and one above a tile, a step (16) or a slab (32, 64); one row, one column of a tile, a sum of one
 SHAPES = [
@@ -26,7 +27,8 @@ def _operands(d_in, d_out, P, b, seed=7):
     rng = np.random.default_rng(seed)
     block = (d_in + 1) * d_out
     ld = block + (3 if d_in % 2 else 0)                                   # rows that start at any element
-    # a wide range of magnitudes, so that a part that is dropped or put to the wrong place shows in some element
+    # a wide range of magnitudes, so that in a short sum a part that is dropped or put to the wrong place shows in some
+    # element (in a long one it does not: see test_long_sums_keep_every_part_of_either_operand)
     A = (rng.standard_normal((P, b, d_in)) * np.exp2(rng.integers(-6, 7, (P, b, d_in)))).astype(F)
     W = (rng.standard_normal((P, ld)) * np.exp2(rng.integers(-6, 7, (P, ld)))).astype(F)
     Z = (rng.standard_normal((P, b, d_out)) * 1e-3).astype(F)
@@ -87,6 +89,58 @@ def test_infinities_and_nan_give_what_fp32_products_give(d_in, d_out, P, b):
     inf = np.isinf(ref)
     np.testing.assert_array_equal(got[inf], ref[inf].astype(F))
     assert np.isfinite(got[np.isfinite(ref)]).all()
+
+
+# Sums of many slabs, so that the loop over whole slabs runs with the products whose loads were issued two slabs before: even
+# and odd numbers of slabs, last slabs of every kind, all tiles (of 256 compute units) in forward and input-gradient form.
+LONG_SHAPES = [
+    (300, 2048, 16, 100), (351, 2048, 16, 128), (2048, 299, 16, 100), (2048, 416, 16, 90),   # 128x128: 10, 11; 10, 13 slabs
+    (500, 2048, 16, 64), (1024, 300, 16, 128), (1024, 415, 16, 100),                         # 64x128
+    (415, 768, 12, 192), (768, 333, 12, 150),                                                # 64x64
+    (415, 2048, 17, 32), (2048, 300, 16, 20),                                                # 32x128
+    (700, 97, 5, 65), (97, 700, 5, 65),                                                      # 32x32
+]
+
+
+def _three_parts(rng, shape):
+    """24-bit numbers of either sign, all three bfloat16 parts of which are needed."""
+    bits = rng.integers(1 << 23, 1 << 24, shape) | 1
+    return (bits * rng.choice((-1.0, 1.0), shape) * 2.0 ** -23).astype(F)
+
+
+@pytest.mark.parametrize("d_in,d_out,P,b", LONG_SHAPES, ids=lambda v: str(v))
+def test_long_sums_keep_every_part_of_either_operand(d_in, d_out, P, b):
+    """One nonzero 24-bit number per row of one operand, powers of two in the other: every result is one product and exact, so
+    a part that is dropped, put to another place or multiplied by another slab's shows whatever the length of the sum.  Then
+    ordinary operands against 64 bits."""
+    import paper_1708_02983_amd as hip
+    rng = np.random.default_rng(d_in + d_out)
+    block = (d_in + 1) * d_out
+    ld = block + (3 if d_in % 2 else 0)
+    for kind in (0, 1, 2):
+        for sparse_first in (True, False):
+            # x (P, M, K) and y (P, K, N) of the product; the bias row of the weights stays zero
+            M, K, n = {0: (b, d_in, d_out), 1: (d_in, b, d_out), 2: (b, d_out, d_in)}[kind]
+            x, y = np.exp2(rng.integers(-3, 4, (P, M, K))).astype(F), np.exp2(rng.integers(-3, 4, (P, K, n))).astype(F)
+            thin = np.zeros((P, M if sparse_first else n, K), dtype=F)
+            at = (np.arange(thin.shape[1])[None, :] * 7 + np.arange(P)[:, None] * 5) % K
+            np.put_along_axis(thin, at[:, :, None], _three_parts(rng, at.shape)[:, :, None], axis=2)
+            if sparse_first: x = thin
+            else: y = thin.transpose(0, 2, 1).copy()
+            W = np.zeros((P, ld), dtype=F)
+            A, Z = np.ones((P, b, d_in), dtype=F), np.zeros((P, b, d_out), dtype=F)
+            if kind == 0: A, w = x, y
+            elif kind == 1: A, Z, w = x.transpose(0, 2, 1).copy(), y, None
+            else: Z, w = x, y.transpose(0, 2, 1)
+            if w is not None: W[:, :d_in * d_out] = w.reshape(P, -1)
+            ref, _, _ = _products(kind, A, W, Z, d_in, d_out)
+            got = _run(hip, kind, A, W, Z, d_in, d_out, ld, ref[0].size).reshape(ref.shape)
+            if kind == 1: got, ref = got[:, :d_in], ref[:, :d_in]         # (the bias row is a sum of many)
+            np.testing.assert_array_equal(got, ref.astype(F), err_msg="kind %d sparse %s" % (kind, sparse_first))
+        A, W, Z, _ = _operands(d_in, d_out, P, b)
+        ref, mag, K = _products(kind, A, W, Z, d_in, d_out)
+        got = _run(hip, kind, A, W, Z, d_in, d_out, W.shape[1], ref[0].size).reshape(ref.shape)
+        assert (np.abs(got - ref) <= (K + 8) * 2.0 ** -24 * mag).all(), kind
 
 
 RANGE_SHAPES = [(300, 2048, 16, 70), (2048, 100, 17, 40), (65, 34, 2, 17), (127, 128, 40, 31)]
