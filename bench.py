@@ -370,9 +370,9 @@ TRAFFIC_PROFILES = {
                                              "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
     ("elastic_bf16", True, 16, 61_000_000): (3_931_723.6 * 1024 * 2.000 + 5_957_033.5 * 1024 * 1.000,
                                              "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
-    ("grad", "cfg2"): (131_412.3 * 1024 * 2.000 + 149_337.0 * 1024 * 1.000, "profiles/easgd_grad_cfg2_hbm_traffic.md"),
+    ("grad", "cfg2"): (131_409.1 * 1024 * 2.000 + 149_337.0 * 1024 * 1.000, "profiles/easgd_grad_cfg2_hbm_traffic.md"),
 }
-TRAFFIC_PROFILED_VERSION = 510      # easgd_version() of the library the summaries above were taken with
+TRAFFIC_PROFILED_VERSION = 511      # easgd_version() of the library the summaries above were taken with
 
 
 def traffic_fields(hip, key):
@@ -533,7 +533,10 @@ def mfma_ceilings(hip, iters=2000, reps=5):
 def mfma_roofline(hip, kernel, traffic_key, flops, ms):
     tflops = flops / (ms * 1e-3) / 1e12
     out = {"bound": "mfma", "kernel": kernel, "achieved": round(tflops, 2), "peak": MFMA_FP32_PEAK_TFLOPS,
-           "unit": "TFLOP/s", "frac": round(tflops / MFMA_FP32_PEAK_TFLOPS, 4), **traffic_fields(hip, traffic_key),
+           "unit": "TFLOP/s", "frac": round(tflops / MFMA_FP32_PEAK_TFLOPS, 4),
+           "peak_of": "fp32 matrix instruction; part of the products run on the bfloat16 matrix cores (split operands), so "
+                      "frac compares rates of fp32 work and is no utilisation",
+           **traffic_fields(hip, traffic_key),
            "useful_flops_per_launch": flops, "avg_launch_ms": round(ms, 4)}
     if MFMA_CEILINGS:
         out["measured_mfma_loop_TFLOPs"] = round(MFMA_CEILINGS["registers"], 1)

@@ -336,8 +336,9 @@ int easgd_mlp_round_bf16v(const int *dims, int n_layers,
 
 /*
  * One matrix product of forward / backward propagation (Section 2.2) alone, for all P workers, through the
- * tile selection and the MFMA kernels that easgd_grad uses for it, except that kind 0 takes the split form (see the
- * conventions), which the hidden layers of a network do not, unless EASGD_OPT_GEMM_TILE forces a tile (a testing aid:
+ * tile selection and the MFMA kernels that easgd_grad uses for it, except that kind 0 may take the split form (see the
+ * conventions), which the hidden layers of a network do not, unless EASGD_OPT_GEMM_TILE forces a tile, and that a network whose
+ * replicas hold 2^26 parameters or more keeps the fp32 instruction in every product (a testing aid:
  * integer-valued operands make every product and partial sum exact in fp32, so the result can be checked bit for bit).
  * For one layer with d_in inputs and d_out outputs, [W ; b] its packed (d_in+1) x d_out block:
  *
@@ -377,7 +378,7 @@ typedef enum {
     EASGD_OPT_GEMM_TILE            = 4,  /* block tile of the wide matrix products of easgd_grad: 0 = chosen per product (default),
                                             split operands (see the conventions) included; the others force the fp32 instruction:
                                             1 = 128x128, 2 = 64x64, 3 = 128x64, 4 = 48, 80 or 112 rows by 128 columns in 16x16x4 matrix
-                                            instructions for the products whose rows are the minibatch (chosen by default when
+                                            instructions for the products whose rows are the minibatch (chosen by default for those that keep the fp32 instruction when
                                             one of these heights covers b with fewer rows than b rounded up to 32, e.g. b = 100) */
     EASGD_OPT_ROUND_OVERLAP        = 5,  /* easgd_mlp_round, where the center rule runs: 0 = a kernel of its own on the caller's
                                             stream; 2 = the same on a second stream of the library, beside forward propagation;

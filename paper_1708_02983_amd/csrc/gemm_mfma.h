@@ -37,8 +37,8 @@ enum { EPI_NONE = 0, EPI_RELU = 1, EPI_MASK = 2, EPI_ELASTIC = 3, EPI_ELASTIC_MO
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// The mean losses, on extra blocks at the end of a weight-gradient launch (blocks == 0: none): as a kernel of its own it
-// is a launch boundary of some 4 us in a round that may take 12.
+// The mean losses, on extra blocks at the end of a weight-gradient launch (blocks == 0: none): as a kernel of its own they
+// took 1.7 us of a round of 784-10, 4 workers, 64 rows (14.8 us -> 13.1 without).
 struct LossJob {
     const float *row_loss;              // [P][b]
     float *loss;                        // [P]
