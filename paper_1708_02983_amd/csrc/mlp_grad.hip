@@ -307,6 +307,7 @@ static bool split_fits(const GemmArgs &a, bool a_k_contig, bool b_k_contig)
 //                              forward                    input gradient, 128-bit loads
 //   128x128  2048, 24, 128     0.90 1.02 1.19 1.22        0.94 1.16 1.27 1.24
 //   128x128  1024, 32, 128     0.76 0.88 1.06 1.25        0.80 0.93 1.11 1.29
+//   128x128  2048, 20,  80     0.86 0.94 1.08 1.18        0.92 1.05 1.12 1.20     (input gradient 2066, 22, 74, a sum of 92: 18.2 us / 16.9)
 //   64x128   1024, 16, 128     0.74 0.82 0.91 1.05        0.80 0.87 1.00 1.12
 //   64x128   2048, 32,  64     1.26 1.49 1.79 1.98        0.92 1.06 1.19 1.11
 //   64x64     768, 12, 192     0.73 0.83 0.94 1.06        0.81 0.87 1.00 1.10
@@ -335,7 +336,8 @@ static SplitPick split_pick(const GemmArgs &a, bool forward, bool vec, bool any_
     int least;                                               // shortest sum
     if (a.M > 64 && blocks(128, 128) >= cus) {
         pick = SPLIT_128x128;
-        least = 2 * blocks(128, 128) >= 3 * cus ? (forward ? 128 : 112) : (forward ? 192 : 160);
+        const size_t n = blocks(128, 128);
+        least = forward ? (2 * n >= 3 * cus ? 128 : 192) : (4 * n >= 5 * cus ? 72 : 160);
     } else if (a.M > 32 && blocks(64, 128) >= cus) {
         pick = SPLIT_64x128;
         least = blocks(64, 128) >= 2 * cus ? (forward ? 0 : 96) : (forward ? 384 : 256);
@@ -390,10 +392,12 @@ static bool split_dw_fits(const GemmArgs &a, bool vec)
 // instruction over that of the split form at 24, 32, 50, 64, 100, 128 rows (layer, workers), no worker rule:
 //   1024->1024, 16   1.08 1.16 1.00 1.14 1.16 1.29
 //   2048->2048,  2   0.97 1.03 0.92 1.04 1.07 1.21
+//   1944-> 648,  8   at 135 rows, five slabs and eleven of twelve half tiles: 1.14
 //   1024-> 160, 32   0.77 0.89 0.79 0.91 0.88 0.99
 //   1024->  48, 32   0.64 0.74 0.67 0.73 0.71 0.83
 // With the worker rule in the epilogue both move the replicas as well and there is less to gain; us a round gained or lost
-// (784-1024-10, 16 workers: -0.5 -1.4 +3.7 +2.7 +1.9 -1.8; 3072-2048-10, 8: -3.5 -0.0 +7.2 +4.4 +0.4 -16.4).
+// (784-1024-10, 16 workers: -0.5 -1.4 +3.7 +2.7 +1.9 -1.8; 3072-2048-10, 8: -3.5 -0.0 +7.2 +4.4 +0.4 -16.4; 3072-600, 32, with
+// momentum: -20 at 100 rows).
 // Without 128-bit loads (no worker rule):
 //   1023->1022, 16   1.16 1.32 1.37 1.57 1.68 1.99   (with the rule, at 40 rows: +2.2 us of 70)
 //    783->1024,  4   0.98 1.12 1.16 1.40 1.47 1.80   (416 blocks)
@@ -408,19 +412,20 @@ static bool split_dw_pays(const GemmArgs &a, bool vec)
         if (a.K > 32 && a.K <= 96) return false;
         const long columns = (a.N + 127) / 128 * 2, needed = (a.N + 63) / 64;        // in tiles of 64
         const long multiplied = (a.K + 31) / 32 * 32 * columns, useful = a.K * needed;
-        return 100 * multiplied <= (a.K > 96 ? 114 : 134) * useful;
+        return 100 * multiplied <= (a.K > 96 ? 130 : 134) * useful;
     }
     if (a.N <= 64 || 2 * blocks < cus) return a.K >= 120;
-    if (blocks >= 2 * cus) return a.K >= 20 && !(a.K > 32 && a.K < 45);
-    return a.K >= (2 * blocks >= 3 * cus ? 44 : 64);
+    if (blocks >= 2 * cus) return a.K >= 20 && !(a.K > 32 && a.K < 42);
+    return a.K >= (4 * blocks >= 5 * cus ? 44 : 54);
 }
 
 // In which form two weight gradients that follow one another are computed, so that they can share a launch; or each in the form
-// that pays for it, in a launch of its own.  Where both forms can take both, the form that pays for the larger one.  Where
-// only the fp32 form can take both, that one, up to the size at which the split form's gain on one of them makes up for a
-// launch (rounds of 3072-512-256-10, 128 rows, one launch / two: 4 workers 119.9 / 128.2 us, 8 140.9 / 145.8, 16
-// 184.6 / 181.7; 3072-768-128-10, 16: 265.5 / 256.3).  Where only the split form can take both, that one (gradient of
-// 1390-126-205-10, 7, 56: 59.6 us against 65.5 in two launches).  EASGD_OPT_GEMM_PAIR has no say: it changes no bit.
+// that pays for it, in a launch of its own.  Where both forms can take both, the split form if it pays for two fifths of the
+// work (gradient of 628-1888-816-10, 6, 103: 136 us against 142).  Where only the fp32 form can take both, that one, up to the
+// size at which the split form's gain on one of them makes up for a launch (rounds of 3072-512-256-10, 128 rows, one
+// launch / two: 4 workers 119.9 / 128.2 us, 8 140.9 / 145.8, 16 184.6 / 181.7; 3072-768-128-10, 16: 265.5 / 256.3).  Where only
+// the split form can take both, that one (gradient of 1390-126-205-10, 7, 56: 59.6 us against 65.5 in two launches).
+// EASGD_OPT_GEMM_PAIR has no say: it changes no bit.
 enum Form { FORM_BY_SIZE, FORM_FP32, FORM_SPLIT };
 
 static Form dw_pair_form(const GemmArgs &a0, bool vec0, const GemmArgs &a1, bool vec1, bool fp32_only)
@@ -432,7 +437,7 @@ static Form dw_pair_form(const GemmArgs &a0, bool vec0, const GemmArgs &a1, bool
     if (!fp32 || fp32_only) return split ? FORM_SPLIT : fp32 ? FORM_FP32 : FORM_BY_SIZE;
     const bool pays0 = split_dw_pays(a0, vec0), pays1 = split_dw_pays(a1, vec1);
     const double size0 = (double)a0.M * a0.N, size1 = (double)a1.M * a1.N;
-    if (split) return (size0 > size1 ? pays0 : pays1) ? FORM_SPLIT : FORM_FP32;
+    if (split) return (pays0 ? size0 : 0) + (pays1 ? size1 : 0) >= 0.4 * (size0 + size1) ? FORM_SPLIT : FORM_FP32;
     const double gain = (pays0 ? size0 * a0.K * a0.P : 0) + (pays1 ? size1 * a1.K * a1.P : 0);
     return gain >= 3.0e9 ? FORM_BY_SIZE : FORM_FP32;
 }
@@ -524,8 +529,10 @@ static inline bool mult4(size_t x) { return (x & 3u) == 0; }
 
 // Whether the launch of a forward product leaves room on the chip for extra blocks that do bandwidth-bound work beside it.
 // Mirrors launch_gemm: the 128x32 and 64x64 tiles use few enough registers and LDS for four blocks per compute unit, the
-// 128x128 tile for two, and it is chosen exactly when its blocks already fill those; the split tiles of 32, 64 and 128 rows
-// four, three and two (split_blocks_per_cu).
+// 128x128 tile for two, and it is chosen exactly when its blocks already fill those; the split tiles of 64 and 128 rows three
+// and two (split_blocks_per_cu).  The 32-row ones leave room whatever their number (rounds with the rule on extra blocks /
+// as a launch of its own: 3072-99, 17, 30, 952 blocks 47.0 / 52.3 us; 3072-400, 32, 32, 2048 blocks 158 / 165; 2000-500, 16, 32,
+// 1024 blocks 91 / 95); 64x128: 3072-593, 3, 124, 420 blocks 79 / 84; 128x128 more than one per unit: 512-1000, 32, 200 198 / 191.
 static bool forward_launch_has_room(const GemmArgs &a, bool vec, Form form)
 {
     const size_t cus = (size_t)num_cus();
@@ -535,8 +542,8 @@ static bool forward_launch_has_room(const GemmArgs &a, bool vec, Form form)
     case SPLIT_128x128: return blocks(128, 128) <= cus;
     case SPLIT_64x128: return blocks(64, 128) <= 2 * cus;
     case SPLIT_64x64: return blocks(64, 64) <= 2 * cus;
-    case SPLIT_32x128: return blocks(32, 128) <= 3 * cus;
-    case SPLIT_32x32: return blocks(32, 32) <= 3 * cus;
+    case SPLIT_32x128:
+    case SPLIT_32x32: return true;
     case SPLIT_NONE: break;
     }
     long tile = options().gemm_tile;
