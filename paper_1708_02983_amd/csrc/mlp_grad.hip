@@ -20,6 +20,7 @@
 // kernel of its own), the input-gradient product of a layer runs before its
 // weight-gradient product, and that product applies the worker rule Eq. (1) /
 // Eq. (5),(6) to the layer's slice of every replica in its epilogue.
+#include "gemm_chain.h"
 #include "gemm_split.h"
 #include "mlp_head.h"
 #include "persistent_round.h"
@@ -363,6 +364,60 @@ static SplitPick split_pick(const GemmArgs &a, bool forward, bool vec, bool any_
     return any_length || std::min(a.K, a.k_per_split) >= least ? pick : SPLIT_NONE;
 }
 
+// ---- fp32 products of small grids (gemm_chain.h) ----
+
+// Which tile of gemm_chain.h takes the place of the fp32 instruction's 64x64 tile: rows x columns, or none.
+enum ChainPick { CHAIN_NONE, CHAIN_32x32, CHAIN_16x64, CHAIN_32x64 };
+
+// All of them give the same bits, so only time counts: a launch takes a + r (c + d K) us, where r is the number of blocks per
+// compute unit, rounded up.  The constants are fitted to 150 products of forward and backward propagation of up to 640 64x64
+// tiles, sums of 48 to 3072 (each tile's time met to 6 %; the tile that is picked is never slower than the 64x64 tile and
+// at most 7 % slower than the best one).  us, 64x64 / 32x32 / 16x64 / 32x64 (64x32 is almost never the best):
+//   forward         784-> 500,  8 workers,  50 rows     18.2 /  8.7 /  9.3 / 11.9
+//                  1023-> 777,  6,  37                  23.2 / 14.3 / 10.4 / 14.1
+//                   784->1520,  4,  64                  18.3 / 13.4 / 14.6 / 12.3
+//                  3072-> 427,  7,  38                  59.5 / 20.3 / 21.0 / 33.7
+//                   784-> 640, 12, 100                  18.5 / 22.7 / 25.3 / 21.1    (stays)
+//   input gradient   95-> 222,  6, 132                  12.9 /  4.4 /  4.8 /  5.9    (no 128-bit loads for 64x64)
+//                  1024-> 100, 32,  64                   9.4 / 14.5 / 18.1 / 13.9    (stays)
+static ChainPick chain_pick(const GemmArgs &a, bool forward, bool vec)
+{
+    if (options().gemm_tile != 0 || a.N <= 32 || !split_fits(a, true, !forward)) return CHAIN_NONE;
+    const size_t cus = (size_t)num_cus();
+    auto blocks = [&](int bm, int bn) { return (size_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * (size_t)a.P * (size_t)a.splits; };
+    if (2 * blocks(64, 64) > 5 * cus) return CHAIN_NONE;
+    const double K = std::min(a.K, a.k_per_split);
+    auto time = [&](int bm, int bn, double start, double per_round, double per_k) {
+        return start + (double)((blocks(bm, bn) + cus - 1) / cus) * (per_round + per_k * K);
+    };
+    // input gradients that rule out 128-bit loads on the 64x64 path take about twice as long there
+    double best = time(64, 64, 2.33, 0.66, 0.0190) * (!forward && !vec ? 2 : 1);
+    ChainPick pick = CHAIN_NONE;
+    auto consider = [&](ChainPick t, double us) {
+        if (us < best) {
+            best = us;
+            pick = t;
+        }
+    };
+    consider(CHAIN_32x32, time(32, 32, 3.02, 0.21, 0.00525));
+    consider(CHAIN_16x64, time(16, 64, 3.06, 0.30, 0.00610));
+    consider(CHAIN_32x64, time(32, 64, 3.04, 0.47, 0.00936));
+    return pick;
+}
+
+template <int WM, int WN, int TM, int BL, int EPI>
+static void launch_chain(const GemmArgs &a_in, hipStream_t s)
+{
+    typedef ChainTile<WM, WN, TM, BL> T;
+    GemmArgs a = a_in;
+    size_t total = place_blocks<T::BM, T::BN>(a);
+    if (a.ctr.blocks > 0) {
+        a.ctr.first_block = (unsigned)total;
+        total += a.ctr.blocks;
+    }
+    EASGD_LAUNCH((gemm_chain_kernel<WM, WN, TM, BL, EPI>), dim3((unsigned)total), dim3(256), 0, s, a);
+}
+
 template <int TM, int WN, int WK, int AL, int BL, int EPI>
 static void launch_split(const GemmArgs &a_in, hipStream_t s)
 {
@@ -513,6 +568,11 @@ static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, Form form = 
         else if (bm16 == 80) launch_tile<80, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
         else if (bm16 == 48) launch_tile<48, 128, 32, 1, 4, AL, BL, EPI, 16>(a, vec, s);
         if (bm16) return;
+        const ChainPick chain = chain_pick(a, forward, vec);
+        if (chain == CHAIN_32x32) launch_chain<2, 2, 1, BL, EPI>(a, s);
+        else if (chain == CHAIN_16x64) launch_chain<1, 4, 1, BL, EPI>(a, s);
+        else if (chain == CHAIN_32x64) launch_chain<1, 4, 2, BL, EPI>(a, s);
+        if (chain != CHAIN_NONE) return;
     } else if (form == FORM_SPLIT ? split_dw_fits(a, vec) : form == FORM_BY_SIZE && split_dw_pays(a, vec)) {
         launch_split<2, 4, 1, AL, BL, EPI>(a, s);
         return;

@@ -1,0 +1,101 @@
+"""Products of small grids in 16x16 tiles of the fp32 matrix instruction: an element is a chain of fused multiply-adds in
+ascending k whatever tile it is computed in, so every tile gives the bits of the 64x64 one (EASGD_OPT_GEMM_TILE 2).  Sizes one
+below, at and above a tile, a slab (64 values of k) and the pipeline's first slabs; rows that start at any element."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from gpu_util import to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+F = np.float32
+
+
+def _with_tile(hip, tile, f):
+    old = hip.get_option(hip.OPT_GEMM_TILE)
+    hip.set_option(hip.OPT_GEMM_TILE, tile)
+    try:
+        return f()
+    finally:
+        hip.set_option(hip.OPT_GEMM_TILE, old)
+
+
+# (dims, P, b): the tiles that 256 compute units take for the hidden layers
+NETWORKS = [
+    ((63, 33, 10), 2, 1), ((64, 48, 10), 3, 15), ((65, 65, 10), 2, 16),           # 32x32; sums of 64, 65, 66
+    ((784, 500, 300, 10), 8, 50), ((255, 34, 257, 12), 5, 33), ((511, 130, 3), 4, 65),
+    ((1023, 777, 333, 7), 6, 37), ((300, 1009, 10), 5, 48), ((129, 1000, 16), 5, 17),   # 16x64
+    ((156, 1041, 10), 13, 17), ((129, 1520, 10), 4, 63), ((256, 513, 10), 7, 65),       # 32x64
+    ((784, 640, 10), 12, 100),                                                          # the 64x64 tile itself
+]
+
+
+@pytest.mark.parametrize("dims,P,b", NETWORKS, ids=lambda v: str(v))
+def test_hidden_layers_keep_the_bits_of_the_64x64_tile(dims, P, b):
+    """The last layer's weight gradient [H 1]^T dZ takes the same kernel for either option and depends on every hidden unit."""
+    import paper_1708_02983_amd as hip
+    rng = np.random.default_rng(sum(dims) + b)
+    N = workloads.mlp_num_params(dims)
+    W = (rng.standard_normal((P, N)) * np.sqrt(2.0 / dims[0])).astype(F)
+    X = rng.random((P, b, dims[0]), dtype=F)
+    y = to_dev(rng.integers(0, dims[-1], (P, b)).astype(np.int32))
+    last = (dims[-2] + 1) * dims[-1]
+    dW, dX = to_dev(W), to_dev(X)
+
+    def grad():
+        G, loss = torch.full((P, N), float("nan"), device="cuda"), torch.empty(P, device="cuda")
+        hip.easgd_grad(dims, dW, dX, y, G, loss)
+        return to_host(G)[:, N - last:], to_host(loss)
+
+    g, loss = _with_tile(hip, 0, grad)
+    g2, loss2 = _with_tile(hip, 2, grad)
+    np.testing.assert_array_equal(loss, loss2)
+    np.testing.assert_array_equal(g, g2)
+    assert np.isfinite(g).all() and (g != 0).any()
+
+
+# (d_in, d_out, P, b): sums too short for the split form; 32x32, 16x64, 32x64 and the 64x64 tile itself
+INPUT_GRADIENTS = [(47, 2, 3, 1), (64, 31, 2, 16), (97, 36, 4, 33), (300, 64, 3, 37), (641, 68, 6, 37),
+                   (321, 63, 24, 1), (321, 64, 24, 17), (353, 100, 23, 17), (1024, 48, 16, 128)]
+
+
+@pytest.mark.parametrize("d_in,d_out,P,b", INPUT_GRADIENTS, ids=lambda v: str(v))
+def test_short_sums_of_input_gradients_keep_the_bits_of_the_64x64_tile(d_in, d_out, P, b):
+    import paper_1708_02983_amd as hip
+    rng = np.random.default_rng(d_in + d_out + b)
+    ld = (d_in + 1) * d_out + 3
+    A, W, Z = (to_dev(rng.standard_normal(s).astype(F)) for s in ((P, b, d_in), (P, ld), (P, b, d_out)))
+
+    def product():
+        out = torch.full((P, b * d_in + 5), float("nan"), device="cuda")
+        hip.easgd_layer_product(2, d_in, d_out, A, out, Wl=W, dZ=Z, ld=ld, out_ws=b * d_in + 5)
+        return to_host(out)
+
+    got, ref = _with_tile(hip, 0, product), _with_tile(hip, 2, product)
+    assert np.isnan(got[:, b * d_in:]).all()
+    gate = to_host(A).reshape(P, -1) > 0
+    exact = (to_host(Z).astype(np.float64) @ to_host(W)[:, :d_in * d_out].reshape(P, d_in, d_out).astype(np.float64).transpose(0, 2, 1)).reshape(P, -1)
+    mag = (np.abs(to_host(Z)).astype(np.float64) @ np.abs(to_host(W))[:, :d_in * d_out].reshape(P, d_in, d_out).astype(np.float64).transpose(0, 2, 1)).reshape(P, -1)
+    # at most d_out additions, each off by half an ulp of a partial sum
+    assert (np.abs(got[:, :b * d_in] - np.where(gate, exact, 0.0)) <= (d_out + 8) * 2.0 ** -24 * mag).all()
+    if d_out % 4 == 0 or d_out < 40:            # the split form starts at sums of 40 where a width rules out 128-bit loads
+        np.testing.assert_array_equal(got[:, :b * d_in], ref[:, :b * d_in])
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_what_lies_behind_a_row_does_not_reach_a_sum(bad):
+    """A 128-bit load at the end of a row brings the values behind it, and the last slab of a sum those of the next layer: none of
+    them may meet a zero in a product (0 * inf is NaN)."""
+    import paper_1708_02983_amd as hip
+    d_in, d_out, P, b = 65, 50, 3, 17
+    rng = np.random.default_rng(3)
+    A, Z = rng.standard_normal((P, b, d_in)).astype(F), rng.standard_normal((P, b, d_out)).astype(F)
+    block = (d_in + 1) * d_out
+    W = np.full((P, block + 70 * d_out), bad, dtype=F)
+    W[:, :block] = rng.standard_normal((P, block))
+    dA, dW, dZ = to_dev(A), to_dev(W), to_dev(Z)
+    for kind, width in ((0, d_out), (2, d_in)):
+        out = torch.empty((P, b * width), device="cuda")
+        hip.easgd_layer_product(kind, d_in, d_out, dA, out, Wl=dW, dZ=dZ, ld=W.shape[1], out_ws=b * width)
+        assert np.isfinite(to_host(out)).all(), kind
