@@ -459,6 +459,81 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
     };
     auto nothing = [] {};
 
+    // A whole slab: the one in buffer `buf` is multiplied, the slab behind it goes from the registers (sa, sb) to the other buffer
+    // and, with LOADS, the one at k0 is requested into (ra, rb).  Every memory instruction has its place behind a matrix instruction
+    // of its own: a wavefront issues in order, so that in a burst (all loads, then half of the matrix instructions, then
+    // all LDS stores) the ones at the end wait for LDS and hold back the matrix instructions behind them.  Burst / spread, us:
+    // forward 784->1024, 16 workers, 128 rows, 64x64 tiles 31.0 / 28.7; 3072->2048, 32, 100, 112x128 tiles 365 / 323;
+    // 3072->2048, 8, 256, 128x128 tiles 203 / 188; input gradient 1024->1024, 16, 128 38.6 / 35.7.
+    auto spread_slab = [&](int buf, auto loads, int k0, f32x4 (&ra)[IT_A], f32x4 (&rb)[IT_B], const f32x4 (&sa)[IT_A], const f32x4 (&sb)[IT_B], auto clamp) {
+        constexpr bool CLAMP = decltype(clamp)::value, LOADS = decltype(loads)::value;
+        constexpr int STEPS = BK / KSTEP, MM = TM * TN, SLOTS = STEPS * MM, READS = TM + TN, DIST = (MM == 1) ? 2 : 1;
+        // the loads go out over the first half of the slab, the LDS stores (four per k-contiguous chunk, one per other chunk) over
+        // the second
+        constexpr int OA = A_LAYOUT == K_CONTIG ? 4 : 1, OB = B_LAYOUT == K_CONTIG ? 4 : 1, STORES = OA * IT_A + OB * IT_B;
+        constexpr int FIRST = SLOTS / 2;
+        const float *as = &As[buf][frag_k * PITCH_A + wm0 + frag_x], *bs = &Bs[buf][frag_k * PITCH_B + wn0 + frag_x];
+        float a[DIST + 1][TM], b[DIST + 1][TN];
+        auto fetch = [&](int st, int r) {
+            const int kk = (MT == 32) ? 2 * st : st;
+            if (r < TN) b[st % (DIST + 1)][r] = bs[kk * PITCH_B + r * MT];
+            else a[st % (DIST + 1)][r - TN] = as[kk * PITCH_A + (r - TN) * MT];
+        };
+        auto store = [&](int o) {
+            const int it = o < OA * IT_A ? o / OA : (o - OA * IT_A) / OB;
+            if (o < OA * IT_A) {
+                if (CHUNKS_A % NTHREADS != 0 && tid + it * NTHREADS >= CHUNKS_A) return;
+                if (A_LAYOUT == K_CONTIG) {
+                    As[buf ^ 1][a_dst[it] + (o % 4) * PITCH_A] = (CLAMP && !a_ok[it]) ? 0.f : sa[it][o % 4];
+                } else {
+                    f32x4 v = sa[it];
+                    if (CLAMP && !a_ok[it]) {
+                        const int m_chunk = m0 + 4 * ((tid + it * NTHREADS) % (BM / 4));
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] = (m_chunk + q == p.a_ones) ? 1.f : 0.f;
+                    }
+                    *reinterpret_cast<f32x4 *>(&As[buf ^ 1][a_dst[it]]) = v;
+                }
+            } else {
+                if (CHUNKS_B % NTHREADS != 0 && tid + it * NTHREADS >= CHUNKS_B) return;
+                if (B_LAYOUT == K_CONTIG) Bs[buf ^ 1][b_dst[it] + (o - OA * IT_A) % 4 * PITCH_B] = (CLAMP && !b_ok[it]) ? 0.f : sb[it][(o - OA * IT_A) % 4];
+                else *reinterpret_cast<f32x4 *>(&Bs[buf ^ 1][b_dst[it]]) = (CLAMP && !b_ok[it]) ? f32x4{0.f, 0.f, 0.f, 0.f} : sb[it];
+            }
+        };
+        auto load = [&](int it) {
+            if (it < IT_A) {
+                if (CHUNKS_A % NTHREADS == 0 || tid + it * NTHREADS < CHUNKS_A) ra[it] = load4(a_src[it] + (size_t)k0 * a_kstep);
+            } else {
+                if (CHUNKS_B % NTHREADS == 0 || tid + (it - IT_A) * NTHREADS < CHUNKS_B) rb[it - IT_A] = load4(b_src[it - IT_A] + (size_t)k0 * b_kstep);
+            }
+        };
+#pragma unroll
+        for (int d = 0; d < DIST; ++d)
+#pragma unroll
+            for (int r = 0; r < READS; ++r) fetch(d, r);
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+#pragma unroll
+            for (int u = 0; u < MM; ++u) {
+                const int slot = st * MM + u, i = u / TN, j = u % TN;
+#pragma unroll
+                for (int r = 0; r < READS; ++r)
+                    if (r * MM / READS == u && st + DIST < STEPS) fetch(st + DIST, r);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (MT == 32) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[st % (DIST + 1)][i], b[st % (DIST + 1)][j], acc[i][j], 0, 0, 0);
+                else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[st % (DIST + 1)][i], b[st % (DIST + 1)][j], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int it = 0; it < IT_A + IT_B; ++it)
+                    if (LOADS && slot == it * FIRST / (IT_A + IT_B)) load(it);
+#pragma unroll
+                for (int o = 0; o < STORES; ++o)
+                    if (slot == FIRST + o * (SLOTS - FIRST - 1) / STORES) store(o);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
     // All slabs of a block go through the 128-bit pipeline when the operands allow 128-bit loads; the last slab may be
     // partial (n_full counts the slabs that lie fully inside both operands along k).  ANY_WIDTH: limits that are no
     // multiples of 4, for a k-contiguous A and an n-contiguous B.  There the partial slab is loaded element by element,
@@ -543,32 +618,36 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
         // (one copy of the loop per kind of tile, so that the kind is not a branch, and a register merge, per slab)
         auto steady = [&](auto clamp) {
             for (; s + 3 < n_full; s += 2) {
-                load_fast(k_begin + (s + 2) * BK, ra0, rb0);
-                multiply_slab(0, BK, [&] { store_lds(1, ra1, rb1, decltype(clamp)::value); });
+                spread_slab(0, std::true_type{}, k_begin + (s + 2) * BK, ra0, rb0, ra1, rb1, clamp);
                 __syncthreads();
-                load_fast(k_begin + (s + 3) * BK, ra1, rb1);
-                multiply_slab(1, BK, [&] { store_lds(0, ra0, rb0, decltype(clamp)::value); });
+                spread_slab(1, std::true_type{}, k_begin + (s + 3) * BK, ra1, rb1, ra0, rb0, clamp);
                 __syncthreads();
             }
         };
         if (inner_tile) steady(std::false_type{});
         else steady(std::true_type{});
+        // slab s, and slab t behind it on its way to LDS, which may be the partial last one
+        auto last_slab = [&](int buf, int t, f32x4 (&sa)[IT_A], f32x4 (&sb)[IT_B]) {
+            if (!ANY_WIDTH && t >= n_full) fix_tail(k_begin + t * BK, sa, sb);
+            if (inner_tile) spread_slab(buf, std::false_type{}, 0, sa, sb, sa, sb, std::false_type{});
+            else spread_slab(buf, std::false_type{}, 0, sa, sb, sa, sb, std::true_type{});
+        };
         // the same with the partial last slab allowed (at most one more trip)
         for (; s + 3 < n_pipe; s += 2) {
             load_slab(s + 2, ra0, rb0);
-            multiply_slab(0, BK, [&] { store_slab(1, s + 1, ra1, rb1); });
+            last_slab(0, s + 1, ra1, rb1);
             __syncthreads();
             load_slab(s + 3, ra1, rb1);
-            multiply_slab(1, BK, [&] { store_slab(0, s + 2, ra0, rb0); });
+            last_slab(1, s + 2, ra0, rb0);
             __syncthreads();
         }
         // two or three slabs are left: s (in LDS 0), s+1 (in R1), and s+2 if n_pipe is odd
         const bool three = (s + 2 < n_pipe);
         if (three) load_slab(s + 2, ra0, rb0);
-        multiply_slab(0, BK, [&] { store_slab(1, s + 1, ra1, rb1); });
+        last_slab(0, s + 1, ra1, rb1);
         __syncthreads();
         if (three) {
-            multiply_slab(1, BK, [&] { store_slab(0, s + 2, ra0, rb0); });
+            last_slab(1, s + 2, ra0, rb0);
             __syncthreads();
             multiply_slab(0, k_in_slab(s + 2), nothing);
         } else {
