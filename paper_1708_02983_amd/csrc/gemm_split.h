@@ -11,7 +11,7 @@
 // that of v_mfma_f32_32x32x2_f32 (relative error of a sum of 1 024: 1.9e-7 against 5.7e-7, of 64: 4.9e-8 against 1.4e-7).
 // The bfloat16 instruction has sixteen times the fp32 one's rate, so six of them still leave 2.7 times; the 6.5 vector
 // instructions per operand element that scale and split it run beside the matrix instructions of the same SIMD (24 matrix
-// instructions with six vector instructions behind each take 3 % longer than without).
+// instructions with four or six vector instructions behind each take as long as, or 3 to 15 % longer than without).
 // Range: every operand is multiplied by 2^32 on its way into the split, every result by 2^-64.  A bfloat16 has fp32's
 // exponents but its last part lies 16 bits below the number, so without that an operand below 2^-110 would lose bits;
 // with it every fp32 number, denormal ones included, is split exactly into normal bfloat16 numbers.  Finite operands from
@@ -22,6 +22,7 @@
 //
 #pragma once
 #include "gemm_mfma.h"
+#include <utility>
 
 namespace easgd {
 
@@ -41,9 +42,10 @@ __device__ __forceinline__ unsigned bf16_pack(float a, float b)
     return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));      // v_cvt_pk_bf16_f32
 }
 
-// The split of eight values in six parts of eight to ten independent instructions each (x is used up): a part fits
-// behind one matrix instruction, and no instruction waits for the one before it.  ONES: x * mul + add is split, which
-// puts ones in the place of x (mul = 0) at no cost; otherwise x alone.
+// The split of eight values in twelve parts of four or so independent instructions each (x is used up), to be placed behind matrix
+// instructions; no instruction waits for the one before it.  ONES: x * mul + add is split, which puts ones in the place
+// of x (mul = 0) at no cost; otherwise x alone.
+constexpr int SPLIT_PARTS = 12;
 template <bool ONES = false>
 __device__ __forceinline__ void split_part(int part, f32x8 &x, SplitFrag &f, u32x4 &t, float mul = SPLIT_SCALE, float add = 0.f)
 {
@@ -54,12 +56,18 @@ __device__ __forceinline__ void split_part(int part, f32x8 &x, SplitFrag &f, u32
     auto take = [&](u32x4 &plane, int e) { plane[e] = bf16_pack(x[2 * e], x[2 * e + 1]); };
     auto widen = [&](const u32x4 &plane, int e) { f.l[e] = low(plane[e]); t[e] = high(plane[e]); };
     auto rest = [&](int e) { x[2 * e] -= __uint_as_float(f.l[e]); x[2 * e + 1] -= __uint_as_float(t[e]); };
-    if (part == 0) { scale(0); scale(1); scale(2); scale(3); }
-    if (part == 1) { take(f.h, 0); take(f.h, 1); take(f.h, 2); take(f.h, 3); widen(f.h, 0); widen(f.h, 1); }
-    if (part == 2) { widen(f.h, 2); widen(f.h, 3); rest(0); rest(1); }
-    if (part == 3) { rest(2); rest(3); take(f.m, 0); take(f.m, 1); widen(f.m, 0); }
-    if (part == 4) { take(f.m, 2); take(f.m, 3); widen(f.m, 1); widen(f.m, 2); widen(f.m, 3); rest(0); }
-    if (part == 5) { rest(1); rest(2); rest(3); take(f.l, 0); take(f.l, 1); take(f.l, 2); take(f.l, 3); }
+    if (part == 0) { scale(0); scale(1); }
+    if (part == 1) { scale(2); scale(3); }
+    if (part == 2) { take(f.h, 0); take(f.h, 1); take(f.h, 2); take(f.h, 3); }
+    if (part == 3) { widen(f.h, 0); widen(f.h, 1); }
+    if (part == 4) { widen(f.h, 2); widen(f.h, 3); }
+    if (part == 5) { rest(0); rest(1); }
+    if (part == 6) { rest(2); rest(3); }
+    if (part == 7) { take(f.m, 0); take(f.m, 1); take(f.m, 2); take(f.m, 3); }
+    if (part == 8) { widen(f.m, 0); widen(f.m, 1); }
+    if (part == 9) { widen(f.m, 2); widen(f.m, 3); rest(0); }
+    if (part == 10) { rest(1); rest(2); take(f.l, 0); }
+    if (part == 11) { rest(3); take(f.l, 1); take(f.l, 2); take(f.l, 3); }
 }
 
 template <bool ONES = false>
@@ -67,8 +75,14 @@ __device__ __forceinline__ void split8(f32x8 &x, SplitFrag &f, float mul = SPLIT
 {
     u32x4 t;
 #pragma unroll
-    for (int part = 0; part < 6; ++part) split_part<ONES>(part, x, f, t, mul, add);
+    for (int part = 0; part < SPLIT_PARTS; ++part) split_part<ONES>(part, x, f, t, mul, add);
 }
+
+// f(0), f(1), ..., f(N - 1) with the index as a constant: what depends on it is decided before the optimiser sees the code
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_each(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
 
 // Tile configuration: a block of four wavefronts, WN side by side along n and WK along k, owns a (TM*32) x (WN*32)
 // tile of C; every wavefront owns all TM*32 rows of 32 columns.  A slab is KS steps of sixteen k per wavefront.
@@ -150,11 +164,10 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
 
     struct RawA { f32x8 x[IT]; };
     struct RawB { f32x8 x[KS]; };
-    auto k8_vec = [](auto rs, unsigned off, unsigned uni, f32x8 &x) {
-        const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, (int)uni, 0);
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off + 16, (int)uni, 0);
+    auto k4_vec = [](auto rs, unsigned off, unsigned uni, int half, f32x8 &x) {
+        const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off + 16 * half, (int)uni, 0);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { x[e] = __uint_as_float(u[e]); x[4 + e] = __uint_as_float(v[e]); }
+        for (int e = 0; e < 4; ++e) x[4 * half + e] = __uint_as_float(u[e]);
     };
     // Slabs that lie inside both operands along k are loaded as they are; in the others every element has an address of
     // its own that is held inside the operand, and is replaced by what it stands for when it is used (cut).
@@ -172,14 +185,20 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     };
     auto whole = [&](int slab) { return early ? start(slab) == k_begin + slab * BK : slab < n_fast; };
     const int k_ones = (A_LAYOUT == K_CONTIG && p.a_ones < k_end) ? p.a_ones : -1;
-    auto load_a = [&](int slab, auto inner, int it, RawA &r) {
+    // inner (a slab inside the operands): piece 0, 1 (or 0..7) is one load each; otherwise piece 0 is all of them
+    auto load_a = [&](int slab, auto inner, int it, int piece, RawA &r) {
+        constexpr bool INNER = decltype(inner)::value;
+        if (piece < 0 || piece >= 8 || (!INNER && piece > 0)) return;
         const int k0 = start(slab);
-        if (decltype(inner)::value || slab < n_fast) {
-            if (A_LAYOUT == K_CONTIG) k8_vec(ab, a_off[it], 4u * (unsigned)k0, r.x[it]);
-            else
+        if (INNER || slab < n_fast) {
+            if (A_LAYOUT == K_CONTIG) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if (!INNER || h == piece) k4_vec(ab, a_off[it], 4u * (unsigned)k0, h, r.x[it]);
+            } else
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    r.x[it][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)a_off[it], (int)(4u * (unsigned)(k0 + e) * (unsigned)p.lda), 0));
+                    if (!INNER || e == piece) r.x[it][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)a_off[it], (int)(4u * (unsigned)(k0 + e) * (unsigned)p.lda), 0));
         } else if (!early && slab < n_slabs) {
             const int ku = a_k(it);
 #pragma unroll
@@ -191,14 +210,19 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
             }
         }
     };
-    auto load_b_step = [&](int slab, auto inner, int ks, RawB &r) {
+    auto load_b_step = [&](int slab, auto inner, int ks, int piece, RawB &r) {
+        constexpr bool INNER = decltype(inner)::value;
+        if (piece < 0 || piece >= 8 || (!INNER && piece > 0)) return;
         const int kb = start(slab) + 16 * (wk + ks * WK);
-        if (decltype(inner)::value || slab < n_fast) {
-            if (B_LAYOUT == K_CONTIG) k8_vec(bb, b_off, 4u * (unsigned)kb, r.x[ks]);
-            else
+        if (INNER || slab < n_fast) {
+            if (B_LAYOUT == K_CONTIG) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if (!INNER || h == piece) k4_vec(bb, b_off, 4u * (unsigned)kb, h, r.x[ks]);
+            } else
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    r.x[ks][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bb, (int)b_off, (int)(4u * (unsigned)(kb + e) * (unsigned)p.ldb), 0));
+                    if (!INNER || e == piece) r.x[ks][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bb, (int)b_off, (int)(4u * (unsigned)(kb + e) * (unsigned)p.ldb), 0));
         } else if (!early && slab < n_slabs) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -211,12 +235,9 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     auto cut_a = [&](int slab, int it, RawA &r) { cut(r.x[it], start(slab) + a_k(it), k_begin + slab * BK, a_klim, k_ones); };
     auto cut_b = [&](int slab, int ks, RawB &r) { cut(r.x[ks], start(slab) + 16 * (wk + ks * WK) + 8 * q, k_begin + slab * BK, k_end, -1); };
     auto a_here = [&](int it) { return T::UNITS % 256 == 0 || tid + it * 256 < T::UNITS; };
-    auto store_a = [&](int buf, int it, const SplitFrag &f) {
+    auto store_plane = [&](int buf, int it, int plane, const SplitFrag &f) {
         if (!a_here(it)) return;
-        u32x4 *dst = lds + buf * T::SLAB_VECS + a_dst[it];
-        dst[0] = f.h;
-        dst[TM * 64] = f.m;
-        dst[2 * TM * 64] = f.l;
+        lds[buf * T::SLAB_VECS + a_dst[it] + plane * TM * 64] = plane == 0 ? f.h : plane == 1 ? f.m : f.l;
     };
 
     f32x16 hi[TM], lo[TM];
@@ -228,13 +249,11 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
     };
     // The fragments of A come from LDS one tile ahead of the products that use them.
-    auto fetch = [&](int buf, int ks, int i, SplitFrag &f) {
+    auto fetch = [&](int buf, int ks, int i, int plane, SplitFrag &f) {
         const int step = wk + ks * WK, k8 = 2 * step + q;
         const int swz = (A_LAYOUT == K_CONTIG) ? k8 * (8 / K8) : 0;
         const u32x4 *src = lds + buf * T::SLAB_VECS + (step * 3 * TM + i) * 64 + ((l32 ^ swz) + 32 * q);
-        f.h = src[0];
-        f.m = src[TM * 64];
-        f.l = src[2 * TM * 64];
+        (plane == 0 ? f.h : plane == 1 ? f.m : f.l) = src[plane * TM * 64];
     };
     auto multiply = [&](int part, int i, const SplitFrag &f, const SplitFrag &fb) {
         if (part == 0) mm(f.l, fb.h, lo[i]);
@@ -245,31 +264,42 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
         if (part == 5) mm(f.h, fb.m, lo[i]);
     };
 
-    // Slab s is multiplied from LDS buffer s % 2, tile by tile and step by step ("items" of six matrix instructions).
-    // The vector instructions that prepare what comes next run between the matrix instructions of an item: the split
-    // of the slab's second step of B, the split of slab s+1 of A on its way to the other LDS buffer, the split of
-    // slab s+1's first step of B.  A raw register is reloaded as soon as it has been split, one slab ahead.
-    constexpr int ITEMS = KS * TM;
+    // Slab s is multiplied from LDS buffer s % 2, tile by tile and step by step ("items" of six matrix instructions, "slots").
+    // What prepares the slabs behind it runs between the matrix instructions, evenly spread, since a vector instruction takes an
+    // eighth of a matrix instruction's time and a wavefront issues in order: one split after the other (the slab's second
+    // step of B, slab s+1 of A on its way to the other LDS buffer, slab s+1's first step of B), SPAN slots each; the
+    // LDS stores and the loads of the raw registers that a split has used up in the slots behind it.  In bursts (a split within
+    // six slots, then its stores and loads) / spread, us: forward 3072->2048, 8 workers, 256 rows 137 / 127; input gradient
+    // 2048->2048, 32, 100 198 / 193; forward 784->1024, 16, 128 in 64x128 tiles 27.6 / 26.6, 784->500, 8, 50 in 32x32 11.3 / 10.4.
+    // What is left of the first of these over its matrix instructions (83 us) is the loads and LDS stores: without loads
+    // from memory it takes 125, without LDS stores 116, without either and with a third of the LDS reads 102.
+    constexpr int ITEMS = KS * TM, SLOTS = 6 * ITEMS, SPLITS = KS + IT, SPAN = SLOTS / SPLITS;
+    constexpr int RATE = SPAN >= 12 ? 1 : 4;                             // pieces of a load per slot, eight in all
+    static_assert(SLOTS % SPLITS == 0 && SPAN >= 3, "a split's three stores come before the end of the slab");
+    // the order of the splits (A's units 0, 1, ..; -1: B's second step; -2: B's first step, which always comes last: the
+    // registers it goes to are in use until the second step begins)
+    constexpr auto split_at = [](int n) { return KS == 1 ? (n < IT ? n : -2) : IT == 1 ? (n == 0 ? -1 : n == 1 ? 0 : -2) : (n == 0 ? 0 : n == 1 ? -1 : n + 1 < SPLITS ? n - 1 : -2); };
+    // (A second set of raw registers, so that a slab's loads have two slabs to arrive in, is slower in every tile: 64x128 DW 38.1 us
+    // -> 51.0, 32x32 input gradient 777->333 7.9 -> 8.7.)
     RawA ra;
     RawB rb;
     SplitFrag fb[2];
-    // before the loop: slab 0 is split, the raw registers hold what the loop expects to find (A from slab 1 on; B from
-    // the second step of slab 0 on)
+    // before the loop: slab 0 is split, the raw registers hold what the loop expects to find (A's slab 1, B's second step of slab 0)
 #pragma unroll
-    for (int u = 0; u < IT; ++u) load_a(0, std::false_type{}, u, ra);
+    for (int u = 0; u < IT; ++u) load_a(0, std::false_type{}, u, 0, ra);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) load_b_step(0, std::false_type{}, ks, rb);
+    for (int ks = 0; ks < KS; ++ks) load_b_step(0, std::false_type{}, ks, 0, rb);
 #pragma unroll
     for (int u = 0; u < IT; ++u) {
         SplitFrag f;
         if (!whole(0)) cut_a(0, u, ra);
         split8<ONES>(ra.x[u], f, a_mul[u], a_add[u]);
-        store_a(0, u, f);
-        load_a(1, std::false_type{}, u, ra);
+#pragma unroll
+        for (int plane = 0; plane < 3; ++plane) store_plane(0, u, plane, f);
+        load_a(1, std::false_type{}, u, 0, ra);
     }
     if (!whole(0)) cut_b(0, 0, rb);
     split8(rb.x[0], fb[0]);
-    load_b_step(1, std::false_type{}, 0, rb);
     __syncthreads();
     auto slab = [&](int s, auto parity, auto last_slabs) {
         constexpr int buf = decltype(parity)::value;
@@ -278,42 +308,48 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
         // fragments of B: step ks of this slab, and where the first step of the next slab goes
         constexpr int F0 = KS == 1 ? buf : 0, F1 = KS == 1 ? (buf ^ 1) : 0;
         SplitFrag fa[2], fs[IT];
-        u32x4 t[IT + 1];
-        fetch(buf, 0, 0, fa[0]);
+        u32x4 t[SPLITS];
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it) {
-            const int ks = it / TM, i = it % TM;
-            if (it + 1 < ITEMS) fetch(buf, (it + 1) / TM, (it + 1) % TM, fa[(it + 1) & 1]);
-            const bool b1 = KS == 2 && it == 0, b0 = it == (KS == 2 ? TM : ITEMS - 1);      // which split of B runs here
-            if (LAST && b1 && !whole(s)) cut_b(s, 1, rb);
-            if (LAST && b0 && !whole(s + 1)) cut_b(s + 1, 0, rb);
-            auto a_unit = [&](int u) { return it == (ITEMS >= 4 ? 1 + u % 2 : 0); };        // which units of A
-#pragma unroll
-            for (int u = 0; u < IT; ++u)
-                if (LAST && a_unit(u) && !whole(s + 1)) cut_a(s + 1, u, ra);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int plane = 0; plane < 3; ++plane) fetch(buf, 0, 0, plane, fa[0]);
+        static_for<SLOTS>([&](auto slot_) {
+            constexpr int slot = decltype(slot_)::value, it = slot / 6, part = slot % 6, ks = it / TM, i = it % TM;
+            constexpr int n = slot / SPAN, u = split_at(n), q0 = (slot % SPAN * SPLIT_PARTS + SPAN - 1) / SPAN;     // split n from part q0 on
             // a step without a k of its own holds zeros only
             const int k_step = start(s) + 16 * (wk + ks * WK);
             const bool live = !LAST || (k_step < k_end && k_step + 16 > k_begin + s * BK);  // uniform
-#pragma unroll
-            for (int part = 0; part < 6; ++part) {
-                if (live) multiply(part, i, fa[it & 1], fb[ks == 0 ? F0 : 1]);
-                if (b1) split_part(part, rb.x[KS - 1], fb[1], t[IT]);
-                if (b0) split_part(part, rb.x[0], fb[F1], t[IT]);
-#pragma unroll
-                for (int u = 0; u < IT; ++u)
-                    if (a_unit(u)) split_part<ONES>(part, ra.x[u], fs[u], t[u], a_mul[u], a_add[u]);
-                __builtin_amdgcn_sched_barrier(0);
+            if constexpr (LAST && slot % SPAN == 0) {
+                if constexpr (u == -1) { if (!whole(s)) cut_b(s, KS - 1, rb); }
+                else if constexpr (u == -2) { if (!whole(s + 1)) cut_b(s + 1, 0, rb); }
+                else if (!whole(s + 1)) cut_a(s + 1, u, ra);
             }
-            if (b1) load_b_step(s + 1, inner, 1, rb);
-            if (b0) load_b_step(s + 2, inner, 0, rb);
-#pragma unroll
-            for (int u = 0; u < IT; ++u)
-                if (a_unit(u)) {
-                    if (!LAST || s + 1 < n_slabs) store_a(buf ^ 1, u, fs[u]);
-                    load_a(s + 2, inner, u, ra);
+            __builtin_amdgcn_sched_barrier(0);
+            if (live) multiply(part, i, fa[it & 1], fb[ks == 0 ? F0 : 1]);
+            static_for<SPLIT_PARTS>([&](auto q_) {
+                constexpr int q = decltype(q_)::value;
+                if constexpr (q >= q0 && q * SPAN / SPLIT_PARTS == slot % SPAN) {
+                    if constexpr (u == -1) split_part(q, rb.x[KS - 1], fb[1], t[n]);
+                    else if constexpr (u == -2) split_part(q, rb.x[0], fb[F1], t[n]);
+                    else split_part<ONES>(q, ra.x[u], fs[u], t[n], a_mul[u], a_add[u]);
                 }
-        }
+            });
+            if constexpr (it + 1 < ITEMS && part < 3) fetch(buf, (it + 1) / TM, (it + 1) % TM, part == 0 ? 2 : part - 1, fa[(it + 1) & 1]);
+            static_for<SPLITS - 1>([&](auto m_) {
+                constexpr int m = decltype(m_)::value, v = split_at(m), after = slot - (m + 1) * SPAN;
+                if constexpr (v >= 0 && after >= 0 && after < 3) {
+                    if (!LAST || s + 1 < n_slabs) store_plane(buf ^ 1, v, after, fs[v]);
+                }
+                if constexpr (after >= 0 && after < 8 / RATE) {
+                    static_for<RATE>([&](auto r_) {
+                        constexpr int piece = after * RATE + decltype(r_)::value;
+                        if constexpr (v >= 0) load_a(s + 2, inner, v, piece, ra);
+                        else load_b_step(s + 1, inner, KS - 1, piece, rb);
+                    });
+                }
+            });
+            if constexpr (slot < 8 / RATE)               // the registers that the slab before has used up at its end
+                static_for<RATE>([&](auto r_) { load_b_step(s + 1, inner, 0, slot * RATE + decltype(r_)::value, rb); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
         __syncthreads();
     };
     constexpr std::integral_constant<int, 0> even{};
