@@ -22,6 +22,7 @@
 //
 #pragma once
 #include "gemm_mfma.h"
+#include "narrow_dw.h"
 #include <utility>
 
 namespace easgd {
@@ -544,15 +545,38 @@ __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_dw_
 }
 
 // An input-gradient product with the weight-gradient product of a narrow layer, whose few blocks come first: they are a
-// chain of round trips to memory, which the blocks of the other product cover.
-template <int TM, int WN, int WK, int EPI, bool VEC_DW>
+// chain of round trips to memory, which the blocks of the other product cover.  DW: the form of the narrow product.
+enum NarrowForm { DW_128x32 = 0, DW_128x32_VEC = 1, DW_NARROW16 = 2 };
+
+template <int DW>
+constexpr int narrow_lds_floats() { return DW == DW_NARROW16 ? 0 : gemm_lds_floats<128, 32, 32, MN_CONTIG, MN_CONTIG>(); }
+
+template <int EPI, int DW>
+__device__ __forceinline__ void narrow_dw_any(const GemmArgs &dw, const unsigned bid, float *__restrict__ lds)
+{
+    if constexpr (DW == DW_NARROW16) narrow_dw_block<1, EPI>(dw, bid);
+    else gemm_block<128, 32, 32, 4, 1, MN_CONTIG, MN_CONTIG, DW == DW_128x32_VEC, EPI>(dw, bid, lds);
+}
+
+template <int TM, int WN, int WK, int EPI, int DW>
 __global__ __launch_bounds__(256, 3) void gemm_split_da_narrow_dw_kernel(GemmArgs da, GemmArgs dw, unsigned n_dw)
 {
-    constexpr int NARROW = gemm_lds_floats<128, 32, 32, MN_CONTIG, MN_CONTIG>() / 4, SPLIT = SplitTile<TM, WN, WK>::LDS_VECS;
+    constexpr int NARROW = narrow_lds_floats<DW>() / 4, SPLIT = SplitTile<TM, WN, WK>::LDS_VECS;
     __shared__ u32x4 lds[NARROW > SPLIT ? NARROW : SPLIT];
     if (dw.mean.blocks > 0 && blockIdx.x >= dw.mean.first_block) mean_loss_block(dw.mean, blockIdx.x - dw.mean.first_block);
-    else if (blockIdx.x < n_dw) gemm_block<128, 32, 32, 4, 1, MN_CONTIG, MN_CONTIG, VEC_DW, EPI>(dw, blockIdx.x, reinterpret_cast<float *>(lds));
+    else if (blockIdx.x < n_dw) narrow_dw_any<EPI, DW>(dw, blockIdx.x, reinterpret_cast<float *>(lds));
     else split_block<TM, WN, WK, K_CONTIG, K_CONTIG, EPI_MASK>(da, blockIdx.x - n_dw, lds);
+}
+
+// The same with 64x64 tiles of the fp32 instruction.
+template <int EPI, int DW>
+__global__ __launch_bounds__(256, 2) void gemm_da_narrow_dw_kernel(GemmArgs da, GemmArgs dw, unsigned n_dw)
+{
+    constexpr int NARROW = narrow_lds_floats<DW>(), WIDE = gemm_lds_floats<64, 64, 32, K_CONTIG, K_CONTIG>();
+    __shared__ __attribute__((aligned(16))) float lds[NARROW > WIDE ? NARROW : WIDE];
+    if (dw.mean.blocks > 0 && blockIdx.x >= dw.mean.first_block) mean_loss_block(dw.mean, blockIdx.x - dw.mean.first_block);
+    else if (blockIdx.x < n_dw) narrow_dw_any<EPI, DW>(dw, blockIdx.x, lds);
+    else gemm_block<64, 64, 32, 2, 2, K_CONTIG, K_CONTIG, true, EPI_MASK>(da, blockIdx.x - n_dw, lds);
 }
 
 }  // namespace easgd

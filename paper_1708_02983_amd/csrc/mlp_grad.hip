@@ -441,6 +441,14 @@ static bool split_dw_fits(const GemmArgs &a, bool vec)
     return options().gemm_tile == 0 && a.N > 32 && split_fits(a, false, false) && (!vec || split_dw_blocks(a) >= (size_t)(2 * num_cus()));
 }
 
+// Blocks of a narrow weight gradient that shares a launch, by its form.
+template <int DW>
+static unsigned place_narrow(GemmArgs &dw)
+{
+    if constexpr (DW == DW_NARROW16) return place_blocks<64, 16>(dw);
+    else return place_blocks<128, 32>(dw);
+}
+
 // ... and whether they are faster than the 64x64 tiles of the fp32 instruction: where the products that they multiply for
 // nothing, in half empty tiles of columns and in the last slab of 32 rows, leave them the advantage.  The same for all
 // epilogues, so that the gradient of a round is that of easgd_grad.  With 128-bit loads on the fp32 path, time of the fp32
@@ -505,16 +513,30 @@ static void launch_split_pair_dw_dw(GemmArgs d0, GemmArgs d1, hipStream_t s)
     EASGD_LAUNCH((gemm_split_dw_pair_kernel<2, 4, 1, EPI>), dim3(n0 + n1 + d0.mean.blocks), dim3(256), 0, s, d0, d1, n0);
 }
 
+// Weight gradients of at most 32 columns: narrow_dw.h or the 128x32 tile (same bits).  us, 128x32 / narrow (layer, workers, rows;
+// plain gradients): 784->10, 4, 64 5.9 / 3.5 (with momentum 7.0 / 4.2), 2048->10, 32, 100 15.1 / 9.2, 3072->10, 32, 256 45.2 / 24.8,
+// 2047->17, 20, 77 9.9 / 9.2; with 128-bit loads 3072->12, 8, 128 6.0 / 5.8, but 1024->32, 32, 256 13.3 / 19.7.
+static bool narrow_dw_fits(const GemmArgs &a, bool vec) { return a.N <= 16 || (a.N <= 32 && !vec); }
+
+template <int TN, int EPI>
+static void launch_narrow_dw(const GemmArgs &a_in, hipStream_t s)
+{
+    GemmArgs a = a_in;
+    const unsigned total = place_blocks<64, 16 * TN>(a);
+    a.mean.first_block = total;
+    EASGD_LAUNCH((narrow_dw_kernel<TN, EPI>), dim3(total + a.mean.blocks), dim3(256), 0, s, a);
+}
+
 // An input-gradient product and the weight-gradient product of a narrow layer in one launch, the first as split tiles of
-// `pick`'s shape; false: this tile has none.
-template <int EPI, bool VEC_DW>
+// `pick`'s shape; false: this tile has none.  DW: the form of the second.
+template <int EPI, int DW>
 static bool launch_split_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, SplitPick pick, hipStream_t s)
 {
     auto launch = [&](auto tm, auto wn, auto wk) {
         constexpr int TM = decltype(tm)::value, WN = decltype(wn)::value, WK = decltype(wk)::value;
-        const unsigned n_dw = place_blocks<128, 32>(dw), n = place_blocks<TM * 32, WN * 32>(da);
+        const unsigned n_dw = place_narrow<DW>(dw), n = place_blocks<TM * 32, WN * 32>(da);
         dw.mean.first_block = n + n_dw;
-        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<TM, WN, WK, EPI, VEC_DW>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
+        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<TM, WN, WK, EPI, DW>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
         return true;
     };
     constexpr std::integral_constant<int, 1> one{};
@@ -528,15 +550,12 @@ static bool launch_split_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, SplitPick p
 }
 
 // The same with 64x64 tiles of the fp32 instruction.
-template <int EPI, bool VEC_DW>
+template <int EPI, int DW>
 static void launch_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, hipStream_t s)
 {
-    const unsigned n0 = place_blocks<64, 64>(da), n1 = place_blocks<128, 32>(dw);
-    da.mean = dw.mean;
-    da.mean.first_block = n0 + n1;
-    EASGD_LAUNCH((gemm_pair_kernel<64, 64, 32, 2, 2, K_CONTIG, K_CONTIG, true, EPI_MASK,
-                                         128, 32, SPLIT_BK, 4, 1, MN_CONTIG, MN_CONTIG, VEC_DW, EPI>),
-                       dim3(n0 + n1 + da.mean.blocks), dim3(256), 0, s, da, dw, n0);
+    const unsigned n_dw = place_narrow<DW>(dw), n = place_blocks<64, 64>(da);
+    dw.mean.first_block = n + n_dw;
+    EASGD_LAUNCH((gemm_da_narrow_dw_kernel<EPI, DW>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
 }
 
 // Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile of the fp32 matrix instruction; input gradients, a
@@ -549,6 +568,13 @@ template <int AL, int BL, int EPI>
 static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, Form form = FORM_BY_SIZE)
 {
     if (a.N <= 32) {
+        if constexpr (AL == MN_CONTIG && BL == MN_CONTIG) {
+            if (narrow_dw_fits(a, vec)) {
+                if (a.N <= 16) launch_narrow_dw<1, EPI>(a, s);
+                else launch_narrow_dw<2, EPI>(a, s);
+                return;
+            }
+        }
         launch_tile<128, 32, SPLIT_BK, 4, 1, AL, BL, EPI>(a, vec, s);
         return;
     }
@@ -973,8 +999,14 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
                 if (fp32_pair || (pick != SPLIT_NONE && pick != SPLIT_128x128)) {
                     by_rule([&](auto e) {
                         constexpr int E = decltype(e)::value;
-                        if (fp32_pair) held.vec ? launch_pair_da_narrow_dw<E, true>(a, held.a, s) : launch_pair_da_narrow_dw<E, false>(a, held.a, s);
-                        else held.vec ? launch_split_pair_da_narrow_dw<E, true>(a, held.a, pick, s) : launch_split_pair_da_narrow_dw<E, false>(a, held.a, pick, s);
+                        auto launch = [&](auto dw) {
+                            constexpr int DW = decltype(dw)::value;
+                            if (fp32_pair) launch_pair_da_narrow_dw<E, DW>(a, held.a, s);
+                            else launch_split_pair_da_narrow_dw<E, DW>(a, held.a, pick, s);
+                        };
+                        if (held.a.N <= 16) launch(std::integral_constant<int, DW_NARROW16>{});
+                        else if (held.vec) launch(std::integral_constant<int, DW_128x32_VEC>{});
+                        else launch(std::integral_constant<int, DW_128x32>{});
                     });
                     shared = true;
                 }

@@ -99,3 +99,33 @@ def test_what_lies_behind_a_row_does_not_reach_a_sum(bad):
         out = torch.empty((P, b * width), device="cuda")
         hip.easgd_layer_product(kind, d_in, d_out, dA, out, Wl=dW, dZ=dZ, ld=W.shape[1], out_ws=b * width)
         assert np.isfinite(to_host(out)).all(), kind
+
+
+# (d_in, d_out, P, b): one, two tiles of sixteen columns; rows one below, at and above a wavefront's and a block's; sums one below,
+# at and above a matrix instruction (4), a trip to memory (64) and two of them
+NARROW = [(1, 1, 2, 1), (15, 3, 3, 3), (16, 10, 2, 4), (17, 16, 4, 5), (63, 10, 9, 63), (64, 12, 8, 64), (65, 2, 16, 65),
+          (127, 17, 3, 30), (130, 31, 8, 129), (785, 10, 5, 130), (96, 32, 4, 40)]
+
+
+@pytest.mark.parametrize("d_in,d_out,P,b", NARROW, ids=lambda v: str(v))
+def test_narrow_weight_gradients_element_by_element(d_in, d_out, P, b):
+    import paper_1708_02983_amd as hip
+    rng = np.random.default_rng(d_in + d_out + b)
+    A, Z = rng.standard_normal((P, b, d_in)).astype(F), rng.standard_normal((P, b, d_out)).astype(F)
+    width = (d_in + 1) * d_out
+    one = np.concatenate([A, np.ones((P, b, 1), F)], axis=2).astype(np.float64).transpose(0, 2, 1)
+    ref, mag = (one @ Z.astype(np.float64)).reshape(P, -1), (np.abs(one) @ np.abs(Z).astype(np.float64)).reshape(P, -1)
+
+    def product(A):
+        out = torch.full((P, width + 5), float("nan"), device="cuda")
+        hip.easgd_layer_product(1, d_in, d_out, to_dev(A), out, dZ=to_dev(Z), out_ws=width + 5)
+        got = to_host(out)
+        assert np.isnan(got[:, width:]).all()
+        return got[:, :width]
+
+    # b additions, each off by half an ulp of a partial sum
+    assert (np.abs(product(A) - ref) <= (b + 8) * 2.0 ** -24 * mag).all()
+    # an infinity in the last row of A reaches the first row of the result and no other
+    A[:, b - 1, 0] = np.inf
+    got = product(A).reshape(P, d_in + 1, d_out)
+    assert not np.isfinite(got[:, 0]).any() and np.isfinite(got[:, 1:]).all()
