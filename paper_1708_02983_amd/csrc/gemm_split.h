@@ -271,10 +271,14 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     // step of B, slab s+1 of A on its way to the other LDS buffer, slab s+1's first step of B), SPAN slots each; the
     // LDS stores and the loads of the raw registers that a split has used up in the slots behind it.  In bursts (a split within
     // six slots, then its stores and loads) / spread, us: forward 3072->2048, 8 workers, 256 rows 137 / 127; input gradient
-    // 2048->2048, 32, 100 198 / 193; forward 784->1024, 16, 128 in 64x128 tiles 27.6 / 26.6, 784->500, 8, 50 in 32x32 11.3 / 10.4.
+    // 2048->2048, 32, 100 198 / 193; forward 784->1024, 16, 128 in 64x128 tiles 27.6 / 26.6, 1024->1024, 16, 128 (input gradient) 32.2 / 31.8.
     // What is left of the first of these over its matrix instructions (83 us) is the loads and LDS stores: without loads
     // from memory it takes 125, without LDS stores 116, without either and with a third of the LDS reads 102.
     constexpr int ITEMS = KS * TM, SLOTS = 6 * ITEMS, SPLITS = KS + IT, SPAN = SLOTS / SPLITS;
+    // The smallest tile has six slots: its two splits share them all, stores and loads follow behind the last (forward 988->1514,
+    // 8 workers, 17 rows 16.4 us against 17.0 with the splits one after the other, 3072->593, 3, 16 31.9 against 34.7; but 784->500, 8, 50 11.4
+    // against 10.4, whose weights come from the L2).
+    constexpr bool TINY = ITEMS == 1;
     constexpr int RATE = SPAN >= 12 ? 1 : 4;                             // pieces of a load per slot, eight in all
     static_assert(SLOTS % SPLITS == 0 && SPAN >= 3, "a split's three stores come before the end of the slab");
     // the order of the splits (A's units 0, 1, ..; -1: B's second step; -2: B's first step, which always comes last: the
@@ -301,6 +305,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     }
     if (!whole(0)) cut_b(0, 0, rb);
     split8(rb.x[0], fb[0]);
+    if constexpr (TINY) load_b_step(1, std::false_type{}, 0, 0, rb);
     __syncthreads();
     auto slab = [&](int s, auto parity, auto last_slabs) {
         constexpr int buf = decltype(parity)::value;
@@ -318,14 +323,22 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
             // a step without a k of its own holds zeros only
             const int k_step = start(s) + 16 * (wk + ks * WK);
             const bool live = !LAST || (k_step < k_end && k_step + 16 > k_begin + s * BK);  // uniform
-            if constexpr (LAST && slot % SPAN == 0) {
+            if constexpr (LAST && TINY && slot == 0) {
+                if (!whole(s + 1)) { cut_a(s + 1, 0, ra); cut_b(s + 1, 0, rb); }
+            } else if constexpr (LAST && !TINY && slot % SPAN == 0) {
                 if constexpr (u == -1) { if (!whole(s)) cut_b(s, KS - 1, rb); }
                 else if constexpr (u == -2) { if (!whole(s + 1)) cut_b(s + 1, 0, rb); }
                 else if (!whole(s + 1)) cut_a(s + 1, u, ra);
             }
             __builtin_amdgcn_sched_barrier(0);
             if (live) multiply(part, i, fa[it & 1], fb[ks == 0 ? F0 : 1]);
-            static_for<SPLIT_PARTS>([&](auto q_) {
+            if constexpr (TINY) {
+#pragma unroll
+                for (int q = 2 * slot; q < 2 * slot + 2; ++q) {
+                    split_part(q, rb.x[0], fb[F1], t[0]);
+                    split_part<ONES>(q, ra.x[0], fs[0], t[1], a_mul[0], a_add[0]);
+                }
+            } else static_for<SPLIT_PARTS>([&](auto q_) {
                 constexpr int q = decltype(q_)::value;
                 if constexpr (q >= q0 && q * SPAN / SPLIT_PARTS == slot % SPAN) {
                     if constexpr (u == -1) split_part(q, rb.x[KS - 1], fb[1], t[n]);
@@ -334,7 +347,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
                 }
             });
             if constexpr (it + 1 < ITEMS && part < 3) fetch(buf, (it + 1) / TM, (it + 1) % TM, part == 0 ? 2 : part - 1, fa[(it + 1) & 1]);
-            static_for<SPLITS - 1>([&](auto m_) {
+            if constexpr (!TINY) static_for<SPLITS - 1>([&](auto m_) {
                 constexpr int m = decltype(m_)::value, v = split_at(m), after = slot - (m + 1) * SPAN;
                 if constexpr (v >= 0 && after >= 0 && after < 3) {
                     if (!LAST || s + 1 < n_slabs) store_plane(buf ^ 1, v, after, fs[v]);
@@ -347,10 +360,19 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
                     });
                 }
             });
-            if constexpr (slot < 8 / RATE)               // the registers that the slab before has used up at its end
+            if constexpr (!TINY && slot < 8 / RATE)               // the registers that the slab before has used up at its end
                 static_for<RATE>([&](auto r_) { load_b_step(s + 1, inner, 0, slot * RATE + decltype(r_)::value, rb); });
             __builtin_amdgcn_sched_barrier(0);
         });
+        if constexpr (TINY) {
+#pragma unroll
+            for (int plane = 0; plane < 3; ++plane)
+                if (!LAST || s + 1 < n_slabs) store_plane(buf ^ 1, 0, plane, fs[0]);
+#pragma unroll
+            for (int piece = 0; piece < 8; ++piece) load_b_step(s + 2, inner, 0, piece, rb);
+#pragma unroll
+            for (int piece = 0; piece < 8; ++piece) load_a(s + 2, inner, 0, piece, ra);
+        }
         __syncthreads();
     };
     constexpr std::integral_constant<int, 0> even{};
