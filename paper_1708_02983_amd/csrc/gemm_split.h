@@ -186,16 +186,18 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     };
     auto whole = [&](int slab) { return early ? start(slab) == k_begin + slab * BK : slab < n_fast; };
     const int k_ones = (A_LAYOUT == K_CONTIG && p.a_ones < k_end) ? p.a_ones : -1;
-    // inner (a slab inside the operands): piece 0, 1 (or 0..7) is one load each; otherwise piece 0 is all of them
+    // inner (a slab inside the operands): piece 0..7 is one 32-bit load each, or piece 0 both halves of a lane's eight k; otherwise
+    // piece 0 is all of them.  The halves go out together: a few slots apart, other wavefronts' loads push the line that
+    // they share out of the first-level cache, and where rows start at any element of a line every line is fetched
+    // twice (input gradient 2974->1332, 30 workers, 101 rows 266 us against 202; rows of whole lines do not mind).
     auto load_a = [&](int slab, auto inner, int it, int piece, RawA &r) {
         constexpr bool INNER = decltype(inner)::value;
-        if (piece < 0 || piece >= 8 || (!INNER && piece > 0)) return;
+        if (piece > 0 && (!INNER || A_LAYOUT == K_CONTIG)) return;
         const int k0 = start(slab);
         if (INNER || slab < n_fast) {
             if (A_LAYOUT == K_CONTIG) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    if (!INNER || h == piece) k4_vec(ab, a_off[it], 4u * (unsigned)k0, h, r.x[it]);
+                k4_vec(ab, a_off[it], 4u * (unsigned)k0, 0, r.x[it]);
+                k4_vec(ab, a_off[it], 4u * (unsigned)k0, 1, r.x[it]);
             } else
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
@@ -213,13 +215,12 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     };
     auto load_b_step = [&](int slab, auto inner, int ks, int piece, RawB &r) {
         constexpr bool INNER = decltype(inner)::value;
-        if (piece < 0 || piece >= 8 || (!INNER && piece > 0)) return;
+        if (piece > 0 && (!INNER || B_LAYOUT == K_CONTIG)) return;
         const int kb = start(slab) + 16 * (wk + ks * WK);
         if (INNER || slab < n_fast) {
             if (B_LAYOUT == K_CONTIG) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    if (!INNER || h == piece) k4_vec(bb, b_off, 4u * (unsigned)kb, h, r.x[ks]);
+                k4_vec(bb, b_off, 4u * (unsigned)kb, 0, r.x[ks]);
+                k4_vec(bb, b_off, 4u * (unsigned)kb, 1, r.x[ks]);
             } else
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
@@ -281,9 +282,9 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     constexpr bool TINY = ITEMS == 1;
     constexpr int RATE = SPAN >= 12 ? 1 : 4;                             // pieces of a load per slot, eight in all
     static_assert(SLOTS % SPLITS == 0 && SPAN >= 3, "a split's three stores come before the end of the slab");
-    // the order of the splits (A's units 0, 1, ..; -1: B's second step; -2: B's first step, which always comes last: the
-    // registers it goes to are in use until the second step begins)
-    constexpr auto split_at = [](int n) { return KS == 1 ? (n < IT ? n : -2) : IT == 1 ? (n == 0 ? -1 : n == 1 ? 0 : -2) : (n == 0 ? 0 : n == 1 ? -1 : n + 1 < SPLITS ? n - 1 : -2); };
+    // the order of the splits (A's units 0, 1, ..; -1: B's second step, which comes first; -2: B's first step, which always comes
+    // last: the registers it goes to are in use until the second step begins)
+    constexpr auto split_at = [](int n) { return n + 1 == SPLITS ? -2 : KS == 1 ? n : n - 1; };
     // (A second set of raw registers, so that a slab's loads have two slabs to arrive in, is slower in every tile: 64x128 DW 38.1 us
     // -> 51.0, 32x32 input gradient 777->333 7.9 -> 8.7.)
     RawA ra;
