@@ -465,12 +465,17 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
     // all LDS stores) the ones at the end wait for LDS and hold back the matrix instructions behind them.  Burst / spread, us:
     // forward 784->1024, 16 workers, 128 rows, 64x64 tiles 31.0 / 28.7; 3072->2048, 32, 100, 112x128 tiles 365 / 323;
     // 3072->2048, 8, 256, 128x128 tiles 203 / 188; input gradient 1024->1024, 16, 128 38.6 / 35.7.
-    auto spread_slab = [&](int buf, auto loads, int k0, f32x4 (&ra)[IT_A], f32x4 (&rb)[IT_B], const f32x4 (&sa)[IT_A], const f32x4 (&sb)[IT_B], auto clamp) {
-        constexpr bool CLAMP = decltype(clamp)::value, LOADS = decltype(loads)::value;
+    // Not for weight gradients: both of their operands go to LDS in 128-bit stores, a burst of four to eight, and their sums are
+    // a few slabs long, so that what counts is how early the loads go out.  Time spread / burst over 3 000 products of 17 to 2048
+    // columns, 2 to 32 workers, 16 to 256 rows: 64x64 tiles 0.96 to 1.09, median 1.01, 128x32 tiles 1.02 to 1.08, median 1.04.
+    constexpr bool SPREAD = A_LAYOUT == K_CONTIG;
+    auto spread_slab = [&](int buf, auto loads, int k0, f32x4 (&ra)[IT_A], f32x4 (&rb)[IT_B], const f32x4 (&sa)[IT_A], const f32x4 (&sb)[IT_B]) {
+        static_assert(SPREAD, "no ones vector to put in A's place");
+        constexpr bool LOADS = decltype(loads)::value;
         constexpr int STEPS = BK / KSTEP, MM = TM * TN, SLOTS = STEPS * MM, READS = TM + TN, DIST = (MM == 1) ? 2 : 1;
         // the loads go out over the first half of the slab, the LDS stores (four per k-contiguous chunk, one per other chunk) over
         // the second
-        constexpr int OA = A_LAYOUT == K_CONTIG ? 4 : 1, OB = B_LAYOUT == K_CONTIG ? 4 : 1, STORES = OA * IT_A + OB * IT_B;
+        constexpr int OA = 4, OB = B_LAYOUT == K_CONTIG ? 4 : 1, STORES = OA * IT_A + OB * IT_B;
         constexpr int FIRST = SLOTS / 2;
         const float *as = &As[buf][frag_k * PITCH_A + wm0 + frag_x], *bs = &Bs[buf][frag_k * PITCH_B + wn0 + frag_x];
         float a[DIST + 1][TM], b[DIST + 1][TN];
@@ -483,21 +488,11 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
             const int it = o < OA * IT_A ? o / OA : (o - OA * IT_A) / OB;
             if (o < OA * IT_A) {
                 if (CHUNKS_A % NTHREADS != 0 && tid + it * NTHREADS >= CHUNKS_A) return;
-                if (A_LAYOUT == K_CONTIG) {
-                    As[buf ^ 1][a_dst[it] + (o % 4) * PITCH_A] = (CLAMP && !a_ok[it]) ? 0.f : sa[it][o % 4];
-                } else {
-                    f32x4 v = sa[it];
-                    if (CLAMP && !a_ok[it]) {
-                        const int m_chunk = m0 + 4 * ((tid + it * NTHREADS) % (BM / 4));
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) v[q] = (m_chunk + q == p.a_ones) ? 1.f : 0.f;
-                    }
-                    *reinterpret_cast<f32x4 *>(&As[buf ^ 1][a_dst[it]]) = v;
-                }
+                As[buf ^ 1][a_dst[it] + (o % 4) * PITCH_A] = sa[it][o % 4];
             } else {
                 if (CHUNKS_B % NTHREADS != 0 && tid + it * NTHREADS >= CHUNKS_B) return;
-                if (B_LAYOUT == K_CONTIG) Bs[buf ^ 1][b_dst[it] + (o - OA * IT_A) % 4 * PITCH_B] = (CLAMP && !b_ok[it]) ? 0.f : sb[it][(o - OA * IT_A) % 4];
-                else *reinterpret_cast<f32x4 *>(&Bs[buf ^ 1][b_dst[it]]) = (CLAMP && !b_ok[it]) ? f32x4{0.f, 0.f, 0.f, 0.f} : sb[it];
+                if (B_LAYOUT == K_CONTIG) Bs[buf ^ 1][b_dst[it] + (o - OA * IT_A) % 4 * PITCH_B] = sb[it][(o - OA * IT_A) % 4];
+                else *reinterpret_cast<f32x4 *>(&Bs[buf ^ 1][b_dst[it]]) = sb[it];
             }
         };
         auto load = [&](int it) {
@@ -615,22 +610,34 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
         // The steady state proper: every slab it loads or stores lies fully inside the operands, so it contains
         // nothing of the partial-slab handling (which the compiler otherwise folds into the loop as selects and
         // per-lane address arithmetic on every slab; the vector unit is what the MFMAs wait for).
-        // (one copy of the loop per kind of tile, so that the kind is not a branch, and a register merge, per slab)
-        auto steady = [&](auto clamp) {
+        if constexpr (SPREAD) {
             for (; s + 3 < n_full; s += 2) {
-                spread_slab(0, std::true_type{}, k_begin + (s + 2) * BK, ra0, rb0, ra1, rb1, clamp);
+                spread_slab(0, std::true_type{}, k_begin + (s + 2) * BK, ra0, rb0, ra1, rb1);
                 __syncthreads();
-                spread_slab(1, std::true_type{}, k_begin + (s + 3) * BK, ra1, rb1, ra0, rb0, clamp);
+                spread_slab(1, std::true_type{}, k_begin + (s + 3) * BK, ra1, rb1, ra0, rb0);
                 __syncthreads();
             }
-        };
-        if (inner_tile) steady(std::false_type{});
-        else steady(std::true_type{});
+        } else {
+            // (one copy of the loop per kind of tile, so that the kind is not a branch, and a register merge, per slab)
+            auto steady = [&](auto clamp) {
+                for (; s + 3 < n_full; s += 2) {
+                    load_fast(k_begin + (s + 2) * BK, ra0, rb0);
+                    multiply_slab(0, BK, [&] { store_lds(1, ra1, rb1, decltype(clamp)::value); });
+                    __syncthreads();
+                    load_fast(k_begin + (s + 3) * BK, ra1, rb1);
+                    multiply_slab(1, BK, [&] { store_lds(0, ra0, rb0, decltype(clamp)::value); });
+                    __syncthreads();
+                }
+            };
+            if (inner_tile) steady(std::false_type{});
+            else steady(std::true_type{});
+        }
         // slab s, and slab t behind it on its way to LDS, which may be the partial last one
         auto last_slab = [&](int buf, int t, f32x4 (&sa)[IT_A], f32x4 (&sb)[IT_B]) {
-            if (!ANY_WIDTH && t >= n_full) fix_tail(k_begin + t * BK, sa, sb);
-            if (inner_tile) spread_slab(buf, std::false_type{}, 0, sa, sb, sa, sb, std::false_type{});
-            else spread_slab(buf, std::false_type{}, 0, sa, sb, sa, sb, std::true_type{});
+            if constexpr (SPREAD) {
+                if (!ANY_WIDTH && t >= n_full) fix_tail(k_begin + t * BK, sa, sb);
+                spread_slab(buf, std::false_type{}, 0, sa, sb, sa, sb);
+            } else multiply_slab(buf, BK, [&] { store_slab(buf ^ 1, t, sa, sb); });
         };
         // the same with the partial last slab allowed (at most one more trip)
         for (; s + 3 < n_pipe; s += 2) {
