@@ -468,7 +468,9 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
     // Not for weight gradients: both of their operands go to LDS in 128-bit stores, a burst of four to eight, and their sums are
     // a few slabs long, so that what counts is how early the loads go out.  Time spread / burst over 3 000 products of 17 to 2048
     // columns, 2 to 32 workers, 16 to 256 rows: 64x64 tiles 0.96 to 1.09, median 1.01, 128x32 tiles 1.02 to 1.08, median 1.04.
-    constexpr bool SPREAD = A_LAYOUT == K_CONTIG;
+    // Nor for the last slabs of an input gradient, which load nothing (both operands go to LDS in four scattered stores per 128 bits):
+    // spread / burst 1.01 to 1.03 below sums of 128 (all of their slabs), 1.00 above.
+    constexpr bool SPREAD = A_LAYOUT == K_CONTIG, SPREAD_LAST = SPREAD && B_LAYOUT == MN_CONTIG;
     auto spread_slab = [&](int buf, auto loads, int k0, f32x4 (&ra)[IT_A], f32x4 (&rb)[IT_B], const f32x4 (&sa)[IT_A], const f32x4 (&sb)[IT_B]) {
         static_assert(SPREAD, "no ones vector to put in A's place");
         constexpr bool LOADS = decltype(loads)::value;
@@ -634,7 +636,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
         }
         // slab s, and slab t behind it on its way to LDS, which may be the partial last one
         auto last_slab = [&](int buf, int t, f32x4 (&sa)[IT_A], f32x4 (&sb)[IT_B]) {
-            if constexpr (SPREAD) {
+            if constexpr (SPREAD_LAST) {
                 if (!ANY_WIDTH && t >= n_full) fix_tail(k_begin + t * BK, sa, sb);
                 spread_slab(buf, std::false_type{}, 0, sa, sb, sa, sb);
             } else multiply_slab(buf, BK, [&] { store_slab(buf ^ 1, t, sa, sb); });
