@@ -513,10 +513,21 @@ static void launch_split_pair_dw_dw(GemmArgs d0, GemmArgs d1, hipStream_t s)
     EASGD_LAUNCH((gemm_split_dw_pair_kernel<2, 4, 1, EPI>), dim3(n0 + n1 + d0.mean.blocks), dim3(256), 0, s, d0, d1, n0);
 }
 
-// Weight gradients of at most 32 columns: narrow_dw.h or the 128x32 tile (same bits).  us, 128x32 / narrow (layer, workers, rows;
-// plain gradients): 784->10, 4, 64 5.9 / 3.5 (with momentum 7.0 / 4.2), 2048->10, 32, 100 15.1 / 9.2, 3072->10, 32, 256 45.2 / 24.8,
-// 2047->17, 20, 77 9.9 / 9.2; with 128-bit loads 3072->12, 8, 128 6.0 / 5.8, but 1024->32, 32, 256 13.3 / 19.7.
-static bool narrow_dw_fits(const GemmArgs &a, bool vec) { return a.N <= 16 || (a.N <= 32 && !vec); }
+// Weight gradients of at most 32 columns: narrow_dw.h or the 128x32 tile (same bits).  A wavefront of the first covers sixteen rows
+// and reads all of dZ for them, one of the second thirty-two from LDS: the first wins where the launch is bound by latency, and
+// loses where many wavefronts share a compute unit.  us, 128x32 / narrow (layer, workers, rows; plain gradients): 784->10, 4, 64
+// 5.9 / 3.5 (with momentum 7.0 / 4.2), 2048->10, 32, 100 15.1 / 9.2, 3072->10, 32, 256 45.2 / 24.8, 2047->17, 20, 77 9.9 / 9.2.
+// Time narrow / 128x32 over 2 000 products by blocks of 64 rows per compute unit, at sums below 128 and above:
+//   at most 16 columns   128-bit loads ruled out   0.35 to 0.86 everywhere
+//                        128-bit loads             up to 1: 0.66 to 0.84, 0.68 to 0.82; above: 0.74 to 0.92, 0.93 to 1.17
+//   17 to 32 columns     128-bit loads ruled out   up to 3: 0.57 to 0.99; above: 0.88 to 1.14
+//                        128-bit loads             1024->32, 32 workers, 256 rows 13.3 us / 19.7
+static bool narrow_dw_fits(const GemmArgs &a, bool vec)
+{
+    const size_t cus = (size_t)num_cus(), blocks = (size_t)((a.M + 63) / 64) * (size_t)a.P;
+    if (a.N <= 16) return !vec || blocks <= cus || a.K <= 128;
+    return a.N <= 32 && !vec && blocks <= 3 * cus;
+}
 
 template <int TN, int EPI>
 static void launch_narrow_dw(const GemmArgs &a_in, hipStream_t s)
@@ -1004,7 +1015,7 @@ static int grad_impl(const char *name, const int *dims, int n_layers, const floa
                             if (fp32_pair) launch_pair_da_narrow_dw<E, DW>(a, held.a, s);
                             else launch_split_pair_da_narrow_dw<E, DW>(a, held.a, pick, s);
                         };
-                        if (held.a.N <= 16) launch(std::integral_constant<int, DW_NARROW16>{});
+                        if (held.a.N <= 16 && narrow_dw_fits(held.a, held.vec)) launch(std::integral_constant<int, DW_NARROW16>{});
                         else if (held.vec) launch(std::integral_constant<int, DW_128x32_VEC>{});
                         else launch(std::integral_constant<int, DW_128x32>{});
                     });

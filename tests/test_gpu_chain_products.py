@@ -129,3 +129,42 @@ def test_narrow_weight_gradients_element_by_element(d_in, d_out, P, b):
     A[:, b - 1, 0] = np.inf
     got = product(A).reshape(P, d_in + 1, d_out)
     assert not np.isfinite(got[:, 0]).any() and np.isfinite(got[:, 1:]).all()
+
+
+# (d_in, d_out, P, b): more blocks of 64 rows than one (three) per compute unit, which take the 128x32 tile; four workers of them
+# take the narrow kernel
+MANY_NARROW = [(640, 12, 24, 132), (640, 16, 24, 192), (1023, 17, 50, 37), (1022, 32, 50, 65)]
+
+
+@pytest.mark.parametrize("d_in,d_out,P,b", MANY_NARROW, ids=lambda v: str(v))
+def test_narrow_weight_gradients_keep_the_bits_of_the_128x32_tile(d_in, d_out, P, b):
+    import paper_1708_02983_amd as hip
+    A, Z = torch.randn((P, b, d_in), device="cuda"), torch.randn((P, b, d_out), device="cuda")
+    width = (d_in + 1) * d_out
+
+    def product(P):
+        out = torch.full((P, width), float("nan"), device="cuda")
+        hip.easgd_layer_product(1, d_in, d_out, A[:P], out, dZ=Z[:P], out_ws=width)
+        return to_host(out)
+
+    np.testing.assert_array_equal(product(P)[:4], product(4))
+
+
+def test_shared_launches_keep_the_bits_of_either_narrow_form():
+    """The last layer's weight gradient in the launch of the hidden layer's input gradient: the 128x32 tile for all workers, the
+    narrow kernel for four of them."""
+    import paper_1708_02983_amd as hip
+    dims, P, b = (20, 48, 640, 12), 24, 132
+    N, last = workloads.mlp_num_params(dims), 641 * 12
+    ld = (N + 3) // 4 * 4
+    W, X = torch.randn((P, ld), device="cuda") * 0.1, torch.rand((P, b, 20), device="cuda")
+    y = torch.randint(0, 12, (P, b), dtype=torch.int32, device="cuda")
+
+    def grad(P):
+        G = torch.full((P, ld), float("nan"), device="cuda")
+        hip.easgd_grad(dims, W[:P], X[:P], y[:P], G)
+        return to_host(G)[:, N - last:N]
+
+    got = grad(P)
+    assert np.isfinite(got).all()
+    np.testing.assert_array_equal(got[:4], grad(4))
