@@ -369,14 +369,18 @@ static SplitPick split_pick(const GemmArgs &a, bool forward, bool vec, bool any_
 // Which tile of gemm_chain.h takes the place of the fp32 instruction's 64x64 tile: rows x columns, or none.
 enum ChainPick { CHAIN_NONE, CHAIN_32x32, CHAIN_16x64, CHAIN_32x64 };
 
-// All of them give the same bits, so only time counts: a launch takes a + r (c + d K) us, where r is the number of blocks per
-// compute unit, rounded up.  The constants are fitted to 150 products of forward and backward propagation of up to 640 64x64
-// tiles, sums of 48 to 3072 (each tile's time met to 6 %; the tile that is picked is never slower than the 64x64 tile and
-// at most 7 % slower than the best one).  us, 64x64 / 32x32 / 16x64 / 32x64 (64x32 is almost never the best):
+// All of them give the same bits, so only time counts: a launch takes a + b r + (c + d r) K us, where r is the number of blocks per
+// compute unit, rounded up, and K the length of the sum (for the chain tiles in whole slabs of 64).  The constants are fitted to
+// 9 600 products of forward and backward propagation of up to 900 64x64 tiles, sums of 48 to 3072, each timed in all four tiles
+// on operands that are not in a cache; r up to 3 (32x64 and 64x64) or 4.  Half of the times are met to 3 % and nine of ten to
+// 9 % (16x64: 11 %), so a chain tile has to promise 3 % over the 64x64 tile: it then is more than 2 % slower in one of 200 of
+// the products that come here, and 12 % at most (several blocks per unit, sums below 330).  us, 64x64 / 32x32 / 16x64 / 32x64 (64x32
+// is almost never the best):
 //   forward         784-> 500,  8 workers,  50 rows     18.2 /  8.7 /  9.3 / 11.9
 //                  1023-> 777,  6,  37                  23.2 / 14.3 / 10.4 / 14.1
 //                   784->1520,  4,  64                  18.3 / 13.4 / 14.6 / 12.3
 //                  3072-> 427,  7,  38                  59.5 / 20.3 / 21.0 / 33.7
+//                   208-> 944, 13, 151                  15.1 / 18.6 / 22.8 / 17.2    (stays)
 //                   784-> 640, 12, 100                  18.5 / 22.7 / 25.3 / 21.1    (stays)
 //   input gradient   95-> 222,  6, 132                  12.9 /  4.4 /  4.8 /  5.9    (no 128-bit loads for 64x64)
 //                  1024-> 100, 32,  64                   9.4 / 14.5 / 18.1 / 13.9    (stays)
@@ -386,12 +390,13 @@ static ChainPick chain_pick(const GemmArgs &a, bool forward, bool vec)
     const size_t cus = (size_t)num_cus();
     auto blocks = [&](int bm, int bn) { return (size_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * (size_t)a.P * (size_t)a.splits; };
     if (2 * blocks(64, 64) > 5 * cus) return CHAIN_NONE;
-    const double K = std::min(a.K, a.k_per_split);
-    auto time = [&](int bm, int bn, double start, double per_round, double per_k) {
-        return start + (double)((blocks(bm, bn) + cus - 1) / cus) * (per_round + per_k * K);
+    const int sum = std::min(a.K, a.k_per_split);
+    auto time = [&](int bm, int bn, int slab, double a0, double b, double c, double d) {
+        const double r = (double)((blocks(bm, bn) + cus - 1) / cus), K = (double)((sum + slab - 1) / slab * slab);
+        return a0 + b * r + (c + d * r) * K;
     };
     // input gradients that rule out 128-bit loads on the 64x64 path take about twice as long there
-    double best = time(64, 64, 2.33, 0.66, 0.0190) * (!forward && !vec ? 2 : 1);
+    double best = 0.97 * (!forward && !vec ? time(64, 64, 1, 3.6, -0.1, 0.0120, 0.0317) : time(64, 64, 1, 2.7, 1.0, 0.0028, 0.0148));
     ChainPick pick = CHAIN_NONE;
     auto consider = [&](ChainPick t, double us) {
         if (us < best) {
@@ -399,9 +404,9 @@ static ChainPick chain_pick(const GemmArgs &a, bool forward, bool vec)
             pick = t;
         }
     };
-    consider(CHAIN_32x32, time(32, 32, 3.02, 0.21, 0.00525));
-    consider(CHAIN_16x64, time(16, 64, 3.06, 0.30, 0.00610));
-    consider(CHAIN_32x64, time(32, 64, 3.04, 0.47, 0.00936));
+    consider(CHAIN_32x32, time(32, 32, 64, 2.6, 0.64, 0.0004, 0.0049));
+    consider(CHAIN_16x64, time(16, 64, 64, 2.6, 0.82, 0.0002, 0.00565));
+    consider(CHAIN_32x64, time(32, 64, 64, 2.25, 1.15, 0.0015, 0.0084));
     return pick;
 }
 

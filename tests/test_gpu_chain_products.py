@@ -25,7 +25,8 @@ def _with_tile(hip, tile, f):
 NETWORKS = [
     ((63, 33, 10), 2, 1), ((64, 48, 10), 3, 15), ((65, 65, 10), 2, 16),           # 32x32; sums of 64, 65, 66
     ((784, 500, 300, 10), 8, 50), ((255, 34, 257, 12), 5, 33), ((511, 130, 3), 4, 65),
-    ((1023, 777, 333, 7), 6, 37), ((300, 1009, 10), 5, 48), ((129, 1000, 16), 5, 17),   # 16x64
+    ((1023, 777, 333, 7), 6, 37), ((300, 1009, 10), 5, 48),                             # 16x64 (and 32x32 for 777->333)
+    ((129, 1000, 16), 5, 17),                                                           # 32x32
     ((156, 1041, 10), 13, 17), ((129, 1520, 10), 4, 63), ((256, 513, 10), 7, 65),       # 32x64
     ((784, 640, 10), 12, 100),                                                          # the 64x64 tile itself
 ]
@@ -55,9 +56,15 @@ def test_hidden_layers_keep_the_bits_of_the_64x64_tile(dims, P, b):
     assert np.isfinite(g).all() and (g != 0).any()
 
 
-# (d_in, d_out, P, b): sums too short for the split form; 32x32, 16x64, 32x64 and the 64x64 tile itself
-INPUT_GRADIENTS = [(47, 2, 3, 1), (64, 31, 2, 16), (97, 36, 4, 33), (300, 64, 3, 37), (641, 68, 6, 37),
-                   (321, 63, 24, 1), (321, 64, 24, 17), (353, 100, 23, 17), (1024, 48, 16, 128)]
+# (d_in, d_out, P, b): sums too short for the split form
+INPUT_GRADIENTS = [(64, 31, 2, 16), (97, 36, 4, 33), (300, 64, 3, 37), (641, 68, 6, 37),         # 32x32
+                   (321, 64, 24, 17), (353, 100, 23, 17),                                        # 32x64
+                   (47, 2, 3, 1), (1024, 48, 16, 128),                                           # the 64x64 tile itself
+                   (321, 63, 24, 1),                                                             # 32x32 of the split form
+                   # one to six slabs of 64, with 128-bit loads on the 64x64 path and without (sums below 40)
+                   (828, 100, 3, 63), (403, 204, 19, 87), (1302, 33, 3, 43),                                # 32x32
+                   (1766, 80, 20, 9), (995, 108, 15, 13), (767, 324, 11, 46), (1517, 312, 6, 45), (1062, 39, 13, 14),   # 16x64
+                   (940, 172, 12, 31), (1752, 244, 5, 94), (901, 224, 9, 78), (1074, 248, 16, 70), (1768, 39, 18, 32)]  # 32x64
 
 
 @pytest.mark.parametrize("d_in,d_out,P,b", INPUT_GRADIENTS, ids=lambda v: str(v))
@@ -83,12 +90,13 @@ def test_short_sums_of_input_gradients_keep_the_bits_of_the_64x64_tile(d_in, d_o
         np.testing.assert_array_equal(got[:, :b * d_in], ref[:, :b * d_in])
 
 
+# 32x32 forward and, at a sum of 50, the split form's input gradient; 32x32, 16x64 and 32x64 input gradients
+@pytest.mark.parametrize("d_in,d_out,P,b", [(65, 50, 3, 17), (65, 34, 3, 17), (1062, 39, 13, 14), (1768, 39, 18, 32)], ids=lambda v: str(v))
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
-def test_what_lies_behind_a_row_does_not_reach_a_sum(bad):
+def test_what_lies_behind_a_row_does_not_reach_a_sum(bad, d_in, d_out, P, b):
     """A 128-bit load at the end of a row brings the values behind it, and the last slab of a sum those of the next layer: none of
     them may meet a zero in a product (0 * inf is NaN)."""
     import paper_1708_02983_amd as hip
-    d_in, d_out, P, b = 65, 50, 3, 17
     rng = np.random.default_rng(3)
     A, Z = rng.standard_normal((P, b, d_in)).astype(F), rng.standard_normal((P, b, d_out)).astype(F)
     block = (d_in + 1) * d_out
@@ -129,6 +137,45 @@ def test_narrow_weight_gradients_element_by_element(d_in, d_out, P, b):
     A[:, b - 1, 0] = np.inf
     got = product(A).reshape(P, d_in + 1, d_out)
     assert not np.isfinite(got[:, 0]).any() and np.isfinite(got[:, 1:]).all()
+
+
+# (kind, d_in, d_out, P, b): several blocks of a small tile per compute unit, at short sums, where the 64x64 tile is faster
+SEVERAL_BLOCKS = [(0, 65, 1326, 27, 34), (0, 80, 1168, 8, 193), (2, 560, 64, 29, 115), (2, 896, 96, 10, 229)]
+
+
+@pytest.mark.parametrize("kind,d_in,d_out,P,b", SEVERAL_BLOCKS, ids=lambda v: str(v))
+def test_the_tile_that_is_picked_is_not_slower_than_the_64x64_tile(kind, d_in, d_out, P, b):
+    """Small tiles took 1.5 to 1.8 times as long here.  Launches in a graph, both sides in turn, the best of nine; two runs of one side
+    differ by a few percent."""
+    import paper_1708_02983_amd as hip
+    ld = (d_in + 1) * d_out
+    A, W, Z = (torch.randn(s, device="cuda") for s in ((P, b, d_in), (P, ld), (P, b, d_out)))
+    width = b * (d_out if kind == 0 else d_in)
+    out = torch.empty((P, width), device="cuda")
+
+    def product():
+        hip.easgd_layer_product(kind, d_in, d_out, A, out, Wl=W, dZ=Z, ld=ld, out_ws=width, relu=kind == 0)
+
+    def graph():
+        product()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for _ in range(40): product()
+        return g
+
+    sides = [graph(), _with_tile(hip, 2, graph)]
+    best = [float("inf"), float("inf")]
+    for _ in range(9):
+        for i, g in enumerate(sides):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            g.replay()
+            e0.record()
+            g.replay()
+            e1.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], e0.elapsed_time(e1))
+    assert best[0] < 1.2 * best[1], best
 
 
 # (d_in, d_out, P, b): more blocks of 64 rows than one (three) per compute unit, which take the 128x32 tile; four workers of them
