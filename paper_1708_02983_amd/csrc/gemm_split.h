@@ -101,7 +101,7 @@ struct SplitTile {
     static constexpr int LDS_VECS = 2 * SLAB_VECS > EXCHANGE_VECS ? 2 * SLAB_VECS : EXCHANGE_VECS;
 };
 
-template <int TM, int WN, int WK, int A_LAYOUT, int B_LAYOUT, int EPI>
+template <int TM, int WN, int WK, int A_LAYOUT, int B_LAYOUT, int EPI, bool EARLY = false>
 __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bid, u32x4 *__restrict__ lds)
 {
     typedef SplitTile<TM, WN, WK> T;
@@ -267,24 +267,34 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     };
 
     // Slab s is multiplied from LDS buffer s % 2, tile by tile and step by step ("items" of six matrix instructions, "slots").
-    // What prepares the slabs behind it runs between the matrix instructions, evenly spread, since a vector instruction takes an
-    // eighth of a matrix instruction's time and a wavefront issues in order: one split after the other (the slab's second
-    // step of B, slab s+1 of A on its way to the other LDS buffer, slab s+1's first step of B), SPAN slots each; the
-    // LDS stores and the loads of the raw registers that a split has used up in the slots behind it.  In bursts (a split within
-    // six slots, then its stores and loads) / spread, us: forward 3072->2048, 8 workers, 256 rows 137 / 127; input gradient
-    // 2048->2048, 32, 100 198 / 193; forward 784->1024, 16, 128 in 64x128 tiles 27.6 / 26.6, 1024->1024, 16, 128 (input gradient) 32.2 / 31.8.
-    // What is left of the first of these over its matrix instructions (83 us) is the loads and LDS stores: without loads
-    // from memory it takes 125, without LDS stores 116, without either and with a third of the LDS reads 102.
+    // What prepares the slabs behind it runs between the matrix instructions, spread over them, since a vector instruction takes an
+    // eighth of a matrix instruction's time and a wavefront issues in order: each split (the slab's second step of B, slab s+1 of A
+    // on its way to the other LDS buffer, slab s+1's first step of B) has a span of slots; the LDS stores and the loads of the raw
+    // registers that a split has used up follow in the slots behind it.
+    // The large tiles take one split after the other, and load B's first step in the first slots of the next slab.  In bursts (a
+    // split within six slots, then its stores and loads) / spread, us: forward 3072->2048, 8 workers, 256 rows 150 / 141; input
+    // gradient 2048->2048, 32, 100 199 / 193; forward 784->1024, 16, 128 in 64x128 tiles 27.6 / 26.6, 1024->1024, 16, 128 (input
+    // gradient) 32.2 / 31.8.  What is left of the first of these over its matrix instructions (83 us) is the loads and LDS
+    // stores: without loads from memory it takes 125, without LDS stores 116, without either and with a third of the LDS reads 102.
+    // In the small tiles a slab's twelve or six slots are shorter than a trip to memory, and where the operands come from far or few
+    // wavefronts share a compute unit, what counts is that the trips of A and B overlap: both loads go out before either is
+    // waited for.  Time over that of the bursts (products of 64 to 3072 inputs, 48 to 2048 outputs, 2 to 32 workers, 16 to 256 rows):
+    //   64x64, one after the other   0.84 to 1.11 forward, 0.88 to 1.12 input gradients
+    //   64x64, EARLY                 0.95 to 1.01          0.96 to 1.02     (faster where split_early says so)
+    //   32x128 forward               0.95 to 1.10 one after the other, 0.97 to 1.03 EARLY      (the same)
+    //   32x32 input gradients        0.94 to 1.06 both splits over all six slots, 0.95 to 1.02 in this order
     constexpr int ITEMS = KS * TM, SLOTS = 6 * ITEMS, SPLITS = KS + IT, SPAN = SLOTS / SPLITS;
-    // The smallest tile has six slots: its two splits share them all, stores and loads follow behind the last (forward 988->1514,
-    // 8 workers, 17 rows 16.4 us against 17.0 with the splits one after the other, 3072->593, 3, 16 31.9 against 34.7; but 784->500, 8, 50 11.4
-    // against 10.4, whose weights come from the L2).
-    constexpr bool TINY = ITEMS == 1;
+    constexpr bool FORWARD = A_LAYOUT == K_CONTIG && B_LAYOUT == MN_CONTIG;
+    constexpr bool TINY = ITEMS == 1;                                    // the 32x32 tile
+    constexpr bool B_BEHIND = TINY || EARLY;                    // B's first step is loaded right behind its split
     constexpr int RATE = SPAN >= 12 ? 1 : 4;                             // pieces of a load per slot, eight in all
+    static_assert(!EARLY || SLOTS == 12, "the 64x64 and 32x128 tiles");
     static_assert(SLOTS % SPLITS == 0 && SPAN >= 3, "a split's three stores come before the end of the slab");
-    // the order of the splits (A's units 0, 1, ..; -1: B's second step, which comes first; -2: B's first step, which always comes
-    // last: the registers it goes to are in use until the second step begins)
+    // the splits in order (A's units 0, 1, ..; -1: B's second step, whose registers are in use from the second step on; -2: B's first
+    // step, whose registers are free from the second step on, or a second set where there is one step)
     constexpr auto split_at = [](int n) { return n + 1 == SPLITS ? -2 : KS == 1 ? n : n - 1; };
+    constexpr auto first_slot = [](int n) { return TINY ? (FORWARD || n == 1 ? 0 : 1) : EARLY ? (KS == 1 ? 6 * n : 3 * n) : SPAN * n; };
+    constexpr auto slots_of = [](int) { return TINY ? (FORWARD ? 6 : 5) : EARLY ? (KS == 1 ? 4 : 3) : SPAN; };
     // (A second set of raw registers, so that a slab's loads have two slabs to arrive in, is slower in every tile: 64x128 DW 38.1 us
     // -> 51.0, 32x32 input gradient 777->333 7.9 -> 8.7.)
     RawA ra;
@@ -306,7 +316,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     }
     if (!whole(0)) cut_b(0, 0, rb);
     split8(rb.x[0], fb[0]);
-    if constexpr (TINY) load_b_step(1, std::false_type{}, 0, 0, rb);
+    if constexpr (B_BEHIND) load_b_step(1, std::false_type{}, 0, 0, rb);
     __syncthreads();
     auto slab = [&](int s, auto parity, auto last_slabs) {
         constexpr int buf = decltype(parity)::value;
@@ -320,60 +330,53 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
         for (int plane = 0; plane < 3; ++plane) fetch(buf, 0, 0, plane, fa[0]);
         static_for<SLOTS>([&](auto slot_) {
             constexpr int slot = decltype(slot_)::value, it = slot / 6, part = slot % 6, ks = it / TM, i = it % TM;
-            constexpr int n = slot / SPAN, u = split_at(n), q0 = (slot % SPAN * SPLIT_PARTS + SPAN - 1) / SPAN;     // split n from part q0 on
             // a step without a k of its own holds zeros only
             const int k_step = start(s) + 16 * (wk + ks * WK);
             const bool live = !LAST || (k_step < k_end && k_step + 16 > k_begin + s * BK);  // uniform
-            if constexpr (LAST && TINY && slot == 0) {
-                if (!whole(s + 1)) { cut_a(s + 1, 0, ra); cut_b(s + 1, 0, rb); }
-            } else if constexpr (LAST && !TINY && slot % SPAN == 0) {
-                if constexpr (u == -1) { if (!whole(s)) cut_b(s, KS - 1, rb); }
-                else if constexpr (u == -2) { if (!whole(s + 1)) cut_b(s + 1, 0, rb); }
-                else if (!whole(s + 1)) cut_a(s + 1, u, ra);
-            }
+            if constexpr (LAST)
+                static_for<SPLITS>([&](auto n_) {
+                    constexpr int n = decltype(n_)::value, u = split_at(n);
+                    if constexpr (first_slot(n) == slot) {
+                        if constexpr (u == -1) { if (!whole(s)) cut_b(s, KS - 1, rb); }
+                        else if constexpr (u == -2) { if (!whole(s + 1)) cut_b(s + 1, 0, rb); }
+                        else if (!whole(s + 1)) cut_a(s + 1, u, ra);
+                    }
+                });
             __builtin_amdgcn_sched_barrier(0);
             if (live) multiply(part, i, fa[it & 1], fb[ks == 0 ? F0 : 1]);
-            if constexpr (TINY) {
-#pragma unroll
-                for (int q = 2 * slot; q < 2 * slot + 2; ++q) {
-                    split_part(q, rb.x[0], fb[F1], t[0]);
-                    split_part<ONES>(q, ra.x[0], fs[0], t[1], a_mul[0], a_add[0]);
-                }
-            } else static_for<SPLIT_PARTS>([&](auto q_) {
-                constexpr int q = decltype(q_)::value;
-                if constexpr (q >= q0 && q * SPAN / SPLIT_PARTS == slot % SPAN) {
-                    if constexpr (u == -1) split_part(q, rb.x[KS - 1], fb[1], t[n]);
-                    else if constexpr (u == -2) split_part(q, rb.x[0], fb[F1], t[n]);
-                    else split_part<ONES>(q, ra.x[u], fs[u], t[n], a_mul[u], a_add[u]);
-                }
+            static_for<(SPLIT_PARTS + slots_of(0) - 1) / slots_of(0)>([&](auto j_) {
+                static_for<SPLITS>([&](auto n_) {                        // B's part before A's
+                    constexpr int n = SPLITS - 1 - decltype(n_)::value, u = split_at(n), at = slot - first_slot(n), L = slots_of(n);
+                    constexpr int q = (at * SPLIT_PARTS + L - 1) / L + decltype(j_)::value;      // split n's parts of this slot: from the first on
+                    if constexpr (at >= 0 && at < L && q < SPLIT_PARTS && q * L / SPLIT_PARTS == at) {
+                        if constexpr (u == -1) split_part(q, rb.x[KS - 1], fb[1], t[n]);
+                        else if constexpr (u == -2) split_part(q, rb.x[0], fb[F1], t[n]);
+                        else split_part<ONES>(q, ra.x[u], fs[u], t[n], a_mul[u], a_add[u]);
+                    }
+                });
             });
             if constexpr (it + 1 < ITEMS && part < 3) fetch(buf, (it + 1) / TM, (it + 1) % TM, part == 0 ? 2 : part - 1, fa[(it + 1) & 1]);
-            if constexpr (!TINY) static_for<SPLITS - 1>([&](auto m_) {
-                constexpr int m = decltype(m_)::value, v = split_at(m), after = slot - (m + 1) * SPAN;
-                if constexpr (v >= 0 && after >= 0 && after < 3) {
-                    if (!LAST || s + 1 < n_slabs) store_plane(buf ^ 1, v, after, fs[v]);
-                }
-                if constexpr (after >= 0 && after < 8 / RATE) {
-                    static_for<RATE>([&](auto r_) {
-                        constexpr int piece = after * RATE + decltype(r_)::value;
-                        if constexpr (v >= 0) load_a(s + 2, inner, v, piece, ra);
-                        else load_b_step(s + 1, inner, KS - 1, piece, rb);
-                    });
-                }
-            });
-            if constexpr (!TINY && slot < 8 / RATE)               // the registers that the slab before has used up at its end
+            if constexpr (!B_BEHIND && slot < 8 / RATE)           // the registers that the slab before has used up at its end
                 static_for<RATE>([&](auto r_) { load_b_step(s + 1, inner, 0, slot * RATE + decltype(r_)::value, rb); });
+            if constexpr (TINY && FORWARD) __builtin_amdgcn_sched_barrier(0);
+            static_for<SPLITS>([&](auto n_) {                            // what is left when the slab ends goes into its last slot
+                constexpr int n = SPLITS - 1 - decltype(n_)::value, u = split_at(n), end = first_slot(n) + slots_of(n);
+                constexpr int after = slot - (end < SLOTS ? end : SLOTS - 1);
+                constexpr bool last = slot == SLOTS - 1;
+                if constexpr (after >= 0 && u >= 0)
+                    static_for<last && after < 3 ? 3 - after : after < 3 ? 1 : 0>([&](auto i_) {
+                        if (!LAST || s + 1 < n_slabs) store_plane(buf ^ 1, u, after + decltype(i_)::value, fs[u]);
+                    });
+                if constexpr (after >= 0 && (u != -2 || B_BEHIND))
+                    static_for<last && after * RATE < 8 ? 8 - after * RATE : after * RATE < 8 ? RATE : 0>([&](auto i_) {
+                        constexpr int piece = after * RATE + decltype(i_)::value;
+                        if constexpr (u == -1) load_b_step(s + 1, inner, KS - 1, piece, rb);
+                        else if constexpr (u == -2) load_b_step(s + 2, inner, 0, piece, rb);
+                        else load_a(s + 2, inner, u, piece, ra);
+                    });
+            });
             __builtin_amdgcn_sched_barrier(0);
         });
-        if constexpr (TINY) {
-#pragma unroll
-            for (int plane = 0; plane < 3; ++plane)
-                if (!LAST || s + 1 < n_slabs) store_plane(buf ^ 1, 0, plane, fs[0]);
-#pragma unroll
-            for (int piece = 0; piece < 8; ++piece) load_b_step(s + 2, inner, 0, piece, rb);
-#pragma unroll
-            for (int piece = 0; piece < 8; ++piece) load_a(s + 2, inner, 0, piece, ra);
-        }
         __syncthreads();
     };
     constexpr std::integral_constant<int, 0> even{};
@@ -541,7 +544,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
 // Blocks per compute unit that the registers leave room for.
 template <int TM> constexpr int split_blocks_per_cu() { return TM == 1 ? 4 : TM == 2 ? 3 : 2; }
 
-template <int TM, int WN, int WK, int A_LAYOUT, int B_LAYOUT, int EPI>
+template <int TM, int WN, int WK, int A_LAYOUT, int B_LAYOUT, int EPI, bool EARLY = false>
 __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_kernel(GemmArgs p)
 {
     __shared__ u32x4 lds[SplitTile<TM, WN, WK>::LDS_VECS];
@@ -554,7 +557,7 @@ __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_ker
         mean_loss_block(p.mean, blockIdx.x - p.mean.first_block);
         return;
     }
-    split_block<TM, WN, WK, A_LAYOUT, B_LAYOUT, EPI>(p, blockIdx.x, lds);
+    split_block<TM, WN, WK, A_LAYOUT, B_LAYOUT, EPI, EARLY>(p, blockIdx.x, lds);
 }
 
 // The weight-gradient products of two layers in one launch (gemm_pair_kernel's purpose).

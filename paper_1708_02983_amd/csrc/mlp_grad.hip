@@ -364,6 +364,20 @@ static SplitPick split_pick(const GemmArgs &a, bool forward, bool vec, bool any_
     return any_length || std::min(a.K, a.k_per_split) >= least ? pick : SPLIT_NONE;
 }
 
+// Whether a 64x64 or a forward product's 32x128 split tile requests both operands of a slab before it waits for either (EARLY in
+// gemm_split.h): where the trips to memory are long, on operands and results of more than a third of the last-level cache (80 MB), or
+// bare, on a single block per compute unit; the 32x128 tile where both hold.  Time of that order over the other one on operands that
+// are not in the second-level cache, 64x64: below 80 MB and on more than one block per unit 0.95 to 1.12, elsewhere 0.89 to 1.05;
+// 32x128: 0.91 to 1.03 by this rule, 0.96 to 1.04 elsewhere.  us, one after the other / early: 3008->544, 30 workers, 53 rows 91.3 /
+// 81.9; input gradients 608->1824, 16, 114 59.8 / 53.3 and 500->641, 16, 128 20.7 / 18.5; 2924->2020, 16, 18 (32x128) 89.4 / 82.6.
+static bool split_early(const GemmArgs &a, SplitPick pick)
+{
+    const bool far = (double)a.P * ((double)a.M * a.K + (double)a.N * a.K + (double)a.M * a.N) > 20e6;
+    const int bn = pick == SPLIT_64x64 ? 64 : 128, bm = pick == SPLIT_64x64 ? 64 : 32;
+    const bool bare = (size_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * (size_t)a.P * (size_t)a.splits <= (size_t)num_cus();
+    return pick == SPLIT_64x64 ? far || bare : far && bare;
+}
+
 // ---- fp32 products of small grids (gemm_chain.h) ----
 
 // Which tile of gemm_chain.h takes the place of the fp32 instruction's 64x64 tile: rows x columns, or none.
@@ -423,7 +437,7 @@ static void launch_chain(const GemmArgs &a_in, hipStream_t s)
     EASGD_LAUNCH((gemm_chain_kernel<WM, WN, TM, BL, EPI>), dim3((unsigned)total), dim3(256), 0, s, a);
 }
 
-template <int TM, int WN, int WK, int AL, int BL, int EPI>
+template <int TM, int WN, int WK, int AL, int BL, int EPI, bool EARLY = false>
 static void launch_split(const GemmArgs &a_in, hipStream_t s)
 {
     GemmArgs a = a_in;
@@ -434,7 +448,7 @@ static void launch_split(const GemmArgs &a_in, hipStream_t s)
     }
     a.mean.first_block = (unsigned)total;
     total += a.mean.blocks;
-    EASGD_LAUNCH((gemm_split_kernel<TM, WN, WK, AL, BL, EPI>), dim3((unsigned)total), dim3(256), 0, s, a);
+    EASGD_LAUNCH((gemm_split_kernel<TM, WN, WK, AL, BL, EPI, EARLY>), dim3((unsigned)total), dim3(256), 0, s, a);
 }
 
 // Weight gradients: whether 64x128 split tiles can take the product (not on grids of less than two blocks per compute unit
@@ -600,8 +614,15 @@ static void launch_gemm(const GemmArgs &a, bool vec, hipStream_t s, Form form = 
         const SplitPick pick = form == FORM_FP32 ? SPLIT_NONE : split_pick(a, forward, vec, form == FORM_SPLIT);
         if (pick == SPLIT_128x128) launch_split<4, 4, 1, AL, BL, EPI>(a, s);
         else if (pick == SPLIT_64x128) launch_split<2, 4, 1, AL, BL, EPI>(a, s);
-        else if (pick == SPLIT_64x64) launch_split<2, 2, 2, AL, BL, EPI>(a, s);
-        else if (pick == SPLIT_32x128) launch_split<1, 4, 1, AL, BL, EPI>(a, s);
+        else if (pick == SPLIT_64x64) {
+            if (split_early(a, pick)) launch_split<2, 2, 2, AL, BL, EPI, true>(a, s);
+            else launch_split<2, 2, 2, AL, BL, EPI>(a, s);
+        } else if (pick == SPLIT_32x128) {
+            if constexpr (forward) {
+                if (split_early(a, pick)) launch_split<1, 4, 1, AL, BL, EPI, true>(a, s);
+                else launch_split<1, 4, 1, AL, BL, EPI>(a, s);
+            } else launch_split<1, 4, 1, AL, BL, EPI>(a, s);
+        }
         else if (pick == SPLIT_32x32) launch_split<1, 1, 4, AL, BL, EPI>(a, s);
         if (pick != SPLIT_NONE) return;
         int bm16 = (tile == 0) ? tile16_rows(a.M, a.N, a.P, a.splits) : 0;

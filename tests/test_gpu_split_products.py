@@ -97,6 +97,8 @@ LONG_SHAPES = [
     (300, 2048, 16, 100), (351, 2048, 16, 128), (2048, 299, 16, 100), (2048, 416, 16, 90),   # 128x128: 10, 11; 10, 13 slabs
     (500, 2048, 16, 64), (1024, 300, 16, 128), (1024, 415, 16, 100),                         # 64x128
     (415, 768, 12, 192), (768, 333, 12, 150),                                                # 64x64
+    (2100, 500, 17, 70), (500, 2101, 17, 70), (500, 641, 16, 128),                           # 64x64, both operands requested early
+    (640, 2048, 16, 20),                                                                     # 32x128, the same
     (415, 2048, 17, 32), (2048, 300, 16, 20),                                                # 32x128
     (700, 97, 5, 65), (97, 700, 5, 65),                                                      # 32x32
 ]
@@ -141,6 +143,15 @@ def test_long_sums_keep_every_part_of_either_operand(d_in, d_out, P, b):
         ref, mag, K = _products(kind, A, W, Z, d_in, d_out)
         got = _run(hip, kind, A, W, Z, d_in, d_out, W.shape[1], ref[0].size).reshape(ref.shape)
         assert (np.abs(got - ref) <= (K + 8) * 2.0 ** -24 * mag).all(), kind
+
+
+def test_64x64_tiles_keep_their_bits_in_either_order_of_the_loads():
+    """Sixteen workers have one block per compute unit and request both operands early, seventeen do not."""
+    import paper_1708_02983_amd as hip
+    d_in, d_out, P, b = 500, 641, 17, 128
+    A, W, Z, ld = _operands(d_in, d_out, P, b)
+    few = _run(hip, 2, A[:16], W[:16], Z[:16], d_in, d_out, ld, b * d_in)
+    np.testing.assert_array_equal(_run(hip, 2, A, W, Z, d_in, d_out, ld, b * d_in)[:16], few)
 
 
 RANGE_SHAPES = [(300, 2048, 16, 70), (2048, 100, 17, 40), (65, 34, 2, 17), (127, 128, 40, 31)]
