@@ -25,6 +25,7 @@
 #include "mlp_head.h"
 #include "persistent_round.h"
 #include <algorithm>
+#include <initializer_list>
 #include <mutex>
 
 // The workspace of easgd_grad_static: device memory that belongs to the library, one copy per GPU, held from
@@ -383,13 +384,12 @@ static bool split_early(const GemmArgs &a, SplitPick pick)
 // Which tile of gemm_chain.h takes the place of the fp32 instruction's 64x64 tile: rows x columns, or none.
 enum ChainPick { CHAIN_NONE, CHAIN_32x32, CHAIN_16x64, CHAIN_32x64 };
 
-// All of them give the same bits, so only time counts: a launch takes a + b r + (c + d r) K us, where r is the number of blocks per
-// compute unit, rounded up, and K the length of the sum (for the chain tiles in whole slabs of 64).  The constants are fitted to
-// 9 600 products of forward and backward propagation of up to 900 64x64 tiles, sums of 48 to 3072, each timed in all four tiles
-// on operands that are not in a cache; r up to 3 (32x64 and 64x64) or 4.  Half of the times are met to 3 % and nine of ten to
-// 9 % (16x64: 11 %), so a chain tile has to promise 3 % over the 64x64 tile: it then is more than 2 % slower in one of 200 of
-// the products that come here, and 12 % at most (several blocks per unit, sums below 330).  us, 64x64 / 32x32 / 16x64 / 32x64 (64x32
-// is almost never the best):
+// All of them give the same bits, so only time counts: a launch takes a_r + d_r K us, where r is the number of blocks per compute
+// unit, rounded up, and K the length of the sum (for the chain tiles in whole slabs of 64).  The constants are fitted to 9 600
+// products of forward and backward propagation of up to 900 64x64 tiles, sums of 48 to 3072, each timed in all four tiles
+// on operands that are not in the second-level cache.  Half of the times are met to 3 % and nine of ten to 9 % (16x64: 11 %), so a
+// chain tile has to promise 1.5 % over the 64x64 tile: it then is more than 2 % slower in one of 160 of the products that come
+// here, and 12 % at most (several blocks per unit, sums below 330).  us, 64x64 / 32x32 / 16x64 / 32x64 (64x32 is almost never the best):
 //   forward         784-> 500,  8 workers,  50 rows     18.2 /  8.7 /  9.3 / 11.9
 //                  1023-> 777,  6,  37                  23.2 / 14.3 / 10.4 / 14.1
 //                   784->1520,  4,  64                  18.3 / 13.4 / 14.6 / 12.3
@@ -404,13 +404,17 @@ static ChainPick chain_pick(const GemmArgs &a, bool forward, bool vec)
     const size_t cus = (size_t)num_cus();
     auto blocks = [&](int bm, int bn) { return (size_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * (size_t)a.P * (size_t)a.splits; };
     if (2 * blocks(64, 64) > 5 * cus) return CHAIN_NONE;
-    const int sum = std::min(a.K, a.k_per_split);
-    auto time = [&](int bm, int bn, int slab, double a0, double b, double c, double d) {
-        const double r = (double)((blocks(bm, bn) + cus - 1) / cus), K = (double)((sum + slab - 1) / slab * slab);
-        return a0 + b * r + (c + d * r) * K;
+    const int sum = std::min(a.K, a.k_per_split), slabs = (sum + 63) / 64 * 64;
+    struct Line { double a, d; };
+    // lines: r = 1, 2, ..; beyond the last one in proportion to it
+    auto time = [&](int bm, int bn, int K, std::initializer_list<Line> lines) {
+        const size_t r = (blocks(bm, bn) + cus - 1) / cus, n = std::min(r, lines.size());
+        const Line &l = lines.begin()[n - 1];
+        return (double)r / (double)n * (l.a + l.d * K);
     };
     // input gradients that rule out 128-bit loads on the 64x64 path take about twice as long there
-    double best = 0.97 * (!forward && !vec ? time(64, 64, 1, 3.6, -0.1, 0.0120, 0.0317) : time(64, 64, 1, 2.7, 1.0, 0.0028, 0.0148));
+    double best = 0.985 * (!forward && !vec ? time(64, 64, sum, {{3.54, 0.0437}, {3.19, 0.0744}, {4.91, 0.1050}})
+                                            : time(64, 64, sum, {{3.74, 0.01756}, {4.66, 0.03255}, {5.94, 0.0467}}));
     ChainPick pick = CHAIN_NONE;
     auto consider = [&](ChainPick t, double us) {
         if (us < best) {
@@ -418,9 +422,9 @@ static ChainPick chain_pick(const GemmArgs &a, bool forward, bool vec)
             pick = t;
         }
     };
-    consider(CHAIN_32x32, time(32, 32, 64, 2.6, 0.64, 0.0004, 0.0049));
-    consider(CHAIN_16x64, time(16, 64, 64, 2.6, 0.82, 0.0002, 0.00565));
-    consider(CHAIN_32x64, time(32, 64, 64, 2.25, 1.15, 0.0015, 0.0084));
+    consider(CHAIN_32x32, time(32, 32, slabs, {{3.23, 0.00535}, {3.83, 0.01042}, {4.34, 0.01542}, {5.38, 0.01977}}));
+    consider(CHAIN_16x64, time(16, 64, slabs, {{3.42, 0.00581}, {4.13, 0.01164}, {4.96, 0.0178}, {6.15, 0.02172}}));
+    consider(CHAIN_32x64, time(32, 64, slabs, {{3.42, 0.00991}, {4.34, 0.01825}, {6.2, 0.0277}, {7.5, 0.035}}));
     return pick;
 }
 

@@ -57,9 +57,9 @@ def test_hidden_layers_keep_the_bits_of_the_64x64_tile(dims, P, b):
 
 
 # (d_in, d_out, P, b): sums too short for the split form
-INPUT_GRADIENTS = [(64, 31, 2, 16), (97, 36, 4, 33), (300, 64, 3, 37), (641, 68, 6, 37),         # 32x32
+INPUT_GRADIENTS = [(47, 2, 3, 1), (64, 31, 2, 16), (97, 36, 4, 33), (300, 64, 3, 37), (641, 68, 6, 37),   # 32x32
                    (321, 64, 24, 17), (353, 100, 23, 17),                                        # 32x64
-                   (47, 2, 3, 1), (1024, 48, 16, 128),                                           # the 64x64 tile itself
+                   (1024, 48, 16, 128),                                                          # the 64x64 tile itself
                    (321, 63, 24, 1),                                                             # 32x32 of the split form
                    # one to six slabs of 64, with 128-bit loads on the 64x64 path and without (sums below 40)
                    (828, 100, 3, 63), (403, 204, 19, 87), (1302, 33, 3, 43),                                # 32x32
