@@ -574,13 +574,13 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &p, const unsigned bid
 
     // Two register stages R0/R1 and two LDS buffers: slab s sits in stage s%2 while in flight and in LDS
     // buffer s%2 while it is multiplied.  In the steady state the loads of slab s+2 are issued, slab s is
-    // multiplied and, half way through its MFMAs, slab s+1 moves registers -> LDS: a prefetch distance of two slabs,
-    // one barrier per slab.
+    // multiplied and, over the second half of its MFMAs (weight gradients: half way through them), slab s+1 moves
+    // registers -> LDS: a prefetch distance of two slabs, one barrier per slab.
     f32x4 ra0[IT_A], rb0[IT_B], ra1[IT_A], rb1[IT_B];
     int s_done = 0;
-    // The narrow tile with the worker rule in its epilogue (the weight gradient of a last layer of a few classes; a
-    // softmax regression has nothing else) is a chain of round trips to memory on a chip that is otherwise idle:
-    // operands, then the replica, center and momentum tiles.  Its epilogue's tiles are requested here, before the
+    // The narrow tile with the worker rule in its epilogue (weight gradients of 17 to 32 columns, and of fewer on large grids; the
+    // others take narrow_dw.h) is a chain of round trips to memory on a chip that is otherwise idle: operands, then the
+    // replica, center and momentum tiles.  Its epilogue's tiles are requested here, before the
     // operands, so that the two trips become one.  (The wide tiles do not do this: their launches fill the chip, and
     // requests made this early only queue ahead of the operand loads of the blocks that share the compute unit; nor
     // does a narrow product that shares its launch with a wide one, ALONE = false: the registers would cost the wide
@@ -920,20 +920,16 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, 2) void gemm_mfma_kernel(Gem
     gemm_block<BM, BN, BK, WAVES_M, WAVES_N, A_LAYOUT, B_LAYOUT, VEC, EPI, MT, true, ANY_WIDTH>(p, blockIdx.x, lds);
 }
 
-// Two independent products in one launch: blocks [0, n0) work on p0 with the first configuration, the rest on
-// p1 with the second.  The products of backward propagation are short, so sharing a launch saves a launch
-// boundary and lets the blocks of one fill the wave slots and the tail the other leaves idle.  Both
-// configurations use 256 threads; the LDS buffer is the larger of the two needs.
-template <int BM0, int BN0, int BK0, int WM0, int WN0, int AL0, int BL0, bool VEC0, int EPI0,
-          int BM1, int BN1, int BK1, int WM1, int WN1, int AL1, int BL1, bool VEC1, int EPI1>
-__global__ __launch_bounds__(256, 2) void gemm_pair_kernel(GemmArgs p0, GemmArgs p1, unsigned n0)
+// The weight-gradient products of two layers in one launch: blocks [0, n0) work on p0, the rest on p1.  The products of backward
+// propagation are short, so sharing a launch saves a launch boundary and lets the blocks of one fill the wave slots and the
+// tail the other leaves idle.
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_dw_pair_kernel(GemmArgs p0, GemmArgs p1, unsigned n0)
 {
-    static_assert(WM0 * WN0 == 4 && WM1 * WN1 == 4, "both products use 256 threads");
-    constexpr int L0 = gemm_lds_floats<BM0, BN0, BK0, AL0, BL0>(), L1 = gemm_lds_floats<BM1, BN1, BK1, AL1, BL1>();
-    __shared__ __attribute__((aligned(16))) float lds[L0 > L1 ? L0 : L1];
+    __shared__ __attribute__((aligned(16))) float lds[gemm_lds_floats<64, 64, 32, MN_CONTIG, MN_CONTIG>()];
     if (p0.mean.blocks > 0 && blockIdx.x >= p0.mean.first_block) mean_loss_block(p0.mean, blockIdx.x - p0.mean.first_block);
-    else if (blockIdx.x < n0) gemm_block<BM0, BN0, BK0, WM0, WN0, AL0, BL0, VEC0, EPI0>(p0, blockIdx.x, lds);
-    else gemm_block<BM1, BN1, BK1, WM1, WN1, AL1, BL1, VEC1, EPI1>(p1, blockIdx.x - n0, lds);
+    else if (blockIdx.x < n0) gemm_block<64, 64, 32, 2, 2, MN_CONTIG, MN_CONTIG, true, EPI>(p0, blockIdx.x, lds);
+    else gemm_block<64, 64, 32, 2, 2, MN_CONTIG, MN_CONTIG, true, EPI>(p1, blockIdx.x - n0, lds);
 }
 
 }  // namespace easgd

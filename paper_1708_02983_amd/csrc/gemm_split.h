@@ -560,7 +560,7 @@ __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_ker
     split_block<TM, WN, WK, A_LAYOUT, B_LAYOUT, EPI, EARLY>(p, blockIdx.x, lds);
 }
 
-// The weight-gradient products of two layers in one launch (gemm_pair_kernel's purpose).
+// The weight-gradient products of two layers in one launch (gemm_dw_pair_kernel's purpose).
 template <int TM, int WN, int WK, int EPI>
 __global__ __launch_bounds__(256, split_blocks_per_cu<TM>()) void gemm_split_dw_pair_kernel(GemmArgs p0, GemmArgs p1, unsigned n0)
 {

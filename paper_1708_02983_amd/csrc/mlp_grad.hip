@@ -22,6 +22,7 @@
 // Eq. (5),(6) to the layer's slice of every replica in its epilogue.
 #include "gemm_chain.h"
 #include "gemm_split.h"
+#include "shared_launches.h"
 #include "mlp_head.h"
 #include "persistent_round.h"
 #include <algorithm>
@@ -192,52 +193,13 @@ static void launch_head(HeadArgs h, hipStream_t s)
 
 enum Kind { FWD, DW, DA };
 
-// Fills in the tile counts and the die-aware block numbering of a product; returns its number of blocks.
-template <int BM, int BN>
-static unsigned place_blocks(GemmArgs &a)
-{
-    a.tiles_m = (a.M + BM - 1) / BM;
-    a.tiles_n = (a.N + BN - 1) / BN;
-    size_t total = (size_t)a.tiles_m * a.tiles_n * a.splits * a.P;
-    a.xcd_chunk = 0;
-    a.die_workers = 0;
-    a.band_log2 = 0;
-    a.band_tiles = 0;
-    if (options().gemm_xcd && total >= 64) {
-        total = (total + 7) / 8 * 8;
-        a.xcd_chunk = (int)(total / 8);
-        // a product with an elastic epilogue (it has a center): interleave the workers of a die
-        const long order = options().gemm_xcd;
-        if (a.center && a.splits == 1 && a.P % 8 == 0 && (order == 1 || order == 3)) {
-            a.die_workers = a.P / 8;
-            // bands of 8 (4, 2) tile columns when the tile columns divide into them
-            if (order == 1 && a.tiles_m > 1)
-                a.band_log2 = a.tiles_n % 8 == 0 ? 3 : a.tiles_n % 4 == 0 ? 2 : a.tiles_n % 2 == 0 ? 1 : 0;
-            a.band_tiles = a.tiles_m << a.band_log2;
-        }
-    }
-    // the kernel's divisions by multiplication: exact while dividend * divisor < 2^32
-    auto magic = [&](size_t dividend_max, int d) -> unsigned {
-        if (d <= 1 || dividend_max * (size_t)d >= ((size_t)1 << 32)) return 0u;
-        return (unsigned)((((size_t)1 << 32) + (size_t)d - 1) / (size_t)d);
-    };
-    const size_t tiles = (size_t)a.tiles_m * a.tiles_n;
-    a.magic_tiles = magic(total, (int)tiles);
-    a.magic_tiles_n = magic(tiles, a.tiles_n);
-    a.magic_die = magic(total / 8 + 1, a.die_workers);
-    a.magic_band = magic(tiles, a.band_tiles);
-    return (unsigned)total;
-}
-
 // The weight-gradient products of two layers (64x64 tiles both) in one launch: one launch boundary and one tail less.
 template <int EPI>
 static void launch_pair_dw_dw(GemmArgs d0, GemmArgs d1, hipStream_t s)
 {
     const unsigned n0 = place_blocks<64, 64>(d0), n1 = place_blocks<64, 64>(d1);
     d0.mean.first_block = n0 + n1;
-    EASGD_LAUNCH((gemm_pair_kernel<64, 64, 32, 2, 2, MN_CONTIG, MN_CONTIG, true, EPI,
-                                         64, 64, 32, 2, 2, MN_CONTIG, MN_CONTIG, true, EPI>),
-                       dim3(n0 + n1 + d0.mean.blocks), dim3(256), 0, s, d0, d1, n0);
+    EASGD_LAUNCH((gemm_dw_pair_kernel<EPI>), dim3(n0 + n1 + d0.mean.blocks), dim3(256), 0, s, d0, d1, n0);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int AL, int BL, int EPI, int MT = 32>
@@ -282,9 +244,6 @@ static int tile16_rows(int M, int N, int P, int splits)
 }
 
 // ---- products on the bfloat16 matrix cores (gemm_split.h) ----
-
-// Which tile of gemm_split.h a product takes: rows x columns, or none.
-enum SplitPick { SPLIT_NONE, SPLIT_128x128, SPLIT_64x128, SPLIT_64x64, SPLIT_32x128, SPLIT_32x32 };
 
 static bool split_fits(const GemmArgs &a, bool a_k_contig, bool b_k_contig)
 {
@@ -464,14 +423,6 @@ static bool split_dw_fits(const GemmArgs &a, bool vec)
     return options().gemm_tile == 0 && a.N > 32 && split_fits(a, false, false) && (!vec || split_dw_blocks(a) >= (size_t)(2 * num_cus()));
 }
 
-// Blocks of a narrow weight gradient that shares a launch, by its form.
-template <int DW>
-static unsigned place_narrow(GemmArgs &dw)
-{
-    if constexpr (DW == DW_NARROW16) return place_blocks<64, 16>(dw);
-    else return place_blocks<128, 32>(dw);
-}
-
 // ... and whether they are faster than the 64x64 tiles of the fp32 instruction: where the products that they multiply for
 // nothing, in half empty tiles of columns and in the last slab of 32 rows, leave them the advantage.  The same for all
 // epilogues, so that the gradient of a round is that of easgd_grad.  With 128-bit loads on the fp32 path, time of the fp32
@@ -561,38 +512,8 @@ static void launch_narrow_dw(const GemmArgs &a_in, hipStream_t s)
     EASGD_LAUNCH((narrow_dw_kernel<TN, EPI>), dim3(total + a.mean.blocks), dim3(256), 0, s, a);
 }
 
-// An input-gradient product and the weight-gradient product of a narrow layer in one launch, the first as split tiles of
-// `pick`'s shape; false: this tile has none.  DW: the form of the second.
-template <int EPI, int DW>
-static bool launch_split_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, SplitPick pick, hipStream_t s)
-{
-    auto launch = [&](auto tm, auto wn, auto wk) {
-        constexpr int TM = decltype(tm)::value, WN = decltype(wn)::value, WK = decltype(wk)::value;
-        const unsigned n_dw = place_narrow<DW>(dw), n = place_blocks<TM * 32, WN * 32>(da);
-        dw.mean.first_block = n + n_dw;
-        EASGD_LAUNCH((gemm_split_da_narrow_dw_kernel<TM, WN, WK, EPI, DW>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
-        return true;
-    };
-    constexpr std::integral_constant<int, 1> one{};
-    constexpr std::integral_constant<int, 2> two{};
-    constexpr std::integral_constant<int, 4> four{};
-    if (pick == SPLIT_64x128) return launch(two, four, one);
-    if (pick == SPLIT_64x64) return launch(two, two, two);
-    if (pick == SPLIT_32x128) return launch(one, four, one);
-    if (pick == SPLIT_32x32) return launch(one, one, four);
-    return false;
-}
-
-// The same with 64x64 tiles of the fp32 instruction.
-template <int EPI, int DW>
-static void launch_pair_da_narrow_dw(GemmArgs da, GemmArgs dw, hipStream_t s)
-{
-    const unsigned n_dw = place_narrow<DW>(dw), n = place_blocks<64, 64>(da);
-    dw.mean.first_block = n + n_dw;
-    EASGD_LAUNCH((gemm_da_narrow_dw_kernel<EPI, DW>), dim3(n + n_dw + dw.mean.blocks), dim3(256), 0, s, da, dw, n_dw);
-}
-
-// Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile of the fp32 matrix instruction; input gradients, a
+// Picks the tile shape.  Outputs at most 32 wide use a 128x32 tile of the fp32 matrix instruction, or as weight gradients
+// narrow_dw.h; small grids of the products whose rows are the minibatch the tiles of gemm_chain.h; input gradients, a
 // wide last layer and weight gradients the tiles of gemm_split.h where split_pick and split_dw_pays say so; everything else, and
 // whatever EASGD_OPT_GEMM_TILE forces, tiles of the fp32 instruction: 64x64 blocks (four per compute unit, so that the
 // epilogue of one overlaps the products of the others), for the products whose rows are the minibatch the 16-row tiles and
@@ -660,6 +581,10 @@ static inline bool mult4(size_t x) { return (x & 3u) == 0; }
 // and two (split_blocks_per_cu).  The 32-row ones leave room whatever their number (rounds with the rule on extra blocks /
 // as a launch of its own: 3072-99, 17, 30, 952 blocks 47.0 / 52.3 us; 3072-400, 32, 32, 2048 blocks 158 / 165; 2000-500, 16, 32,
 // 1024 blocks 91 / 95); 64x128: 3072-593, 3, 124, 420 blocks 79 / 84; 128x128 more than one per unit: 512-1000, 32, 200 198 / 191.
+// The tiles of gemm_chain.h, which a product of at most two and a half 64x64 tiles per unit may take instead, leave two or three
+// blocks per unit room and lend the rule's blocks their LDS, and still always have room: 625 drawn rounds that begin
+// with one, the rule as a launch of its own over the rule on extra blocks 1.00 to 1.22, median 1.07 (784-112-7, 25, 18 35.7 us /
+// 29.3; 3072-1504-1440-10, 3, 42 145.8 / 145.2).
 static bool forward_launch_has_room(const GemmArgs &a, bool vec, Form form)
 {
     const size_t cus = (size_t)num_cus();
