@@ -365,15 +365,19 @@ static ChainPick chain_pick(const GemmArgs &a, bool forward, bool vec)
     if (2 * blocks(64, 64) > 5 * cus) return CHAIN_NONE;
     const int sum = std::min(a.K, a.k_per_split), slabs = (sum + 63) / 64 * 64;
     struct Line { double a, d; };
+    // input gradients that rule out 128-bit loads on the 64x64 path take about twice as long there
+    const bool slow = !forward && !vec;
     // lines: r = 1, 2, ..; beyond the last one in proportion to it
     auto time = [&](int bm, int bn, int K, std::initializer_list<Line> lines) {
         const size_t r = (blocks(bm, bn) + cus - 1) / cus, n = std::min(r, lines.size());
         const Line &l = lines.begin()[n - 1];
+        // with more than four blocks per unit the chain tiles' loads, several times the 64x64 tile's per product, decide in long sums
+        // (3072->1554, 9 workers, 70 rows: five blocks of 16x64 take a gradient of 212 us to 247)
+        if (r > n && bm * bn < 64 * 64 && !slow) return 1e9;
         return (double)r / (double)n * (l.a + l.d * K);
     };
-    // input gradients that rule out 128-bit loads on the 64x64 path take about twice as long there
-    double best = 0.985 * (!forward && !vec ? time(64, 64, sum, {{3.54, 0.0437}, {3.19, 0.0744}, {4.91, 0.1050}})
-                                            : time(64, 64, sum, {{3.74, 0.01756}, {4.66, 0.03255}, {5.94, 0.0467}}));
+    double best = 0.985 * (slow ? time(64, 64, sum, {{3.54, 0.0437}, {3.19, 0.0744}, {4.91, 0.1050}})
+                                : time(64, 64, sum, {{3.74, 0.01756}, {4.66, 0.03255}, {5.94, 0.0467}}));
     ChainPick pick = CHAIN_NONE;
     auto consider = [&](ChainPick t, double us) {
         if (us < best) {
