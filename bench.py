@@ -356,23 +356,23 @@ def triad_ceiling(hip, n=488_000_000, reps=20):
 # them are dropped from the JSON line (traffic: null) when the running library reports another version than the one
 # that was profiled, or non-default launch options.
 TRAFFIC_PROFILES = {
-    ("elastic", False, 8, 61_000_000): (2_025_425.6 * 1024 * 2.000 + 2_144_531.6 * 1024 * 1.000,
+    ("elastic", False, 8, 61_000_000): (2_025_425.5 * 1024 * 2.000 + 2_144_531.5 * 1024 * 1.000,
                                         "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
-    ("elastic", True, 16, 61_000_000): (5_837_958.2 * 1024 * 2.000 + 7_863_341.6 * 1024 * 1.000,
+    ("elastic", True, 16, 61_000_000): (5_837_957.7 * 1024 * 2.000 + 7_863_314.7 * 1024 * 1.000,
                                         "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
-    ("sync_sgd", False, 8, 61_000_000): (1_906_280.9 * 1024 * 2.000 + 1_906_253.2 * 1024 * 1.000,
+    ("sync_sgd", False, 8, 61_000_000): (1_906_280.9 * 1024 * 2.000 + 1_906_253.7 * 1024 * 1.000,
                                          "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
-    ("async", False, 8, 61_000_000): (2_025_431.2 * 1024 * 2.000 + 2_144_531.3 * 1024 * 1.000,
+    ("async", False, 8, 61_000_000): (2_025_431.3 * 1024 * 2.000 + 2_144_531.3 * 1024 * 1.000,
                                       "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
-    ("hogwild", False, 8, 61_000_000): (2_869_045.6 * 1024 * 2.000 + 9_531_250.0 * 1024 * 1.000,
+    ("hogwild", False, 8, 61_000_000): (2_869_132.3 * 1024 * 2.000 + 9_531_250.0 * 1024 * 1.000,
                                         "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
-    ("elastic_bf16", False, 8, 61_000_000): (1_548_869.4 * 1024 * 2.000 + 2_144_531.8 * 1024 * 1.000,
+    ("elastic_bf16", False, 8, 61_000_000): (1_548_869.4 * 1024 * 2.000 + 2_144_531.7 * 1024 * 1.000,
                                              "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
-    ("elastic_bf16", True, 16, 61_000_000): (3_931_723.6 * 1024 * 2.000 + 5_957_033.5 * 1024 * 1.000,
+    ("elastic_bf16", True, 16, 61_000_000): (3_931_723.8 * 1024 * 2.000 + 5_957_033.7 * 1024 * 1.000,
                                              "profiles/elastic_update_cfg4_cfg5_hbm_traffic.md"),
-    ("grad", "cfg2"): (131_409.1 * 1024 * 2.000 + 149_337.0 * 1024 * 1.000, "profiles/easgd_grad_cfg2_hbm_traffic.md"),
+    ("grad", "cfg2"): (131_544.7 * 1024 * 2.000 + 149_337.0 * 1024 * 1.000, "profiles/easgd_grad_cfg2_hbm_traffic.md"),
 }
-TRAFFIC_PROFILED_VERSION = 511      # easgd_version() of the library the summaries above were taken with
+TRAFFIC_PROFILED_VERSION = 512      # easgd_version() of the library the summaries above were taken with
 
 
 def traffic_fields(hip, key):
