@@ -274,8 +274,9 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     // The large tiles take one split after the other, and load B's first step in the first slots of the next slab.  In bursts (a
     // split within six slots, then its stores and loads) / spread, us: forward 3072->2048, 8 workers, 256 rows 150 / 141; input
     // gradient 2048->2048, 32, 100 199 / 193; forward 784->1024, 16, 128 in 64x128 tiles 27.6 / 26.6, 1024->1024, 16, 128 (input
-    // gradient) 32.2 / 31.8.  What is left of the first of these over its matrix instructions (83 us) is the loads and LDS
-    // stores: without loads from memory it takes 125, without LDS stores 116, without either and with a third of the LDS reads 102.
+    // gradient) 32.2 / 31.8.  What the first of these takes over its matrix instructions (83 us) is the loads and LDS stores (in a
+    // kernel trace on another box, as built 127): without loads from memory 125, without LDS stores 116, without either and with a
+    // third of the LDS reads 102.
     // In the small tiles a slab's twelve or six slots are shorter than a trip to memory, and where the operands come from far or few
     // wavefronts share a compute unit, what counts is that the trips of A and B overlap: both loads go out before either is
     // waited for.  Time over that of the bursts (products of 64 to 3072 inputs, 48 to 2048 outputs, 2 to 32 workers, 16 to 256 rows):
@@ -286,7 +287,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     constexpr int ITEMS = KS * TM, SLOTS = 6 * ITEMS, SPLITS = KS + IT, SPAN = SLOTS / SPLITS;
     constexpr bool FORWARD = A_LAYOUT == K_CONTIG && B_LAYOUT == MN_CONTIG;
     constexpr bool TINY = ITEMS == 1;                                    // the 32x32 tile
-    constexpr bool B_BEHIND = TINY || EARLY;                    // B's first step is loaded right behind its split
+    constexpr bool B_BEHIND = TINY || EARLY;                             // B's first step is loaded right behind its split
     constexpr int RATE = SPAN >= 12 ? 1 : 4;                             // pieces of a load per slot, eight in all
     static_assert(!EARLY || SLOTS == 12, "the 64x64 and 32x128 tiles");
     static_assert(SLOTS % SPLITS == 0 && SPAN >= 3, "a split's three stores come before the end of the slab");
@@ -295,6 +296,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &p, const unsigned bi
     constexpr auto split_at = [](int n) { return n + 1 == SPLITS ? -2 : KS == 1 ? n : n - 1; };
     constexpr auto first_slot = [](int n) { return TINY ? (FORWARD || n == 1 ? 0 : 1) : EARLY ? (KS == 1 ? 6 * n : 3 * n) : SPAN * n; };
     constexpr auto slots_of = [](int) { return TINY ? (FORWARD ? 6 : 5) : EARLY ? (KS == 1 ? 4 : 3) : SPAN; };
+    static_assert(KS == 1 || (first_slot(0) + slots_of(0) <= 6 * TM && first_slot(SPLITS - 1) >= 6 * TM), "the two steps of B");
     // (A second set of raw registers, so that a slab's loads have two slabs to arrive in, is slower in every tile: 64x128 DW 38.1 us
     // -> 51.0, 32x32 input gradient 777->333 7.9 -> 8.7.)
     RawA ra;
